@@ -148,37 +148,35 @@ __device__ __forceinline__ int source_texel_exact(int x, int y, int z, int logn)
 // towards z then y), for a direction given as exact binary32 integers.
 //
 // The fast path works on x = q / n + 1 + e, q = h sc / D + h the exact texel
-// coordinate and e = 2^-22, so that x lies in (1, 2) and the bits of its
+// coordinate and e = 2^-23, so that x lies in (1, 2) and the bits of its
 // significand are q's: the top log2(n) bits are floor(q + n e), the rest its
 // fraction.  sc and |ma| = 2 D are exact, v_rcp_f32 is within one ulp
 // (2^-23 relative), so sc / |ma| (at most 1/2) is within 2^-24 of the exact
 // ratio, and the fma that adds 3/2 + e rounds once (at most 2^-24): x is
-// within 2^-23 = e / 2 of its exact value.  If the fraction bits of both
-// coordinates are at least 4 (the fraction of n (x - 1) is at least 2 n e),
-// the exact q lies strictly between the same two integers, so the top bits
-// are the exact floor (in [0, n - 1]); otherwise the exact form replaces the
-// result.  An estimate at or above 2 has fraction bits below 4 (x < 2 + 3/2 e)
-// and also takes the exact form.
+// within e of its exact value.  If the fraction bits of both coordinates are
+// at least 2 (the fraction of x is at least 2 e), the exact q lies at or above
+// the same integer, and below the next one since x does; the limit 3 also
+// sends every q that is an integer itself (x at most 2 e above it) to the
+// exact form.  An estimate at or above 2 (at most 2 + 2 e) has fraction bits
+// below 3 and takes the exact form, too.
 //
 // With exact components the binary32 face comparison can differ from the
 // exact one only at an exact tie broken the other way; the exact major
-// component is then an in-face coordinate equal to +-D, whose x is within
-// e / 2 of 1 + e or 2 + e, where the fraction test fails.  A zero direction
-// gives NaN, whose fraction bits are zero for n >= 2: the exact form.
+// component is then an in-face coordinate equal to +-D, an integer q, where
+// the fraction test fails.  A zero direction gives NaN, whose fraction bits
+// are zero for n >= 2: the exact form.
 // 127 (n^2 + n): the offset that the significand bits of x add to a flat
 // index (see source_texel_biased).
 __device__ __forceinline__ unsigned texel_bias(int logn) {
   return (127u << (2 * logn)) + (127u << logn);
 }
 
-// Strip layout of a source map (n >= 4): global rows R = face n + i are
-// grouped in strips of four, each strip stored column by column, so texel
-// (R, j) sits at ((R >> 2) << (log2 n + 2)) + 4 j + (R & 3) and a 4-row x
-// 8-column patch (32 binary32 values) shares one 128-byte cache line.  A
-// rotated 8 x 8 patch of destination texels then touches about half the
-// lines it touches in row-major order.
-__device__ __forceinline__ unsigned strip_offset(unsigned R, unsigned j, int logn) {
-  return ((R >> 2) << (logn + 2)) + (j << 2) + (R & 3u);
+// Column-strip layout of a source map (n >= 8): every face is cut into strips
+// of eight columns, stored one after the other row by row, so texel (face, i,
+// j) sits at face n^2 + (j >> 3) 8n + 8 i + (j & 7) and a 4-row x 8-column
+// patch is one 128-byte cache line.
+__device__ __forceinline__ unsigned strip_offset(unsigned face, unsigned i, unsigned j, int logn) {
+  return (face << (2 * logn)) + ((j >> 3) << (logn + 3)) + (i << 3) + (j & 7u);
 }
 // 127 n^2: the offset of the strip index built from significand bits.
 __device__ __forceinline__ unsigned strip_bias(int logn) { return 127u << (2 * logn); }
@@ -186,20 +184,20 @@ __device__ __forceinline__ unsigned strip_bias(int logn) { return 127u << (2 * l
 // Fast path of the map (see source_texel_biased for the error analysis):
 // significands of x for both in-face coordinates, the face, and whether the
 // top bits are exact floors.
+constexpr float kTexelOff = 1.5f + 0x1p-23f;
+constexpr unsigned kTexelLimit = 3u;  // a fraction below it is not sure
 struct FastTexel {
   unsigned bs, bt, face;
   bool ok;
 };
 __device__ __forceinline__ FastTexel fast_texel(float fx, float fy, float fz, int logn) {
   const float r = __builtin_amdgcn_rcpf(fabsf(__builtin_amdgcn_cubema(fx, fy, fz)));
-  constexpr float kOff = 1.5f + 0x1p-22f;
   FastTexel t;
-  t.bs = __float_as_uint(__builtin_fmaf(__builtin_amdgcn_cubesc(fx, fy, fz), r, kOff));
-  t.bt = __float_as_uint(__builtin_fmaf(__builtin_amdgcn_cubetc(fx, fy, fz), r, kOff));
+  t.bs = __float_as_uint(__builtin_fmaf(__builtin_amdgcn_cubesc(fx, fy, fz), r, kTexelOff));
+  t.bt = __float_as_uint(__builtin_fmaf(__builtin_amdgcn_cubetc(fx, fy, fz), r, kTexelOff));
   t.face = unsigned(__builtin_amdgcn_cubeid(fx, fy, fz));
-  // fraction bits at least 4 in both: some bit of [2, 23 - log2 n) set in each
-  const unsigned fr = ((1u << (23 - logn)) - 1u) & ~3u;
-  t.ok = min(t.bs & fr, t.bt & fr) != 0u;
+  const unsigned fr = (1u << (23 - logn)) - 1u;
+  t.ok = min(t.bs & fr, t.bt & fr) >= kTexelLimit;
   return t;
 }
 
@@ -215,27 +213,57 @@ __device__ __forceinline__ unsigned source_texel_biased(float fx, float fy, floa
   return at;
 }
 
-// Strip offset (strip_offset) of the source texel plus strip_bias(logn), for
-// n >= 4; in [strip_bias, strip_bias + 6 n^2).
+// (a & mask) | (b & ~mask) in one v_bfi_b32 (where the mask is loop-invariant
+// the compiler would otherwise not see its complement).
+__device__ __forceinline__ unsigned bit_select(unsigned mask, unsigned a, unsigned b) {
+  unsigned r;
+  asm("v_bfi_b32 %0, %1, %2, %3" : "=v"(r) : "v"(mask), "v"(a), "v"(b));
+  return r;
+}
+
+// Strip offset (strip_offset) inside its face, plus strip_bias(logn), of the
+// texel whose column and row are the top significand bits of bs and bt: the
+// column's low three bits, the row above them, the column's others on top.
+// The shifts leave fraction bits below and the exponent's 127 above each field,
+// which the selections drop (but for the exponent of the topmost: the bias).
+__device__ __forceinline__ unsigned strip_index(unsigned bs, unsigned bt, int logn) {
+  const int sh = 23 - logn;
+  const unsigned lo = bit_select(7u, bs >> sh, bt >> (sh - 3));
+  return bit_select(~((8u << logn) - 1u), bs >> (sh - logn), lo);
+}
+
+// Strip offset plus strip_bias(logn) by the exact form: the face by the same
+// comparisons as source_texel_exact (every component is an exact integer),
+// and the floor of q = h (sc + D) / D from the nearest integer to its binary32
+// estimate (far less than half a texel off): q >= c exactly when
+// n sc - (2c - n) D >= 0, and the fma rounds that difference once, which
+// keeps its sign.
+__device__ __forceinline__ unsigned source_texel_strip_exact(float x, float y, float z, int logn) {
+  const float n = float(1 << logn), h = 0.5f * n;
+  const float ax = fabsf(x), ay = fabsf(y), az = fabsf(z);
+  const bool px = ax >= fmaxf(ay, az);
+  const bool py = !px && ay >= az;
+  const float D = fmaxf(fmaxf(fmaxf(ax, ay), az), 1.0f);
+  const bool neg = (px ? x : (py ? y : z)) < 0.0f;
+  const float sc = px ? (neg ? z : -z) : (!py && neg ? -x : x);
+  const float tc = py ? (neg ? -z : z) : -y;
+  const unsigned face = (px ? 0u : (py ? 2u : 4u)) + unsigned(neg);
+  const float hr = h * __builtin_amdgcn_rcpf(D);
+  const float cs = __builtin_rintf(__builtin_fmaf(sc, hr, h));
+  const float ct = __builtin_rintf(__builtin_fmaf(tc, hr, h));
+  const int j = int(cs) - int(__builtin_fmaf(n - 2.0f * cs, D, n * sc) < 0.0f);
+  const int i = int(ct) - int(__builtin_fmaf(n - 2.0f * ct, D, n * tc) < 0.0f);
+  const int last = (1 << logn) - 1;
+  return strip_offset(face, unsigned(min(max(i, 0), last)), unsigned(min(max(j, 0), last)), logn) +
+         strip_bias(logn);
+}
+
+// Strip offset of the source texel plus strip_bias(logn), for n >= 8; in
+// [strip_bias, strip_bias + 6 n^2).
 __device__ __forceinline__ unsigned source_texel_strip(float fx, float fy, float fz, int logn) {
   const FastTexel t = fast_texel(fx, fy, fz, logn);
-  const int sh = 23 - logn;
-  // low part 4 j + (i & 3): column bits from bs, the row's two low bits from
-  // bt's top part 127 n + i (127 n is a multiple of 4 for n >= 4)
-  const unsigned lo = ((t.bt >> sh) & 3u) | ((t.bs >> (sh - 2)) & ~3u);
-  // high part (strip (face + 127) n / 4 + (i >> 2)) << (log2 n + 2): the bits
-  // of ((face + 127) n + i) n above log2 n + 2 (bt shifted to that scale
-  // carries fraction bits below log2 n, which the mask drops)
-  const unsigned R = (t.face << (2 * logn)) + (t.bt >> (sh - logn));
-  const unsigned hi = ~((4u << logn) - 1u);
-  // (R & hi) | (lo & ~hi) in one v_bfi_b32 (the mask is loop-invariant, so the
-  // compiler would otherwise not see its complement and emit two operations)
-  unsigned at;
-  asm("v_bfi_b32 %0, %1, %2, %3" : "=v"(at) : "s"(hi), "v"(R), "v"(lo));
-  if (!t.ok) {
-    const unsigned q = unsigned(source_texel_exact(int(fx), int(fy), int(fz), logn));
-    at = strip_offset(q >> logn, q & ((1u << logn) - 1u), logn) + strip_bias(logn);
-  }
+  unsigned at = (t.face << (2 * logn)) + strip_index(t.bs, t.bt, logn);
+  if (!t.ok) at = source_texel_strip_exact(fx, fy, fz, logn);
   return at;
 }
 

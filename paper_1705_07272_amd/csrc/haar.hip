@@ -129,9 +129,9 @@ __global__ __launch_bounds__(64) void haar_inv_coarse(const float* coef, float* 
 }
 
 // grid: count * 6 * G * G; the tile sum comes from coef[face][0] when G == 1,
-// else from stage[face * n * n + ty * rs + tx * cs].  With `strips` (n >= 4)
-// the pixels are written in strips of four rows, each strip column by column:
-// row r, column c of a square at ((r >> 2) << (log2 n + 2)) + 4 c + (r & 3).
+// else from stage[face * n * n + ty * rs + tx * cs].  With `strips` (n >= 8)
+// the pixels are written in strips of eight columns, each row by row
+// (strip_offset): row r, column c of a square at (c >> 3) 8n + 8 r + (c & 7).
 __global__ __launch_bounds__(kThreads) void haar_inv_tiles(const float* coef, const float* stage,
                                                            float* pix, int n, int logq, int G,
                                                            int64_t rs, int64_t cs, bool strips) {
@@ -167,9 +167,8 @@ __global__ __launch_bounds__(kThreads) void haar_inv_tiles(const float* coef, co
   if (strips) {
     // consecutive threads write consecutive elements of a strip
     for (int e = threadIdx.x; e < Q * Q; e += kThreads) {
-      const int st = e >> (logq + 2), c = (e >> 2) & (Q - 1), rl = e & 3;
-      const int r = 4 * st + rl;
-      dst[int64_t((row0 + r) >> 2) * 4 * n + 4 * (col0 + c) + rl] = lds[r * Q + c];
+      const int r = (e >> 3) & (Q - 1), c = ((e >> (logq + 3)) << 3) + (e & 7);
+      dst[int64_t((col0 + c) >> 3) * 8 * n + 8 * (row0 + r) + (c & 7)] = lds[r * Q + c];
     }
   } else {
     for (int e = threadIdx.x; e < Q * Q; e += kThreads) {
@@ -197,11 +196,11 @@ int launch_haar_forward(const float* pix, float* coef, int n, int64_t squares, h
 int launch_haar_inverse(const float* coef, float* pix, int n, int64_t squares, hipStream_t s,
                         bool strips) {
   if (squares == 0) return RRT_OK;
-  if (n < 4) strips = false;
+  if (n < 8) strips = false;
   const int Q = n < kTile ? n : kTile;
   const int G = n / Q;
-  // first texel of each output tile (also in strips: tile rows start strips)
-  const int64_t rs = int64_t(Q) * n, cs = strips ? 4 * Q : Q;
+  // first texel of each output tile (row and column multiples of Q)
+  const int64_t rs = strips ? 8 * Q : int64_t(Q) * n, cs = strips ? int64_t(Q) * n : Q;
   if (G > 1) {
     hipLaunchKernelGGL(haar_inv_coarse, dim3(unsigned(squares)), dim3(64), 0, s, coef, pix, n,
                        G, rs, cs);

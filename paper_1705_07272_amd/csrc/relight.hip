@@ -14,8 +14,8 @@
 // Work decomposition (one wave per vertex, all frames; no workgroup barrier):
 //   * the faces touched by the vertex's transport row are processed, each as
 //     G x G blocks of Q x Q texels (Q = min(n, 32));
-//   * per block, lane (ty, tx) gathers texel (8a + ty, 8b + tx) of each 8 x 8
-//     patch (a compact patch per load instruction) into an LDS image, then
+//   * per block, a lane gathers one texel of each 8 x 8 patch (a compact patch
+//     per load instruction) into an LDS image, then
 //     runs the levels of its own 4 x 4 tile in registers and the levels up to
 //     the block with lane shuffles, in place (the coefficient of a block of
 //     side B at its corner offset by B/2 for H/V/D);
@@ -386,6 +386,159 @@ __device__ __forceinline__ void tile_level_above(float& s, float* img, int lane,
   if constexpr (4 * HT <= TS) tile_level_above<2 * HT, TS, T, STRIDE>(s, img, lane, tx, ty, owns_tile);
 }
 
+// ---------------------------------------------------------------------------
+// Gather of a 32 x 32 block in quarters of 16 x 16 texels (cube map, n >= 32).
+// A quarter whose texels all lie in one source face needs no cube-map
+// instructions and no face index: its in-face coordinates and major component
+// are components of the direction.  Of the quarters of a randomly rotated face
+// 55 % are so at n = 64, 76 % at 128, 88 % at 256.
+//
+// What bounds it: vector instruction issue (a timing copy without the loads
+// takes 0.90 of the time) closely followed by the texture path.  Cycles per
+// wave instruction and SIMD, measured on independent chains: add, mul, fma,
+// and, or, shifts and moves with vector or inline operands 2.7 to 3.3, any
+// with a scalar operand and all three-operand integer, min, compare, convert
+// and cube-map instructions 4.4 to 4.8, v_rcp_f32 8.4; one texel of a uniform
+// quarter takes 13 instructions, 48 cycles (21 and 80 with the cube-map
+// instructions).  Cycles per load instruction and CU of rotated 8 x 8 patches: 24
+// with the lanes in Morton order and 4 x 8 texels of the map in a cache line,
+// 32 with the lanes row by row.  Copying a quarter's footprint to LDS and
+// gathering there was slower: 0.78 against 0.60 ms on the launch below (each
+// quarter waits for its copy, and fewer waves fit).
+//
+// Calls, before (one way for every texel, lanes row by row) and after: lighting
+// step with 50,000 vertices, n = 128, 256 coefficients, 0.639 -> 0.584 ms; 200,000
+// vertices, n = 256, 8.14 -> 7.21 ms; 12,500 vertices x 64 frames, n = 128, 9.03 ->
+// 8.07 ms.
+// ---------------------------------------------------------------------------
+constexpr int kMixed = 6;  // quarter_face: several faces
+
+// Texel of a lane in an 8 x 8 patch, Morton order: 16 consecutive lanes take a
+// 4 x 4 block of texels.
+__device__ __forceinline__ int morton_x(int lane) {
+  return (lane & 1) | ((lane >> 1) & 2) | ((lane >> 2) & 4);
+}
+__device__ __forceinline__ int morton_y(int lane) { return morton_x(lane >> 1); }
+
+// Source face of quarter q (2 x 2) of block kb of a face, or kMixed: a source
+// face is a convex cone, so four corner texels in one face put every texel of
+// the quarter there.  (Texels on the face's boundary may count to a neighbour
+// by the exact tie rule; they fail the fraction test and take the exact form.)
+template <int LOGN>
+__device__ __forceinline__ int quarter_face(const FaceAxes& ax, int kb, int q, bool rot_ok) {
+  constexpr int n = 1 << LOGN, g = LOGN - 5;  // log2 blocks per side
+  const int by = kb >> g, bx = kb & ((1 << g) - 1);
+  const float U = float(2 * (32 * bx + 16 * (q & 1)) + 1 - n);
+  const float V = float(2 * (32 * by + 16 * (q >> 1)) + 1 - n);
+  const float3 zero3 = make_float3(0.0f, 0.0f, 0.0f);
+  float3 d = dir_mad(ax.mU, U, ax.mV, V, dir_add(ax.mN, float(n), zero3));
+  const float face = __builtin_amdgcn_cubeid(d.x, d.y, d.z);
+  bool one = rot_ok;
+#pragma unroll
+  for (int c = 0; c < 4; ++c) {
+    // corners (0, 0), (15, 0), (15, 15), (0, 15)
+    if (c == 1) d = dir_add(ax.mU, 30.0f, d);
+    if (c == 2) d = dir_add(ax.mV, 30.0f, d);
+    if (c == 3) d = dir_add(ax.mU, -30.0f, d);
+    one = one && __builtin_amdgcn_cubeid(d.x, d.y, d.z) == face &&
+          fabsf(__builtin_amdgcn_cubema(d.x, d.y, d.z)) >= 1.0f;
+  }
+  return one ? int(face) : kMixed;
+}
+
+__device__ __forceinline__ unsigned min3_u16(unsigned acc, unsigned a, unsigned b) {
+  asm("v_min3_u16 %0, %0, %1, %2" : "+v"(acc) : "v"(a), "v"(b));
+  return acc;  // the low half; the high half is acc's
+}
+
+// Four texels (patches at 0 and 8 columns and rows) of a lane in a quarter
+// inside source face 2 A or 2 A + 1.  The coordinates are those of fast_texel,
+// doubled (the same significands): sc / |m| and tc / |m| with the face's signs
+// folded into the major component's: +X and -X (-z/x, -y/|x|), +Y and -Y
+// (x/|y|, z/y), +Z and -Z (x/z, -y/|z|).
+template <int LOGN, int A>
+__device__ __forceinline__ void face_texels(unsigned (&bs)[4], unsigned (&bt)[4], float3 d0,
+                                            float3 us, float3 vs) {
+#pragma unroll
+  for (int k = 0; k < 4; ++k) {
+    float3 d = d0;
+    if (k >> 1) d = make_float3(d.x + vs.x, d.y + vs.y, d.z + vs.z);
+    if (k & 1) d = make_float3(d.x + us.x, d.y + us.y, d.z + us.z);
+    const float r = __builtin_amdgcn_rcpf(A == 0 ? d.x : (A == 1 ? d.y : d.z));
+    const float s = A == 0 ? __builtin_fmaf(-d.z, r, 2.0f * kTexelOff)
+                           : __builtin_fmaf(d.x, A == 1 ? fabsf(r) : r, 2.0f * kTexelOff);
+    const float t = A == 1 ? __builtin_fmaf(d.z, r, 2.0f * kTexelOff)
+                           : __builtin_fmaf(-d.y, fabsf(r), 2.0f * kTexelOff);
+    bs[k] = __float_as_uint(s);
+    bt[k] = __float_as_uint(t);
+  }
+}
+
+// A lane's four texels of a quarter (face: uniform; d0: its direction in the
+// first patch).
+template <int LOGN>
+__device__ __forceinline__ void gather_quarter(float (&val)[4], int face, float3 d0, float3 us,
+                                               float3 vs, const float* map) {
+  constexpr int n2 = 1 << (2 * LOGN);
+  unsigned bs[4], bt[4];
+  if (face != kMixed) {
+    if (face < 2)
+      face_texels<LOGN, 0>(bs, bt, d0, us, vs);
+    else if (face < 4)
+      face_texels<LOGN, 1>(bs, bt, d0, us, vs);
+    else
+      face_texels<LOGN, 2>(bs, bt, d0, us, vs);
+    // the face's part of the map; the exponent of doubled coordinates adds n^2
+    const __amdgpu_buffer_rsrc_t src =
+        source_resource(map + face * n2, n2, strip_bias(LOGN) + unsigned(n2));
+#pragma unroll
+    for (int k = 0; k < 4; ++k) val[k] = load_src(src, strip_index(bs[k], bt[k], LOGN));
+  } else {
+    const __amdgpu_buffer_rsrc_t src = source_resource(map, 6 * n2, strip_bias(LOGN));
+#pragma unroll
+    for (int k = 0; k < 4; ++k) {
+      float3 d = d0;
+      if (k >> 1) d = make_float3(d.x + vs.x, d.y + vs.y, d.z + vs.z);
+      if (k & 1) d = make_float3(d.x + us.x, d.y + us.y, d.z + us.z);
+      const FastTexel t = fast_texel(d.x, d.y, d.z, LOGN);
+      bs[k] = t.bs;
+      bt[k] = t.bt;
+      val[k] = load_src(src, (t.face << (2 * LOGN)) + strip_index(t.bs, t.bt, LOGN));
+    }
+  }
+  // texels too close to a texel boundary to be sure of take the exact form
+  constexpr unsigned kFraction = (1u << (23 - LOGN)) - 1u;
+  bool close;
+  if constexpr (LOGN <= 7) {
+    // at least 16 fraction bits: the low halves
+    unsigned acc = 0xffffu;
+#pragma unroll
+    for (int k = 0; k < 4; ++k) acc = min3_u16(acc, bs[k], bt[k]);
+    close = (acc & 0xffffu) < kTexelLimit;
+  } else {
+    unsigned acc = ~0u;
+#pragma unroll
+    for (int k = 0; k < 4; ++k) acc = min(min(acc, bs[k] & kFraction), bt[k] & kFraction);
+    close = acc < kTexelLimit;
+  }
+  if (__ballot(close)) {
+    const __amdgpu_buffer_rsrc_t src = source_resource(map, 6 * n2, strip_bias(LOGN));
+    unsigned todo = 0;
+#pragma unroll
+    for (int k = 0; k < 4; ++k)
+      todo |= min(bs[k] & kFraction & 0xffffu, bt[k] & kFraction & 0xffffu) < kTexelLimit ? 1u << k : 0u;
+#pragma unroll 1
+    while (todo) {
+      const int k = __builtin_ctz(todo);
+      const float3 d = dir_add(us, float(k & 1), dir_add(vs, float(k >> 1), d0));
+      const float x = load_src(src, source_texel_strip_exact(d.x, d.y, d.z, LOGN));
+#pragma unroll
+      for (int j = 0; j < 4; ++j) val[j] = j == k ? x : val[j];
+      todo &= todo - 1;
+    }
+  }
+}
+
 template <int CTRL>
 __device__ __forceinline__ float dpp_mov(float x) {
   return __int_as_float(__builtin_amdgcn_mov_dpp(__float_as_int(x), CTRL, 0xF, 0xF, true));
@@ -539,9 +692,12 @@ __device__ __forceinline__ int classify(int idx, int logn, int G, unsigned faces
 // spilled): 0.430 -> 0.411 ms on the benchmark launch against 4 waves
 // unspilled; the lat-long variant held to 6 waves spills more and runs
 // slower, so it keeps its 5.
-template <int Q, bool CHAIN, bool BRDF, bool LL>
-__global__ __launch_bounds__(kThreads, CHAIN ? 5 : 1) void relight_kernel(RelightParams p) {
+// LOGN: log2 n where the block is gathered in quarters (cube map, exact
+// rotation, n >= 32), else 0 and n is a parameter.
+template <int Q, bool CHAIN, bool BRDF, bool LL, int LOGN>
+__global__ __launch_bounds__(kThreads, CHAIN || LOGN ? 5 : 1) void relight_kernel(RelightParams p) {
   constexpr int NF = LL ? 2 : 6;  // faces (squares) of the map
+  constexpr bool QUARTERS = LOGN > 0;
   // Blocks holding no listed entry of their own only feed the levels above
   // them through their sum: with SUM_ONLY such a block skips the image, the
   // levels inside it and the entry scan (with CHAIN it also skips the chain
@@ -560,13 +716,13 @@ __global__ __launch_bounds__(kThreads, CHAIN ? 5 : 1) void relight_kernel(Religh
   const int lane = threadIdx.x;
   const int64_t v = p.order ? int64_t(p.order[blockIdx.x]) : int64_t(blockIdx.x);
   if (v < 0 || v >= p.nvert) return;  // not a permutation entry: skipped (uniform)
-  const int logn = p.logn;
+  const int logn = QUARTERS ? LOGN : p.logn;
   const int n = 1 << logn;
   const int G = n >> LOGQ;  // blocks per face side
   const int G2 = G * G;
   const int FG = p.group_faces;
-  // the cube map's source map is in strips of four rows for n >= 4 (Q >= 4)
-  constexpr bool STRIPS = Q >= 4 && !LL;
+  // the cube map's source map is in strips of eight columns for n >= 8 (Q >= 8)
+  constexpr bool STRIPS = Q >= 8 && !LL;
   const __amdgpu_buffer_rsrc_t src = source_resource(
       p.src, NF * (n << logn),
       LL ? 0u : (STRIPS ? strip_bias(logn) : texel_bias(logn)));
@@ -645,6 +801,14 @@ __global__ __launch_bounds__(kThreads, CHAIN ? 5 : 1) void relight_kernel(Religh
 #pragma unroll
       for (int k = 0; k < 9; ++k) R.m[k] = __builtin_amdgcn_readfirstlane(R.m[k]);
     }
+    // Entries of a rotation are at most one (2^k quantised): the directions
+    // are exact.  With anything larger no quarter counts as uniform.
+    [[maybe_unused]] bool rot_ok = true;
+    if constexpr (QUARTERS) {
+      const int one = (1 << scale_bits(logn)) + 2;
+#pragma unroll
+      for (int k = 0; k < 9; ++k) rot_ok = rot_ok && R.m[k] <= one && R.m[k] >= -one;
+    }
     Acc acc = {0.0f, 0.0f};
 
     for (int grp = 0; grp < ngroups; ++grp) {
@@ -708,8 +872,19 @@ __global__ __launch_bounds__(kThreads, CHAIN ? 5 : 1) void relight_kernel(Religh
         const int hn = n >> 1;
         const float3 h0 = dir_mad(ax.mU, float(2 * tx + 1 - hn), ax.mV, float(2 * ty + 1 - hn),
                                   dir_add(ax.mN, float(hn), zero3));
-        for (int by = 0; by < G; ++by) {
-          for (int bx = 0; bx < G; ++bx, ++gi) {
+        // quarters: this lane's texel of an 8 x 8 patch in the face's first
+        // block, and the steps of 8 texels along both axes
+        [[maybe_unused]] float3 s0, us, vs;
+        [[maybe_unused]] int quarters = 0;
+        if constexpr (QUARTERS) {
+          s0 = dir_mad(ax.mU, float(2 * morton_x(lane) + 1 - n), ax.mV,
+                       float(2 * morton_y(lane) + 1 - n), dir_add(ax.mN, float(n), zero3));
+          us = dir_add(ax.mU, 16.0f, zero3);
+          vs = dir_add(ax.mV, 16.0f, zero3);
+        }
+        for (int kb = 0; kb < G2; ++kb, ++gi) {
+          {
+            const int by = kb >> (logn - LOGQ), bx = kb & (G - 1);
             // entries past the list may fall in any block: then every block is full
             bool full = true;
             if constexpr (SUM_ONLY)
@@ -807,6 +982,29 @@ __global__ __launch_bounds__(kThreads, CHAIN ? 5 : 1) void relight_kernel(Religh
                   img[(r0 + 1) * STRIDE + c0] = o.z;
                   img[(r0 + 1) * STRIDE + c0 + 1] = o.w;
                 }
+              }
+            } else if constexpr (QUARTERS) {
+              // 16 blocks at a time, each lane looks at one of their quarters
+              if ((kb & 15) == 0)
+                quarters = quarter_face<LOGN>(ax, kb + (lane >> 2), lane & 3, rot_ok);
+              const float3 rb = dir_add(us, float(4 * bx), dir_add(vs, float(4 * by), s0));
+              float val[4][4];
+#pragma unroll
+              for (int q = 0; q < 4; ++q) {
+                const float3 d0 =
+                    dir_add(us, float(2 * (q & 1)), dir_add(vs, float(2 * (q >> 1)), rb));
+                gather_quarter<LOGN>(val[q], __builtin_amdgcn_readlane(quarters, 4 * (kb & 15) + q),
+                                     d0, us, vs, p.src);
+              }
+              if (full) {
+#pragma unroll
+                for (int q = 0; q < 4; ++q)
+#pragma unroll
+                  for (int k = 0; k < 4; ++k)
+                    img[(16 * (q >> 1) + 8 * (k >> 1) + morton_y(lane)) * STRIDE + 16 * (q & 1) +
+                        8 * (k & 1) + morton_x(lane)] = val[q][k];
+              } else {
+                lane_sum = tile_sum<4>(val);
               }
             } else if (owns_tile) {
             // Gather in TS x TS patches of adjacent texels (one load instruction
@@ -988,11 +1186,11 @@ __global__ void source_blocks_kernel(const float* __restrict__ src, int logn,
   const int q = blockIdx.x * blockDim.x + threadIdx.x;
   if (q >= 6 << (2 * hl)) return;
   const int f = q >> (2 * hl), bi = (q >> hl) & ((1 << hl) - 1), bj = q & ((1 << hl) - 1);
-  // the source map is in strips of four rows (n >= 32 here): the block's
-  // two rows share a strip, its columns are four elements apart
-  const unsigned at = strip_offset(unsigned((f << logn) + 2 * bi), unsigned(2 * bj), logn);
-  const float a = src[at], b = src[at + 4];
-  const float c = src[at + 1], d = src[at + 5];
+  // the source map is in strips of eight columns (n >= 32 here): the block's
+  // two rows are eight elements apart
+  const unsigned at = strip_offset(unsigned(f), unsigned(2 * bi), unsigned(2 * bj), logn);
+  const float a = src[at], b = src[at + 1];
+  const float c = src[at + 8], d = src[at + 9];
   blocks[q] = make_float4(0.5f * ((a + b) + (c + d)), 0.5f * ((a - b) + (c - d)),
                           0.5f * ((a + b) - (c + d)), 0.5f * ((a - b) - (c - d)));
 }
@@ -1132,7 +1330,7 @@ __global__ void rotate_pixels(const float* __restrict__ src, const float* __rest
   dst[int64_t(r) * 6 * per_face + q] = src[min(at, unsigned(6 * per_face - 1))];
 }
 
-template <int Q, bool CHAIN = false, bool BRDF = false, bool LL = false>
+template <int Q, bool CHAIN = false, bool BRDF = false, bool LL = false, int LOGN = 0>
 int launch_q(const RelightParams& prm_in, int64_t nvert, hipStream_t s) {
   RelightParams prm = prm_in;
   const int G = (1 << prm.logn) / Q;
@@ -1142,19 +1340,24 @@ int launch_q(const RelightParams& prm_in, int64_t nvert, hipStream_t s) {
     prm.ll_tab_off = int(lds);
     lds += size_t(latlong_grid_floats(1 << prm.logn)) * 4;
   }
-  hipLaunchKernelGGL((relight_kernel<Q, CHAIN, BRDF, LL>), dim3(unsigned(nvert)),
+  hipLaunchKernelGGL((relight_kernel<Q, CHAIN, BRDF, LL, LOGN>), dim3(unsigned(nvert)),
                      dim3(kThreads), lds, s, prm);
   return check_launch("relight_kernel");
 }
 
 template <bool BRDF>
 int launch_size(const RelightParams& prm, int n, int64_t nvert, hipStream_t s) {
-  switch (n < kBlock ? n : kBlock) {
+  switch (n) {
     case 2: return launch_q<2, false, BRDF>(prm, nvert, s);
     case 4: return launch_q<4, false, BRDF>(prm, nvert, s);
     case 8: return launch_q<8, false, BRDF>(prm, nvert, s);
     case 16: return launch_q<16, false, BRDF>(prm, nvert, s);
-    default: return launch_q<kBlock, false, BRDF>(prm, nvert, s);
+    case 32: return launch_q<kBlock, false, BRDF, false, 5>(prm, nvert, s);
+    case 64: return launch_q<kBlock, false, BRDF, false, 6>(prm, nvert, s);
+    case 128: return launch_q<kBlock, false, BRDF, false, 7>(prm, nvert, s);
+    case 256: return launch_q<kBlock, false, BRDF, false, 8>(prm, nvert, s);
+    case 512: return launch_q<kBlock, false, BRDF, false, 9>(prm, nvert, s);
+    default: return launch_q<kBlock, false, BRDF, false, 10>(prm, nvert, s);
   }
 }
 

@@ -38,8 +38,8 @@ int check_relight_flags(const rrt_light* L, unsigned flags, const rrt_transport*
 // Haar transform launchers (haar.hip).
 // squares: number of n x n squares (a cube map is 6, a longitude-latitude map 2)
 int launch_haar_forward(const float* pix, float* coef, int n, int64_t squares, hipStream_t s);
-// strips: write the pixels in strips of four rows (the cube-map relight's
-// source-map layout, n >= 4; see strip_offset in geometry.h) instead of
+// strips: write the pixels in strips of eight columns (the cube-map relight's
+// source-map layout, n >= 8; see strip_offset in geometry.h) instead of
 // row-major order
 int launch_haar_inverse(const float* coef, float* pix, int n, int64_t squares, hipStream_t s,
                         bool strips = false);
@@ -58,8 +58,8 @@ int launch_rotate_pixels(const float* src, const float* rot, int nrot, int n, fl
                          hipStream_t s);
 
 struct RelightLaunch {
-  const float* src;         // [6][n][n] source map, in strips of four rows for n >= 4
-                            // (row-major for n < 4 and for the [2][n][n] lat-long map)
+  const float* src;         // [6][n][n] source map, in strips of eight columns for n >= 8
+                            // (row-major for n < 8 and for the [2][n][n] lat-long map)
   const float* vert_rot;    // [V][9]
   const float* frame_rot;   // [F][9] or nullptr
   const int32_t* t_idx;     // [V][nnz] or nullptr (dense)
