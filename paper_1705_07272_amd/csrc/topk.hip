@@ -2,16 +2,13 @@
 // entries of largest magnitude of each row, ties to the lower position,
 // output in ascending position order.
 //
-// One workgroup per row (256 threads for many rows, 1024 for a few long
-// rows such as one environment map).  The k-th largest key is found by a
-// four-pass radix select over the 31 magnitude bits of binary32 (|x| orders
-// like its bit pattern): each pass builds a 256-bin histogram of the next
-// byte among the keys that share the already-fixed high bytes, one private
-// LDS histogram per wave (keys of one map crowd into few bins, so shared
-// bins would serialise the atomics), then merged.  A final ordered pass
-// keeps every key above the threshold and the first `need` keys equal to it,
-// using block-wide prefix sums so that positions come out in ascending
-// order.
+// One workgroup per row.  The k-th largest key (|x| orders like its bit
+// pattern) is found from one histogram of the top 11 magnitude bits: the keys
+// of the bin that holds it are candidates, ranked against each other in LDS.
+// A bit per position collects what is kept; the output follows from a prefix
+// sum over the bits in position order.  Three other ways remain: rows longer
+// than the bits' LDS (a radix select and an ordered compaction), a few long
+// rows (several workgroups per row) and k = len (a copy).
 #include "rrt_internal.h"
 
 namespace rrt {
@@ -152,9 +149,222 @@ __global__ __launch_bounds__(kThreads) void topk_rows(const float* __restrict__ 
 }
 
 // ---------------------------------------------------------------------------
+// One workgroup per row, the row read twice.
+//
+// What bounds it: reading the row.  The radix select above reads it five
+// times, adds every value to a histogram of 256 bins in LDS (the zeros that
+// fill most of a transport row all into one) and has one thread look through
+// each; here zeros are counted by difference, and a bin of 11 bits (an eighth
+// of a power of two) leaves a few hundred candidates.  512 rows of 98,304, k =
+// 256: 446 -> 80 us, 2.5 TB/s of the row once (it is read twice); 1,024 threads
+// per row, two rows per CU; 256 threads for rows up to 8,192.
+// ---------------------------------------------------------------------------
+constexpr int kSelBits = 11;
+constexpr int kSelBins = 1 << kSelBits;
+constexpr int kSelShift = 31 - kSelBits;
+constexpr int kSelCand = kSelBins / 2;        // candidates (key, position) in the bins' place
+constexpr int64_t kSelMaxLen = 6 * 256 * 256;  // 48 KiB of bits
+
+// f(position, value) for every value of the row, 16 bytes at a time where its
+// start and length allow; the same thread takes the same positions each time.
+template <int kThreads, typename F>
+__device__ __forceinline__ void for_row(const float* __restrict__ row, int len, bool wide, F f) {
+  const int tid = threadIdx.x;
+  if (wide) {
+    const float4* r4 = reinterpret_cast<const float4*>(row);
+    const int n4 = len >> 2;
+    int i = tid;
+    for (; i + 3 * kThreads < n4; i += 4 * kThreads) {
+      float4 v[4];
+#pragma unroll
+      for (int j = 0; j < 4; ++j) v[j] = r4[i + j * kThreads];
+#pragma unroll
+      for (int j = 0; j < 4; ++j) {
+        const int at = 4 * (i + j * kThreads);
+        f(at, v[j].x);
+        f(at + 1, v[j].y);
+        f(at + 2, v[j].z);
+        f(at + 3, v[j].w);
+      }
+    }
+    for (; i < n4; i += kThreads) {
+      const float4 v = r4[i];
+      f(4 * i, v.x);
+      f(4 * i + 1, v.y);
+      f(4 * i + 2, v.z);
+      f(4 * i + 3, v.w);
+    }
+  } else {
+    for (int i = tid; i < len; i += kThreads) f(i, row[i]);
+  }
+}
+
+// The bin of `nb` (a multiple of kThreads, at most kSelBins) that holds the
+// need-th largest key, with zeros added to bin 0: bin and the number needed
+// from it, through s_bin and s_need.
+template <int kThreads>
+__device__ __forceinline__ void find_bin(const unsigned* hist, int nb, unsigned zeros, unsigned need,
+                                         int* s_bin, int* s_need, int* sh) {
+  const int tid = threadIdx.x;
+  const int per = nb / kThreads > 0 ? nb / kThreads : 1;
+  const bool mine_ok = per * tid < nb;
+  unsigned mine = 0;
+  for (int j = 0; mine_ok && j < per; ++j) mine += hist[per * tid + j];
+  if (tid == 0) mine += zeros;
+  int total;
+  const int before = block_scan<kThreads / 64>(int(mine), &total, sh);
+  unsigned above = unsigned(total) - unsigned(before) - mine;
+  for (int j = per - 1; mine_ok && j >= 0; --j) {
+    unsigned c = hist[per * tid + j];
+    if (tid == 0 && j == 0) c += zeros;
+    if (above < need && above + c >= need) {
+      *s_bin = per * tid + j;
+      *s_need = int(need - above);
+    }
+    above += c;
+  }
+  __syncthreads();
+}
+
+template <int kThreads>
+__global__ __launch_bounds__(kThreads) void topk_select(const float* __restrict__ x, int len, int k,
+                                                        int32_t* __restrict__ oidx,
+                                                        float* __restrict__ oval) {
+  constexpr int kWaves = kThreads / 64;
+  extern __shared__ unsigned lds[];
+  unsigned* hist = lds;             // kSelBins; later the candidates
+  unsigned* bits = lds + kSelBins;  // one bit per position
+  __shared__ int sh[kWaves];
+  __shared__ int s_bin, s_need, s_count;
+  const int tid = threadIdx.x;
+  const int words = (len + 31) >> 5;
+  const float* row = x + int64_t(blockIdx.x) * len;
+  int32_t* ri = oidx + int64_t(blockIdx.x) * k;
+  float* rv = oval + int64_t(blockIdx.x) * k;
+  const bool wide = ((reinterpret_cast<uintptr_t>(row) | unsigned(len * 4)) & 15u) == 0;
+  for (int b = tid; b < kSelBins + words; b += kThreads) lds[b] = 0u;
+  if (tid == 0) s_count = 0;
+  __syncthreads();
+  // histogram of the nonzero keys; zeros are the rest
+  int nonzero = 0;
+  for_row<kThreads>(row, len, wide, [&](int, float v) {
+    const unsigned u = key_of(v);
+    if (u) {
+      atomicAdd(&hist[u >> kSelShift], 1u);
+      ++nonzero;
+    }
+  });
+  __syncthreads();
+  int total;
+  block_scan<kWaves>(nonzero, &total, sh);
+  const unsigned zeros = unsigned(len - total);
+  find_bin<kThreads>(hist, kSelBins, zeros, unsigned(k), &s_bin, &s_need, sh);
+  const unsigned bin = unsigned(s_bin);
+  unsigned need = unsigned(s_need);
+  const unsigned in_bin = hist[bin] + (bin == 0 ? zeros : 0u);
+  __syncthreads();
+  if (in_bin <= unsigned(kSelCand)) {
+    // keys above the bin are kept, the bin's are listed ...
+    for_row<kThreads>(row, len, wide, [&](int i, float v) {
+      const unsigned u = key_of(v), b = u >> kSelShift;
+      if (b > bin) {
+        atomicOr(&bits[i >> 5], 1u << (i & 31));
+      } else if (b == bin) {
+        const int at = atomicAdd(&s_count, 1);
+        hist[2 * at] = u;
+        hist[2 * at + 1] = unsigned(i);
+      }
+    });
+    __syncthreads();
+    // ... and those of a rank (larger key, then lower position) below `need` kept
+    const int m = int(in_bin);
+    for (int c = tid; c < m; c += kThreads) {
+      const unsigned u = hist[2 * c], i = hist[2 * c + 1];
+      unsigned rank = 0;
+      for (int j = 0; j < m; ++j) {
+        const unsigned v = hist[2 * j];
+        rank += (v > u || (v == u && hist[2 * j + 1] < i)) ? 1u : 0u;
+      }
+      if (rank < need) atomicOr(&bits[i >> 5], 1u << (i & 31));
+    }
+  } else {
+    // many equal or nearly equal keys: the threshold from the remaining bits
+    // in two steps, then the first `need` keys equal to it in position order
+    unsigned prefix = bin << kSelShift, mask = ~((1u << kSelShift) - 1u) & 0x7fffffffu;
+    for (int shift = kSelShift - 10; shift >= 0; shift -= 10) {
+      for (int b = tid; b < 1024; b += kThreads) hist[b] = 0u;
+      __syncthreads();
+      for_row<kThreads>(row, len, wide, [&](int, float v) {
+        const unsigned u = key_of(v);
+        if (u && (u & mask) == prefix) atomicAdd(&hist[(u >> shift) & 1023u], 1u);
+      });
+      __syncthreads();
+      find_bin<kThreads>(hist, 1024, prefix == 0 ? zeros : 0u, need, &s_bin, &s_need, sh);
+      prefix |= unsigned(s_bin) << shift;
+      need = unsigned(s_need);
+      mask |= 1023u << shift;
+      __syncthreads();
+    }
+    int base = 0;
+    for (int c0 = 0; c0 < len; c0 += kThreads * kItems) {
+      unsigned keep = 0, eq = 0;
+#pragma unroll
+      for (int j = 0; j < kItems; ++j) {
+        const int i = c0 + tid * kItems + j;
+        const unsigned u = i < len ? key_of(row[i]) : 0u;
+        if (i < len && u > prefix) keep |= 1u << j;
+        if (i < len && u == prefix) eq |= 1u << j;
+      }
+      int eqs;
+      int rank = base + block_scan<kWaves>(__popc(eq), &eqs, sh);
+#pragma unroll
+      for (int j = 0; j < kItems; ++j) {
+        if (eq & (1u << j)) {
+          if (rank < int(need)) keep |= 1u << j;
+          ++rank;
+        }
+      }
+      base += eqs;
+      const int i = c0 + tid * kItems;  // kItems positions share a word
+      if (keep) atomicOr(&bits[i >> 5], keep << (i & 31));
+    }
+  }
+  __syncthreads();
+  // emission: each thread's words follow those of the threads before it
+  const int per = (words + kThreads - 1) / kThreads;
+  const int w0 = tid * per, w1 = w0 + per < words ? w0 + per : words;
+  int count = 0;
+  for (int w = w0; w < w1; ++w) count += __popc(bits[w]);
+  int kept;
+  int pos = block_scan<kWaves>(count, &kept, sh);
+  for (int w = w0; w < w1; ++w) {
+    unsigned m = bits[w];
+    while (m) {
+      const int i = 32 * w + __builtin_ctz(m);
+      m &= m - 1;
+      if (pos < k) {
+        ri[pos] = i;
+        rv[pos] = row[i];
+      }
+      ++pos;
+    }
+  }
+}
+
+// k = len: every value in place.
+__global__ void topk_all(const float* __restrict__ x, int64_t total, int64_t len,
+                         int32_t* __restrict__ oidx, float* __restrict__ oval) {
+  const int64_t i = int64_t(blockIdx.x) * blockDim.x + threadIdx.x;
+  if (i >= total) return;
+  oidx[i] = int32_t(i % len);
+  oval[i] = x[i];
+}
+
+// ---------------------------------------------------------------------------
 // A few long rows (one environment map): the row is split into chunks
 // processed by many workgroups.
-//   1. per-chunk histograms of the top 12 key bits;
+//   1. per-chunk histograms of the top 12 key bits, added up over the chunks
+//      (in the candidate list's space, cleared first);
 //   2. per row: the bin holding the k-th largest key and, per chunk, the
 //      start of that bin's keys in a candidate list;
 //   3. per chunk: the candidates, compacted in position order;
@@ -226,9 +436,17 @@ __device__ __forceinline__ int block_sum(int x, int* sh) {
   return total;
 }
 
+__global__ __launch_bounds__(kChunkThreads) void tk_clear(uint32_t* __restrict__ tot, int64_t len) {
+  tot[int64_t(blockIdx.y) * len + blockIdx.x * kChunkThreads + threadIdx.x] = 0u;
+}
+
+// tot: the row's histogram, at the start of its candidate list.  (The bin
+// search read it from the chunks' own before, one after the other: 32 us of the
+// 57 that one row of 98,304 took.)
 __global__ __launch_bounds__(kChunkThreads) void tk_hist(const float* __restrict__ x, int64_t len,
                                                          int64_t chunk_len, int chunks,
-                                                         uint32_t* __restrict__ hist) {
+                                                         uint32_t* __restrict__ hist,
+                                                         uint32_t* __restrict__ tot) {
   __shared__ unsigned h[kBins];
   const int tid = threadIdx.x, c = blockIdx.x, row = blockIdx.y;
   for (int b = tid; b < kBins; b += kChunkThreads) h[b] = 0;
@@ -247,7 +465,12 @@ __global__ __launch_bounds__(kChunkThreads) void tk_hist(const float* __restrict
   for (; i < hi; i += kChunkThreads) atomicAdd(&h[key_of(r[i]) >> kLowBits], 1u);
   __syncthreads();
   uint32_t* out = hist + (int64_t(row) * chunks + c) * kBins;
-  for (int b = tid; b < kBins; b += kChunkThreads) out[b] = h[b];
+  uint32_t* sum = tot + int64_t(row) * len;
+  for (int b = tid; b < kBins; b += kChunkThreads) {
+    const unsigned c = h[b];
+    out[b] = c;
+    if (c) atomicAdd(&sum[b], c);
+  }
 }
 
 // The single-workgroup steps of a long row run as four waves (one per SIMD)
@@ -257,7 +480,8 @@ __global__ __launch_bounds__(kChunkThreads) void tk_hist(const float* __restrict
 constexpr int kSmallThreads = 256;
 #define RRT_SMALL_STEP __global__ __launch_bounds__(kSmallThreads)
 
-RRT_SMALL_STEP void tk_bin(const uint32_t* __restrict__ hist, int chunks, int k,
+RRT_SMALL_STEP void tk_bin(const uint32_t* __restrict__ hist, const uint32_t* __restrict__ sums,
+                           int64_t len, int chunks, int k,
                            uint32_t* __restrict__ eq_base, uint32_t* __restrict__ par) {
   constexpr int kWaves = kSmallThreads / 64;
   constexpr int kPer = kBins / kSmallThreads;
@@ -273,14 +497,8 @@ RRT_SMALL_STEP void tk_bin(const uint32_t* __restrict__ hist, int chunks, int k,
     s_need = 0;
   }
   const uint32_t* h = hist + int64_t(row) * chunks * kBins;
-  // per-bin totals over the chunks (each thread owns bins tid + 64 j)
-#pragma unroll 1
-  for (int b = tid; b < kBins; b += kSmallThreads) {
-    unsigned t = 0;
 #pragma unroll 4
-    for (int c = 0; c < chunks; ++c) t += h[int64_t(c) * kBins + b];
-    tot[b] = t;
-  }
+  for (int b = tid; b < kBins; b += kSmallThreads) tot[b] = sums[int64_t(row) * len + b];
   __syncthreads();
   // this thread's bins kPer tid .. kPer tid + kPer - 1
   const unsigned* mt = tot + kPer * tid;
@@ -497,28 +715,51 @@ __global__ __launch_bounds__(kChunkThreads) void tk_emit(const float* __restrict
       });
 }
 
-bool use_chunks(int64_t rows, int64_t len, int k) {
+bool few_long_rows(int64_t rows, int64_t len, int k) {
   return rows <= 8 && len >= 16384 && int64_t(k) < len;
 }
 
 }  // namespace
 
 size_t topk_workspace_bytes(int64_t rows, int64_t len, int k) {
-  return use_chunks(rows, len, k) ? carve(nullptr, rows, len, nullptr) : 0;
+  return few_long_rows(rows, len, k) ? carve(nullptr, rows, len, nullptr) : 0;
 }
 
 int launch_topk(const float* x, int64_t rows, int64_t len, int k, int32_t* idx, float* val,
                 void* ws, hipStream_t s) {
   if (rows == 0 || k == 0) return RRT_OK;
-  if (use_chunks(rows, len, k)) {
+  const int64_t total = rows * len;
+  if (int64_t(k) == len && total <= int64_t(0x7fffffff) * 256) {
+    hipLaunchKernelGGL(topk_all, dim3(unsigned((total + 255) / 256)), dim3(256), 0, s, x, total, len,
+                       idx, val);
+    return check_launch("topk_all");
+  }
+  // One workgroup for a row of a map's coefficients: 80 us for 512 rows of
+  // 98,304 (radix select 446), 26 us for 9 (192), 26 us for 2,048 rows of 6,144
+  // (108); a few long rows would leave most CUs idle (92 us for one row of
+  // 98,304 log-normal values against 33).
+  if (len <= kSelMaxLen && !few_long_rows(rows, len, k)) {
+    const size_t lds = (kSelBins + size_t((len + 31) >> 5)) * sizeof(unsigned);
+    if (len > 8192) {
+      hipLaunchKernelGGL(topk_select<1024>, dim3(unsigned(rows)), dim3(1024), lds, s, x, int(len), k,
+                         idx, val);
+    } else {
+      hipLaunchKernelGGL(topk_select<256>, dim3(unsigned(rows)), dim3(256), lds, s, x, int(len), k,
+                         idx, val);
+    }
+    return check_launch("topk_select");
+  }
+  if (few_long_rows(rows, len, k)) {
     TopkWs w;
     carve(ws, rows, len, &w);
     const ChunkPlan cp = chunk_plan(len);
     const dim3 grid(unsigned(cp.chunks), unsigned(rows));
+    hipLaunchKernelGGL(tk_clear, dim3(kBins / kChunkThreads, unsigned(rows)), dim3(kChunkThreads), 0, s,
+                       w.ckey, len);
     hipLaunchKernelGGL(tk_hist, grid, dim3(kChunkThreads), 0, s, x, len, cp.chunk_len, cp.chunks,
-                       w.hist);
+                       w.hist, w.ckey);
     hipLaunchKernelGGL(tk_bin, dim3(unsigned(rows)), dim3(kSmallThreads), kBins * sizeof(unsigned), s,
-                       w.hist, cp.chunks, k,
+                       w.hist, w.ckey, len, cp.chunks, k,
                        w.eq_base, w.par);
     hipLaunchKernelGGL(tk_cand, grid, dim3(kChunkThreads), 0, s, x, len, cp.chunk_len, cp.chunks,
                        w.eq_base, w.par, w.ckey, w.cidx);
