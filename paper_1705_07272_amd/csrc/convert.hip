@@ -52,69 +52,62 @@ __device__ __forceinline__ int16_t to_s16(float y) {
   return int16_t(r == r ? r : 0.0f);
 }
 
-// One thread per (row, block of 64); codes = round(x * M / max|x|).
-template <typename CodeT, int M>
-__global__ void convert_blocks(const float* __restrict__ src, CodeT* __restrict__ dst,
-                               float* __restrict__ scale, int64_t rows, int cols) {
-  const int nblk = (cols + RRT_BLOCK - 1) / RRT_BLOCK;
-  const int64_t t = int64_t(blockIdx.x) * blockDim.x + threadIdx.x;
-  if (t >= rows * nblk) return;
-  const int64_t row = t / nblk;
-  const int blk = int(t - row * nblk);
-  const int c0 = blk * RRT_BLOCK;
-  const int c1 = min(cols, c0 + RRT_BLOCK);
-  const float* s = src + row * cols;
-  float amax = 0.0f;
-  for (int c = c0; c < c1; ++c) amax = fmaxf(amax, fabsf(s[c]));
-  const float sc = amax > 0.0f ? __fdiv_rn(amax, float(M)) : 1.0f;
-  const float inv = amax > 0.0f ? __fdiv_rn(float(M), amax) : 1.0f;
-  for (int c = c0; c < c1; ++c) {
-    const float y = s[c] * inv;
-    if constexpr (M == 448) {
-      dst[row * cols + c] = to_e4m3(y);
-    } else {
-      dst[row * cols + c] = to_s16(y);
-    }
-  }
-  scale[t] = sc;
+// Block-scaled forms: one wave per (row, block of 64), one value per lane; the
+// scale from a maximum over the wave; codes = round(x * M / max|x|).  (One thread per block
+// read its 64 values one after the other, 256 bytes apart from its
+// neighbours': 512 rows of 256 packed to 11 bits 23 -> 12 us, launch included;
+// 200,000 rows 1.82 -> 0.22 ms, to 16 bits 2.18 -> 0.17 ms.)
+__device__ __forceinline__ float wave_max(float x) {
+#pragma unroll
+  for (int o = 32; o >= 1; o >>= 1) x = fmaxf(x, __shfl_xor(x, o, 64));
+  return x;
 }
 
-// One thread per (row, block of 64) of the packed 11-bit form: the block's
-// 64 codes fill exactly 22 words of the row's bit stream (a shorter last
-// block ends inside a word whose remaining bits stay zero), so no two
-// threads share a word.
-__global__ void convert_s11(const float* __restrict__ src, uint32_t* __restrict__ dst,
-                            float* __restrict__ scale, int64_t rows, int cols) {
+constexpr int kConvThreads = 256;
+
+template <int FORM>
+__global__ __launch_bounds__(kConvThreads) void convert_blocks(const float* __restrict__ src,
+                                                               void* __restrict__ dst,
+                                                               float* __restrict__ scale,
+                                                               int64_t rows, int cols) {
+  constexpr float M = FORM == RRT_E4M3 ? 448.0f : (FORM == RRT_S11 ? 1023.0f : 32767.0f);
   const int nblk = (cols + RRT_BLOCK - 1) / RRT_BLOCK;
-  const int64_t t = int64_t(blockIdx.x) * blockDim.x + threadIdx.x;
-  if (t >= rows * nblk) return;
-  const int64_t row = t / nblk;
-  const int blk = int(t - row * nblk);
-  const int c0 = blk * RRT_BLOCK;
-  const int c1 = min(cols, c0 + RRT_BLOCK);
-  const float* s = src + row * cols;
-  float amax = 0.0f;
-  for (int c = c0; c < c1; ++c) amax = fmaxf(amax, fabsf(s[c]));
-  const float sc = amax > 0.0f ? __fdiv_rn(amax, 1023.0f) : 1.0f;
-  const float inv = amax > 0.0f ? __fdiv_rn(1023.0f, amax) : 1.0f;
-  const int64_t words = RRT_S11_WORDS(cols);
-  uint32_t* w = dst + row * words + int64_t(blk) * 22;
-  const int nw = int(min(int64_t(22), words - int64_t(blk) * 22));
-  uint64_t acc = 0;  // the block's bit stream not yet written
-  int have = 0, out = 0;
-  for (int c = c0; c < c1; ++c) {
-    const float r = rintf(fminf(fmaxf(s[c] * inv, -1023.0f), 1023.0f));
-    const unsigned code = unsigned(int(r == r ? r : 0.0f)) & 0x7ffu;
-    acc |= uint64_t(code) << have;
-    have += 11;
-    if (have >= 32) {
-      w[out++] = uint32_t(acc);
-      acc >>= 32;
-      have -= 32;
+  const int lane = threadIdx.x & 63;
+  const int64_t nt = rows * nblk;
+  const int64_t waves = int64_t(gridDim.x) * (kConvThreads / 64);
+  for (int64_t t = int64_t(blockIdx.x) * (kConvThreads / 64) + (threadIdx.x >> 6); t < nt;
+       t += waves) {
+    const int64_t row = t / nblk;
+    const int blk = int(t - row * nblk);
+    const int c = blk * RRT_BLOCK + lane;
+    const float v = c < cols ? src[row * cols + c] : 0.0f;
+    const float amax = wave_max(fabsf(v));
+    const float sc = amax > 0.0f ? __fdiv_rn(amax, M) : 1.0f;
+    const float inv = amax > 0.0f ? __fdiv_rn(M, amax) : 1.0f;
+    const float y = v * inv;
+    if constexpr (FORM == RRT_E4M3) {
+      if (c < cols) static_cast<uint8_t*>(dst)[row * cols + c] = to_e4m3(y);
+    } else if constexpr (FORM == RRT_S16) {
+      if (c < cols) static_cast<int16_t*>(dst)[row * cols + c] = to_s16(y);
+    } else {
+      // the block's 64 codes fill exactly 22 words of the row's bit stream (a
+      // shorter last block ends inside a word whose remaining bits stay zero);
+      // lane w < 22 puts word w together from the four codes that reach into it
+      const float r = rintf(fminf(fmaxf(y, -1023.0f), 1023.0f));
+      const unsigned code = c < cols ? unsigned(int(r == r ? r : 0.0f)) & 0x7ffu : 0u;
+      const int first = 32 * lane / 11;
+      unsigned word = 0;
+#pragma unroll
+      for (int j = 0; j < 4; ++j) {
+        const unsigned x = unsigned(__shfl(int(code), (first + j) & 63, 64));
+        const int sh = 11 * (first + j) - 32 * lane;
+        if (first + j < RRT_BLOCK && sh < 32) word |= sh >= 0 ? x << sh : x >> -sh;
+      }
+      const int64_t words = RRT_S11_WORDS(cols), w = int64_t(blk) * 22 + lane;
+      if (lane < 22 && w < words) static_cast<uint32_t*>(dst)[row * words + w] = word;
     }
+    if (lane == 0) scale[t] = sc;
   }
-  if (out < nw) w[out] = uint32_t(acc);
-  scale[t] = sc;
 }
 
 }  // namespace
@@ -131,15 +124,17 @@ int launch_convert(const float* src, int64_t rows, int cols, int dtype, void* ds
                        static_cast<uint16_t*>(dst), total);
   } else {
     const int64_t nt = rows * ((cols + RRT_BLOCK - 1) / RRT_BLOCK);
+    const int64_t wanted = (nt + kConvThreads / 64 - 1) / (kConvThreads / 64);
+    const dim3 grid(unsigned(wanted < (1 << 20) ? wanted : (1 << 20)));
     if (dtype == RRT_E4M3) {
-      hipLaunchKernelGGL((convert_blocks<uint8_t, 448>), dim3(unsigned((nt + 255) / 256)),
-                         dim3(256), 0, s, src, static_cast<uint8_t*>(dst), scale, rows, cols);
+      hipLaunchKernelGGL(convert_blocks<RRT_E4M3>, grid, dim3(kConvThreads), 0, s, src, dst, scale,
+                         rows, cols);
     } else if (dtype == RRT_S11) {
-      hipLaunchKernelGGL(convert_s11, dim3(unsigned((nt + 255) / 256)), dim3(256), 0, s, src,
-                         static_cast<uint32_t*>(dst), scale, rows, cols);
+      hipLaunchKernelGGL(convert_blocks<RRT_S11>, grid, dim3(kConvThreads), 0, s, src, dst, scale,
+                         rows, cols);
     } else {
-      hipLaunchKernelGGL((convert_blocks<int16_t, 32767>), dim3(unsigned((nt + 255) / 256)),
-                         dim3(256), 0, s, src, static_cast<int16_t*>(dst), scale, rows, cols);
+      hipLaunchKernelGGL(convert_blocks<RRT_S16>, grid, dim3(kConvThreads), 0, s, src, dst, scale,
+                         rows, cols);
     }
   }
   return check_launch("convert");
