@@ -61,17 +61,13 @@ __device__ __forceinline__ float gelu_grad_f(float z) {
 enum Epilogue {
   kEpiHidden = 0,   // z = acc + bias -> store z (FP32) and gelu(z) (BF16)
   kEpiOutput = 1,   // out = acc + bias -> FP32
-  kEpiGeluGrad = 2, // dz = acc * gelu'(zprev) -> BF16
-  kEpiPlain = 3     // acc -> FP32
+  kEpiGeluGrad = 2  // dz = acc * gelu'(zprev) -> BF16
 };
 
 struct GemmArgs {
   const uint16_t* A;
   const uint16_t* B;
   int M, N, K;
-  int k_chunk;         // split over k: workgroup z takes [z k_chunk, (z + 1) k_chunk) (a
-                       // multiple of kBK) and writes its partial sums to out_f32 + z M N
-                       // (kEpiPlain only); 0 = the whole K in one workgroup
   const float* bias;   // [N] (kEpiHidden / kEpiOutput)
   const float* zprev;  // [M][N] (kEpiGeluGrad)
   float* out_f32;      // [M][N]
@@ -133,17 +129,15 @@ __global__ __launch_bounds__(256) void gemm_bf16(GemmArgs g) {
 #pragma unroll
     for (int j = 0; j < TM; ++j) acc[i][j] = float16_t{};
 
-  const int kb = g.k_chunk ? int(blockIdx.z) * g.k_chunk : 0;
-  const int ke = g.k_chunk ? min(g.K, kb + g.k_chunk) : g.K;
   Slice<BM, !AT> sa;
   Slice<BN, BT> sb;
-  sa.load(g.A, g.M, g.K, m0, kb);
-  sb.load(g.B, g.N, g.K, n0, kb);
-  for (int k0 = kb; k0 < ke; k0 += kBK) {
+  sa.load(g.A, g.M, g.K, m0, 0);
+  sb.load(g.B, g.N, g.K, n0, 0);
+  for (int k0 = 0; k0 < g.K; k0 += kBK) {
     sa.store(As);
     sb.store(Bs);
     __syncthreads();
-    if (k0 + kBK < ke) {
+    if (k0 + kBK < g.K) {
       sa.load(g.A, g.M, g.K, m0, k0 + kBK);
       sb.load(g.B, g.N, g.K, n0, k0 + kBK);
     }
@@ -178,20 +172,14 @@ __global__ __launch_bounds__(256) void gemm_bf16(GemmArgs g) {
         if (m >= g.M || n >= g.N) continue;
         const int64_t at = int64_t(m) * g.N + n;
         float x = acc[i][j][r];
-        if (EPI == kEpiPlain && g.k_chunk) {
-          g.out_f32[int64_t(blockIdx.z) * g.M * g.N + at] = x;
-          continue;
-        }
         if (EPI == kEpiHidden) {
           x += g.bias[n];
           g.out_f32[at] = x;
           g.out_bf16[at] = bf16_bits(gelu_f(x));
         } else if (EPI == kEpiOutput) {
           g.out_f32[at] = x + g.bias[n];
-        } else if (EPI == kEpiGeluGrad) {
-          g.out_bf16[at] = bf16_bits(x * gelu_grad_f(g.zprev[at]));
         } else {
-          g.out_f32[at] = x;
+          g.out_bf16[at] = bf16_bits(x * gelu_grad_f(g.zprev[at]));
         }
       }
 }
@@ -447,19 +435,147 @@ __global__ void to_bf16_kernel(const float* __restrict__ in, uint16_t* __restric
   if (t < n) out[t] = bf16_bits(in[t]);
 }
 
-// part[c][n] = sum over rows [c R, c R + R) of dz[m][n] (BF16 gradient
-// rows); the chunks' partial sums are then added in chunk order
-// (sum_splits_kernel), so the bias gradient is deterministic.
-__global__ void colsum_kernel(const uint16_t* __restrict__ dz, int64_t M, int N, int R,
-                              float* __restrict__ part) {
-  const int n = blockIdx.x * blockDim.x + threadIdx.x;
-  if (n >= N) return;
-  const int64_t r0 = int64_t(blockIdx.y) * R;
-  const int64_t r1 = r0 + R < M ? r0 + R : M;
+// Weight and bias gradients of up to three layers: dW_l[m][n] = sum_b dz_l[b][m]
+// a_l[b][n] and db_l[m] = sum_b dz_l[b][m], over the batch rows b, which both
+// operands store row by row.  A 256-thread workgroup takes a 64 x 64 tile of one
+// dW over one range of rows, 128 rows at a time: each thread loads an 8 x 8
+// block of one operand (eight 16-byte loads, the next 128 rows' under way while
+// the matrix cores consume these), transposes it in registers (32 byte
+// permutes) and stores it as eight 16-byte LDS rows of 8 consecutive k, which
+// is how the MFMA reads them.  The workgroups of the first column tile also add
+// up their dz for the bias.  Row ranges leave partial sums that grad_sum_kernel
+// adds in order; with one range the results go straight out.
+//
+// What bounds it: latency, at 16 workgroups per layer and range, so the layers
+// whose operands are ready share a launch.  It replaces a GEMM that stored
+// transposed slices two bytes at a time, and column sums in launches of their own:
+// 4,096 rows, all five layers GRADOLD -> GRADNEW us.
+constexpr int kGradRows = 128;
+constexpr int kGradStride = kGradRows + 8;  // bf16 per LDS row
+constexpr int kGradLayers = 3;
+
+struct GradLayer {
+  const uint16_t* dz;  // [B][256]
+  const uint16_t* a;   // [B][n]
+  int n;
+  float* dw;           // [256][n]
+  float* db;           // [256]
+};
+struct GradArgs {
+  GradLayer layer[kGradLayers];
+  int64_t B;
+  int splits;          // row ranges per layer
+  int64_t rows;        // rows of a range (a multiple of kGradRows)
+  float* part;         // [layers][splits][kGradPart], unused with one range
+};
+constexpr int64_t kGradPart = int64_t(RRT_MLP_HIDDEN) * RRT_MLP_HIDDEN + RRT_MLP_HIDDEN;
+
+__global__ __launch_bounds__(256) void grad_kernel(GradArgs g) {
+  __shared__ __align__(16) uint16_t lds[2][64 * kGradStride];
+  const int li = int(blockIdx.z) / g.splits, split = int(blockIdx.z) % g.splits;
+  const GradLayer L = g.layer[li];
+  const int m0 = blockIdx.y * 64, n0 = blockIdx.x * 64;
+  if (n0 >= L.n) return;
+  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+  const int64_t b0 = int64_t(split) * g.rows;
+  const int64_t b1 = b0 + g.rows < g.B ? b0 + g.rows : g.B;
+  // threads 0..127 load dz, 128..255 the activations: block kb (8 rows) x mb
+  // (8 columns) of the 128 x 64 slice
+  const bool acts = tid >= 128;
+  const int kb = (tid & 127) >> 3, mb = tid & 7;
+  const int width = acts ? L.n : RRT_MLP_HIDDEN;
+  const uint16_t* from = (acts ? L.a + n0 : L.dz + m0) + 8 * mb;
+  uint16_t* to = lds[acts ? 1 : 0] + 8 * mb * kGradStride + 8 * kb;
+  u32x4_t v[8];
+  auto load = [&](int64_t b) {
+#pragma unroll
+    for (int i = 0; i < 8; ++i) {
+      const int64_t r = b + 8 * kb + i;
+      v[i] = u32x4_t{0u, 0u, 0u, 0u};
+      if (r < b1) v[i] = *reinterpret_cast<const u32x4_t*>(from + r * width);
+    }
+  };
+  const bool bias = blockIdx.x == 0 && !acts;
+  float sum[8];
+#pragma unroll
+  for (int j = 0; j < 8; ++j) sum[j] = 0.0f;
+  float16_t acc = {};
+  const int wm = (wave >> 1) * 32, wn = (wave & 1) * 32;
+  const uint16_t* ar = lds[0] + (wm + (lane & 31)) * kGradStride + 8 * (lane >> 5);
+  const uint16_t* br = lds[1] + (wn + (lane & 31)) * kGradStride + 8 * (lane >> 5);
+  load(b0);
+  for (int64_t b = b0; b < b1; b += kGradRows) {
+#pragma unroll
+    for (int j = 0; j < 8; ++j) {
+      u32x4_t t;
+#pragma unroll
+      for (int p = 0; p < 4; ++p)
+        t[p] = __builtin_amdgcn_perm(v[2 * p + 1][j / 2], v[2 * p][j / 2],
+                                     (j & 1) ? 0x07060302u : 0x05040100u);
+      *reinterpret_cast<u32x4_t*>(to + j * kGradStride) = t;
+      if (bias) {
+#pragma unroll
+        for (int p = 0; p < 4; ++p)
+          sum[j] += __uint_as_float(t[p] << 16) + __uint_as_float(t[p] & 0xffff0000u);
+      }
+    }
+    __syncthreads();
+    if (b + kGradRows < b1) load(b + kGradRows);
+#pragma unroll
+    for (int s = 0; s < kGradRows / 16; ++s)
+      acc = __builtin_amdgcn_mfma_f32_32x32x16_bf16(
+          *reinterpret_cast<const bf16x8_t*>(ar + 16 * s),
+          *reinterpret_cast<const bf16x8_t*>(br + 16 * s), acc, 0, 0, 0);
+    __syncthreads();
+  }
+  float* dw = L.dw;
+  float* db = L.db;
+  if (g.splits > 1) {
+    dw = g.part + (int64_t(li) * g.splits + split) * kGradPart;
+    db = dw + int64_t(RRT_MLP_HIDDEN) * RRT_MLP_HIDDEN;
+  }
+#pragma unroll
+  for (int r = 0; r < 16; ++r) {
+    const int m = m0 + wm + 8 * (r >> 2) + 4 * (lane >> 5) + (r & 3);
+    dw[int64_t(m) * L.n + n0 + wn + (lane & 31)] = acc[r];
+  }
+  if (blockIdx.x == 0) {  // (uniform) bias: the 16 row blocks' sums, in order
+    float* red = reinterpret_cast<float*>(lds[0]);
+    if (!acts) {
+#pragma unroll
+      for (int j = 0; j < 8; ++j) red[kb * 64 + 8 * mb + j] = sum[j];
+    }
+    __syncthreads();
+    if (tid < 64) {
+      float s = 0.0f;
+#pragma unroll
+      for (int k = 0; k < 16; ++k) s += red[k * 64 + tid];
+      db[m0 + tid] = s;
+    }
+  }
+}
+
+// Sums of the row ranges' partial gradients, in order (all loads of a chunk of
+// ranges are in flight together).
+__global__ __launch_bounds__(256) void grad_sum_kernel(GradArgs g) {
+  const int64_t i = int64_t(blockIdx.x) * 256 + threadIdx.x;
+  const GradLayer L = g.layer[blockIdx.y];
+  const int64_t nw = int64_t(RRT_MLP_HIDDEN) * L.n;
+  constexpr int64_t kBias = int64_t(RRT_MLP_HIDDEN) * RRT_MLP_HIDDEN;
+  if (i >= nw + RRT_MLP_HIDDEN) return;
+  const float* p = g.part + int64_t(blockIdx.y) * g.splits * kGradPart + (i < nw ? i : kBias + i - nw);
   float s = 0.0f;
-#pragma unroll 8
-  for (int64_t m = r0; m < r1; ++m) s += bf16_value(dz[m * N + n]);
-  part[int64_t(blockIdx.y) * N + n] = s;
+  for (int z0 = 0; z0 < g.splits; z0 += 8) {
+    float v[8];
+#pragma unroll
+    for (int z = 0; z < 8; ++z) v[z] = z0 + z < g.splits ? p[(z0 + z) * kGradPart] : 0.0f;
+#pragma unroll
+    for (int z = 0; z < 8; ++z) s += v[z];
+  }
+  if (i < nw)
+    L.dw[i] = s;
+  else
+    L.db[i - nw] = s;
 }
 
 // dout = 2 (out - target) / count; loss += sum (out - target)^2 / count (FP64).
@@ -499,26 +615,6 @@ __global__ void adam_kernel(float* __restrict__ p, uint16_t* __restrict__ p_bf16
   if (p_bf16) p_bf16[t] = bf16_bits(pt);
 }
 
-// out[i] = sum over z < S of part[z count + i], in order of z.
-__global__ void sum_splits_kernel(const float* __restrict__ part, int S, int64_t count,
-                                  float* __restrict__ out) {
-  const int64_t i = int64_t(blockIdx.x) * blockDim.x + threadIdx.x;
-  if (i >= count) return;
-  float acc = 0.0f;
-  for (int z = 0; z < S; ++z) acc += part[int64_t(z) * count + i];
-  out[i] = acc;
-}
-
-// out[i] += sum over z < S of part[z count + i], in order of z.
-__global__ void sum_splits_acc_kernel(const float* __restrict__ part, int S, int64_t count,
-                                      float* __restrict__ out) {
-  const int64_t i = int64_t(blockIdx.x) * blockDim.x + threadIdx.x;
-  if (i >= count) return;
-  float acc = 0.0f;
-  for (int z = 0; z < S; ++z) acc += part[int64_t(z) * count + i];
-  out[i] += acc;
-}
-
 // 128 x 128 tiles when they still give every CU a workgroup, else 64 x 64.
 template <bool AT, bool BT, int EPI>
 int gemm(const GemmArgs& a, hipStream_t s) {
@@ -537,35 +633,30 @@ int gemm(const GemmArgs& a, hipStream_t s) {
 
 inline unsigned blocks(int64_t n, int per = 256) { return unsigned((n + per - 1) / per); }
 
-// Splits of the weight-gradient GEMM's reduction over a batch of B rows:
-// 256-row chunks, at most kMaxSplits, so that the 16 (or 8) 64 x 64 output
-// tiles of a layer become 256 (or 128) workgroups.
+// Partial weight gradients the workspace holds (256 x 256 floats each): one
+// per 256 rows, at most kMaxSplits.
 constexpr int kMaxSplits = 16;
-// 64-row chunks of the bias gradient's column sums per pass: their partials
-// (kColsumChunks x 256 floats) fit in the weight gradient's partial space.
-constexpr int kColsumChunks = kMaxSplits * RRT_MLP_HIDDEN / 64;
 inline int dw_splits(int64_t B) {
   const int64_t s = (B + 255) / 256;
   return int(s < 1 ? 1 : (s > kMaxSplits ? kMaxSplits : s));
 }
 
-// C[M][N] = A^T B over K with the k range split in `splits` (partials in
-// `part`, S M N floats), then summed in split order into out.
-int gemm_dw_split(GemmArgs a, int splits, float* part, hipStream_t s) {
-  if (a.M % 8 || a.N % 8) return RRT_ERR_UNSUPPORTED;
-  float* out = a.out_f32;
-  const int chunk = ((a.K + splits - 1) / splits + kBK - 1) / kBK * kBK;
-  splits = (a.K + chunk - 1) / chunk;
-  a.k_chunk = chunk;
-  a.out_f32 = part;
-  const dim3 grid(unsigned((a.N + 63) / 64), unsigned((a.M + 63) / 64), unsigned(splits));
-  hipLaunchKernelGGL((gemm_bf16<true, false, kEpiPlain, 1>), grid, dim3(256), 0, s, a);
-  int st = check_launch("gemm_bf16 split");
-  if (st) return st;
-  const int64_t count = int64_t(a.M) * a.N;
-  hipLaunchKernelGGL(sum_splits_kernel, dim3(blocks(count)), dim3(256), 0, s, part, splits, count,
-                     out);
-  return check_launch("sum_splits");
+// Gradients of `layers` layers over the batch, in as many row ranges as their
+// partials have room for (one: written straight out).
+int launch_grads(GradArgs g, int layers, hipStream_t s) {
+  const int64_t room = int64_t(dw_splits(g.B)) * RRT_MLP_HIDDEN * RRT_MLP_HIDDEN;
+  int64_t splits = room / (layers * kGradPart);
+  const int64_t most = (g.B + kGradRows - 1) / kGradRows;
+  if (splits > most) splits = most;
+  if (splits < 1) splits = 1;
+  g.rows = ((g.B + splits - 1) / splits + kGradRows - 1) / kGradRows * kGradRows;
+  g.splits = int((g.B + g.rows - 1) / g.rows);
+  hipLaunchKernelGGL(grad_kernel, dim3(4, 4, unsigned(layers * g.splits)), dim3(256), 0, s, g);
+  int st = check_launch("grad");
+  if (st || g.splits == 1) return st;
+  hipLaunchKernelGGL(grad_sum_kernel, dim3(unsigned((kGradPart + 255) / 256), unsigned(layers)),
+                     dim3(256), 0, s, g);
+  return check_launch("grad_sum");
 }
 
 }  // namespace
@@ -688,52 +779,39 @@ int launch_mlp_backward(const void* w, const void* x, int64_t B, const float* do
   hipLaunchKernelGGL(to_bf16_kernel, dim3(blocks(nout)), dim3(256), 0, s, dout, k.dout_bf16, nout);
   int st = check_launch("to_bf16");
   if (st) return st;
-  const uint16_t* dz = k.dout_bf16;
-  for (int l = RRT_MLP_WEIGHTS - 1; l >= 0; --l) {
-    const uint16_t* a_in = l == 0 ? static_cast<const uint16_t*>(x) : k.a[l - 1];
-    // dW_l = dz^T a_in : [out][in], reduction over the batch
-    GemmArgs gw = {};
-    gw.A = dz;          // stored [B][out] = [K][M] -> transposed A
-    gw.B = a_in;        // stored [B][in]  = [K][N]
-    gw.M = kOut[l];
-    gw.N = kIn[l];
-    gw.K = int(B);
-    gw.out_f32 = dw + mlp_weight_offset(l);
-    if ((st = gemm_dw_split(gw, dw_splits(B), k.dw_part, s))) return st;
-    // bias gradient: column sums of dz in chunks of 64 rows (the weight
-    // gradient's partials are already summed, so their space is free)
-    const int nch = int((B + 63) / 64);
-    for (int c0 = 0; c0 < nch; c0 += kColsumChunks) {
-      const int nc = nch - c0 < kColsumChunks ? nch - c0 : kColsumChunks;
-      const int64_t rows = (int64_t(c0) + nc) * 64 < B ? int64_t(nc) * 64 : B - int64_t(c0) * 64;
-      hipLaunchKernelGGL(colsum_kernel, dim3(blocks(kOut[l], 64), unsigned(nc)), dim3(64), 0, s,
-                         dz + int64_t(c0) * 64 * kOut[l], rows, kOut[l], 64, k.dw_part);
-      if ((st = check_launch("colsum"))) return st;
-      float* dst = db + mlp_bias_offset(l);
-      if (c0 == 0) {
-        hipLaunchKernelGGL(sum_splits_kernel, dim3(blocks(kOut[l])), dim3(256), 0, s, k.dw_part,
-                           nc, int64_t(kOut[l]), dst);
-      } else {
-        hipLaunchKernelGGL(sum_splits_acc_kernel, dim3(blocks(kOut[l])), dim3(256), 0, s,
-                           k.dw_part, nc, int64_t(kOut[l]), dst);
-      }
-      if ((st = check_launch("colsum sum"))) return st;
-    }
-    if (l == 0) break;
-    // dz_{l-1} = (dz W_l) * gelu'(z_{l-1})
+  // dz_{l-1} = (dz_l W_l) * gelu'(z_{l-1}): the buffers of dz hold three layers'
+  // at a time, so the gradients are taken in two launches
+  const uint16_t* dz[RRT_MLP_WEIGHTS];
+  dz[4] = k.dout_bf16;
+  auto step_back = [&](int l, uint16_t* next) {
     GemmArgs gx = {};
-    gx.A = dz;                           // [B][out]
+    gx.A = dz[l];                        // [B][out]
     gx.B = W + mlp_weight_offset(l);     // [out][in] = [K][N]
     gx.M = int(B);
     gx.N = kIn[l];
     gx.K = kOut[l];
     gx.zprev = k.z[l - 1];
-    uint16_t* next = k.dz[l & 1];
     gx.out_bf16 = next;
-    if ((st = gemm<false, false, kEpiGeluGrad>(gx, s))) return st;
-    dz = next;
-  }
-  return RRT_OK;
+    dz[l - 1] = next;
+    return gemm<false, false, kEpiGeluGrad>(gx, s);
+  };
+  auto grads = [&](int top, int layers) {
+    GradArgs g = {};
+    g.B = B;
+    g.part = k.dw_part;
+    for (int i = 0; i < layers; ++i) {
+      const int l = top - i;
+      g.layer[i] = {dz[l], l == 0 ? static_cast<const uint16_t*>(x) : k.a[l - 1], kIn[l],
+                    dw + mlp_weight_offset(l), db + mlp_bias_offset(l)};
+    }
+    return launch_grads(g, layers, s);
+  };
+  if ((st = step_back(4, k.dz[0]))) return st;
+  if ((st = step_back(3, k.dz[1]))) return st;
+  if ((st = grads(4, 3))) return st;
+  if ((st = step_back(2, k.dout_bf16))) return st;
+  if ((st = step_back(1, k.dz[0]))) return st;
+  return grads(1, 2);
 }
 
 int launch_mse(const float* out, const float* tgt, int64_t count, float* dout, double* loss,
