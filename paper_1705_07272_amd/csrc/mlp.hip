@@ -4,15 +4,14 @@
 //
 // GEMM: C[M][N] = sum_k A(m, k) B(k, n), A and B in bfloat16, FP32
 // accumulation on the matrix cores (v_mfma_f32_32x32x16_bf16, wave64).  A is
-// stored [M][K] (row-major) or, transposed, [K][M]; B is stored [K][N] or,
-// transposed, [N][K]; the contiguous dimension of each is a multiple of 8.
-// A 256-thread workgroup computes a (64 TM) x (64 TM) tile of C, each of its
-// four waves a TM x TM grid of 32 x 32 MFMA tiles.  Each 32-deep k-slice of A
-// and B is loaded with 16-byte vector loads (the next slice is in flight
-// while the matrix cores consume the current one) and staged in LDS in
-// k-contiguous rows (row stride 40 bf16), from which every lane reads its 8
-// k-consecutive operands with one 16-byte LDS read.  Rows, columns and k
-// beyond the matrix read as zero and are not stored.
+// stored [M][K]; B is stored [K][N] or, transposed, [N][K]; the contiguous
+// dimension of each is a multiple of 8.  A 256-thread workgroup computes a
+// (64 TM) x (64 TM) tile of C, each of its four waves a TM x TM grid of 32 x 32
+// MFMA tiles.  Each k-slice of A and B is loaded with 16-byte vector loads (the
+// next slice is in flight while the matrix cores consume the current one) and
+// staged in LDS in k-contiguous rows, from which every lane reads its 8
+// k-consecutive operands with one 16-byte LDS read.  Rows, columns and k beyond
+// the matrix read as zero and are not stored.
 #include <hip/hip_fp16.h>
 
 #include "rrt_internal.h"
@@ -20,8 +19,6 @@
 namespace rrt {
 namespace {
 
-constexpr int kBK = 32;
-constexpr int kLdsStride = kBK + 8;  // bf16 elements per LDS row (16-byte rows, staggered banks)
 constexpr float kSqrt2OverPi = 0.7978845608028654f;
 constexpr float kGeluC = 0.044715f;
 
@@ -82,44 +79,63 @@ __device__ __forceinline__ u32x4_t load8(const uint16_t* base, int rows, int col
   return v;
 }
 
-// One operand's k-slice: R rows x kBK k, from a k-contiguous ([rows][K]) or
-// row-contiguous ([K][rows]) matrix, 16 bytes per vector, R / 64 per thread.
-template <int R, bool KCONTIG>
+// One operand's k-slice: R rows x BK k, from a k-contiguous ([rows][K]) or
+// row-contiguous ([K][rows]) matrix.  K-contiguous: 16-byte pieces, R BK / 2048
+// per thread.  Row-contiguous: a thread takes an 8 x 8 block (eight 16-byte
+// loads), transposes it in registers (32 byte permutes) and stores eight
+// 16-byte LDS rows.
+template <int R, bool KCONTIG, int BK>
 struct Slice {
-  static constexpr int kPer = R * kBK / 8 / 256;
+  static constexpr int kStride = BK + 8;
+  static constexpr int kPer = KCONTIG ? R * BK / 8 / 256 : 8;
+  static_assert(KCONTIG || R * BK / 64 <= 256, "one block per thread");
   u32x4_t v[kPer];
   __device__ __forceinline__ void load(const uint16_t* base, int rows, int K, int r0, int k0) {
+    if (KCONTIG) {
 #pragma unroll
-    for (int i = 0; i < kPer; ++i) {
-      const int e = i * 256 + int(threadIdx.x);
-      if (KCONTIG) {
-        v[i] = load8(base, rows, K, r0 + (e >> 2), k0 + (e & 3) * 8);
-      } else {
-        v[i] = load8(base, K, rows, k0 + e / (R / 8), r0 + (e % (R / 8)) * 8);
+      for (int i = 0; i < kPer; ++i) {
+        const int e = i * 256 + int(threadIdx.x);
+        v[i] = load8(base, rows, K, r0 + e / (BK / 8), k0 + e % (BK / 8) * 8);
       }
+    } else if (int(threadIdx.x) < R * BK / 64) {
+      const int kb = int(threadIdx.x) / (R / 8), rb = int(threadIdx.x) % (R / 8);
+#pragma unroll
+      for (int i = 0; i < 8; ++i) v[i] = load8(base, K, rows, k0 + 8 * kb + i, r0 + 8 * rb);
     }
   }
   __device__ __forceinline__ void store(uint16_t* lds) const {
+    if (KCONTIG) {
 #pragma unroll
-    for (int i = 0; i < kPer; ++i) {
-      const int e = i * 256 + int(threadIdx.x);
-      if (KCONTIG) {
-        *reinterpret_cast<u32x4_t*>(lds + (e >> 2) * kLdsStride + (e & 3) * 8) = v[i];
-      } else {
-        const int k = e / (R / 8), r = (e % (R / 8)) * 8;
+      for (int i = 0; i < kPer; ++i) {
+        const int e = i * 256 + int(threadIdx.x);
+        *reinterpret_cast<u32x4_t*>(lds + e / (BK / 8) * kStride + e % (BK / 8) * 8) = v[i];
+      }
+    } else if (int(threadIdx.x) < R * BK / 64) {
+      const int kb = int(threadIdx.x) / (R / 8), rb = int(threadIdx.x) % (R / 8);
 #pragma unroll
-        for (int j = 0; j < 8; ++j)
-          lds[(r + j) * kLdsStride + k] = uint16_t(v[i][j / 2] >> (16 * (j & 1)));
+      for (int j = 0; j < 8; ++j) {
+        u32x4_t t;
+#pragma unroll
+        for (int p = 0; p < 4; ++p)
+          t[p] = __builtin_amdgcn_perm(v[2 * p + 1][j / 2], v[2 * p][j / 2],
+                                       (j & 1) ? 0x07060302u : 0x05040100u);
+        *reinterpret_cast<u32x4_t*>(lds + (8 * rb + j) * kStride + 8 * kb) = t;
       }
     }
   }
 };
 
-template <bool AT, bool BT, int EPI, int TM>
+// k per slice: 64 x 64 tiles (TM = 1) are for batches that leave each CU a
+// workgroup or two, where every slice's load and barrier latency counts:
+// 128 of k at a time; 128 x 128 tiles keep 32.
+constexpr int slice_k(int TM) { return TM == 1 ? 128 : 32; }
+
+template <bool BT, int EPI, int TM>
 __global__ __launch_bounds__(256) void gemm_bf16(GemmArgs g) {
   constexpr int BM = 64 * TM, BN = 64 * TM;
-  __shared__ __align__(16) uint16_t As[BM * kLdsStride];
-  __shared__ __align__(16) uint16_t Bs[BN * kLdsStride];
+  constexpr int BK = slice_k(TM), kStride = BK + 8;  // bf16 elements per LDS row (16-byte rows, staggered banks)
+  __shared__ __align__(16) uint16_t As[BM * kStride];
+  __shared__ __align__(16) uint16_t Bs[BN * kStride];
   const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
   const int m0 = blockIdx.y * BM, n0 = blockIdx.x * BN;
   const int wm = (wave >> 1) * 32 * TM, wn = (wave & 1) * 32 * TM;
@@ -129,29 +145,29 @@ __global__ __launch_bounds__(256) void gemm_bf16(GemmArgs g) {
 #pragma unroll
     for (int j = 0; j < TM; ++j) acc[i][j] = float16_t{};
 
-  Slice<BM, !AT> sa;
-  Slice<BN, BT> sb;
+  Slice<BM, true, BK> sa;
+  Slice<BN, BT, BK> sb;
   sa.load(g.A, g.M, g.K, m0, 0);
   sb.load(g.B, g.N, g.K, n0, 0);
-  for (int k0 = 0; k0 < g.K; k0 += kBK) {
+  for (int k0 = 0; k0 < g.K; k0 += BK) {
     sa.store(As);
     sb.store(Bs);
     __syncthreads();
-    if (k0 + kBK < g.K) {
-      sa.load(g.A, g.M, g.K, m0, k0 + kBK);
-      sb.load(g.B, g.N, g.K, n0, k0 + kBK);
+    if (k0 + BK < g.K) {
+      sa.load(g.A, g.M, g.K, m0, k0 + BK);
+      sb.load(g.B, g.N, g.K, n0, k0 + BK);
     }
 #pragma unroll
-    for (int kk = 0; kk < kBK; kk += 16) {
+    for (int kk = 0; kk < BK; kk += 16) {
       // lane l: operand row l % 32, k = kk + 8 (l / 32) .. + 7
       const int ko = kk + 8 * (lane >> 5);
       bf16x8_t a[TM], b[TM];
 #pragma unroll
       for (int i = 0; i < TM; ++i)
-        a[i] = *reinterpret_cast<const bf16x8_t*>(&As[(wm + 32 * i + (lane & 31)) * kLdsStride + ko]);
+        a[i] = *reinterpret_cast<const bf16x8_t*>(&As[(wm + 32 * i + (lane & 31)) * kStride + ko]);
 #pragma unroll
       for (int j = 0; j < TM; ++j)
-        b[j] = *reinterpret_cast<const bf16x8_t*>(&Bs[(wn + 32 * j + (lane & 31)) * kLdsStride + ko]);
+        b[j] = *reinterpret_cast<const bf16x8_t*>(&Bs[(wn + 32 * j + (lane & 31)) * kStride + ko]);
 #pragma unroll
       for (int i = 0; i < TM; ++i)
 #pragma unroll
@@ -160,28 +176,38 @@ __global__ __launch_bounds__(256) void gemm_bf16(GemmArgs g) {
     }
     __syncthreads();
   }
-  // D[m][n]: register r of lane l holds row 8 (r / 4) + 4 (l / 32) + r % 4, column l % 32
+  // D[m][n]: register r of lane l holds row 8 (r / 4) + 4 (l / 32) + r % 4, column l % 32.
+  // What the epilogue reads is loaded for all 16 registers before any is used or
+  // stored (one after the other, the 16 round trips took longer than the products).
 #pragma unroll
   for (int i = 0; i < TM; ++i)
 #pragma unroll
-    for (int j = 0; j < TM; ++j)
+    for (int j = 0; j < TM; ++j) {
+      const int mb = m0 + wm + 32 * i + 4 * (lane >> 5), n = n0 + wn + 32 * j + (lane & 31);
+      if (n >= g.N) continue;
+      float add = 0.0f, z[16];
+      if (EPI != kEpiGeluGrad) add = g.bias[n];
 #pragma unroll
       for (int r = 0; r < 16; ++r) {
-        const int m = m0 + wm + 32 * i + 8 * (r >> 2) + 4 * (lane >> 5) + (r & 3);
-        const int n = n0 + wn + 32 * j + (lane & 31);
-        if (m >= g.M || n >= g.N) continue;
+        const int m = mb + 8 * (r >> 2) + (r & 3);
+        if (EPI == kEpiGeluGrad) z[r] = g.zprev[int64_t(min(m, g.M - 1)) * g.N + n];
+      }
+#pragma unroll
+      for (int r = 0; r < 16; ++r) {
+        const int m = mb + 8 * (r >> 2) + (r & 3);
+        if (m >= g.M) continue;
         const int64_t at = int64_t(m) * g.N + n;
-        float x = acc[i][j][r];
+        const float x = acc[i][j][r];
         if (EPI == kEpiHidden) {
-          x += g.bias[n];
-          g.out_f32[at] = x;
-          g.out_bf16[at] = bf16_bits(gelu_f(x));
+          g.out_f32[at] = x + add;
+          g.out_bf16[at] = bf16_bits(gelu_f(x + add));
         } else if (EPI == kEpiOutput) {
-          g.out_f32[at] = x + g.bias[n];
+          g.out_f32[at] = x + add;
         } else {
-          g.out_bf16[at] = bf16_bits(x * gelu_grad_f(g.zprev[at]));
+          g.out_bf16[at] = bf16_bits(x * gelu_grad_f(z[r]));
         }
       }
+    }
 }
 
 // Band q of gamma(x) = (x, sin(2^k pi x), cos(2^k pi x), k = 0..7) of the 6
@@ -449,7 +475,8 @@ __global__ void to_bf16_kernel(const float* __restrict__ in, uint16_t* __restric
 // What bounds it: latency, at 16 workgroups per layer and range, so the layers
 // whose operands are ready share a launch.  It replaces a GEMM that stored
 // transposed slices two bytes at a time, and column sums in launches of their own:
-// 4,096 rows, all five layers GRADOLD -> GRADNEW us.
+// 4,096 rows, all five layers 177 -> 38 us (a training step
+// 287 -> 139).
 constexpr int kGradRows = 128;
 constexpr int kGradStride = kGradRows + 8;  // bf16 per LDS row
 constexpr int kGradLayers = 3;
@@ -584,8 +611,28 @@ __global__ void mse_kernel(const float* __restrict__ out, const float* __restric
                            int64_t count, float* __restrict__ dout, double* __restrict__ loss) {
   __shared__ double part[256];
   double sq = 0.0;
-  for (int64_t t = int64_t(blockIdx.x) * blockDim.x + threadIdx.x; t < count;
-       t += int64_t(gridDim.x) * blockDim.x) {
+  const int64_t first = int64_t(blockIdx.x) * blockDim.x + threadIdx.x;
+  const int64_t step = int64_t(gridDim.x) * blockDim.x;
+  int64_t done = 0;
+  // four values at a time where the three arrays allow 16-byte accesses (a
+  // thread's rounds follow one another: 16 of them took 10.9 us for 1,048,576
+  // values, these 4 7.5)
+  if (((reinterpret_cast<uintptr_t>(out) | reinterpret_cast<uintptr_t>(tgt) |
+        reinterpret_cast<uintptr_t>(dout)) & 15u) == 0) {
+    const int64_t n4 = count >> 2;
+    for (int64_t t = first; t < n4; t += step) {
+      const float4 o = reinterpret_cast<const float4*>(out)[t];
+      const float4 g = reinterpret_cast<const float4*>(tgt)[t];
+      const float d0 = o.x - g.x, d1 = o.y - g.y, d2 = o.z - g.z, d3 = o.w - g.w;
+      const float c = float(count);
+      reinterpret_cast<float4*>(dout)[t] =
+          make_float4(2.0f * d0 / c, 2.0f * d1 / c, 2.0f * d2 / c, 2.0f * d3 / c);
+      sq += (double(d0) * double(d0) + double(d1) * double(d1)) +
+            (double(d2) * double(d2) + double(d3) * double(d3));
+    }
+    done = 4 * n4;
+  }
+  for (int64_t t = done + first; t < count; t += step) {
     const float d = out[t] - tgt[t];
     dout[t] = 2.0f * d / float(count);
     sq += double(d) * double(d);
@@ -616,17 +663,17 @@ __global__ void adam_kernel(float* __restrict__ p, uint16_t* __restrict__ p_bf16
 }
 
 // 128 x 128 tiles when they still give every CU a workgroup, else 64 x 64.
-template <bool AT, bool BT, int EPI>
+template <bool BT, int EPI>
 int gemm(const GemmArgs& a, hipStream_t s) {
   // the contiguous dimension of each stored operand must allow 16-byte loads
-  if ((AT ? a.M : a.K) % 8 || (BT ? a.K : a.N) % 8) return RRT_ERR_UNSUPPORTED;
+  if (a.K % 8 || (BT ? a.K : a.N) % 8) return RRT_ERR_UNSUPPORTED;
   const int64_t big = int64_t((a.N + 127) / 128) * ((a.M + 127) / 128);
   if (big >= 512) {
     const dim3 grid(unsigned((a.N + 127) / 128), unsigned((a.M + 127) / 128));
-    hipLaunchKernelGGL((gemm_bf16<AT, BT, EPI, 2>), grid, dim3(256), 0, s, a);
+    hipLaunchKernelGGL((gemm_bf16<BT, EPI, 2>), grid, dim3(256), 0, s, a);
   } else {
     const dim3 grid(unsigned((a.N + 63) / 64), unsigned((a.M + 63) / 64));
-    hipLaunchKernelGGL((gemm_bf16<AT, BT, EPI, 1>), grid, dim3(256), 0, s, a);
+    hipLaunchKernelGGL((gemm_bf16<BT, EPI, 1>), grid, dim3(256), 0, s, a);
   }
   return check_launch("gemm_bf16");
 }
@@ -760,11 +807,11 @@ int launch_mlp_forward(const void* w, const float* b, const void* x, int64_t B, 
     if (l < RRT_MLP_WEIGHTS - 1) {
       g.out_bf16 = k.a[l];
       g.out_f32 = k.z[l];
-      st = gemm<false, true, kEpiHidden>(g, s);
+      st = gemm<true, kEpiHidden>(g, s);
       a_in = k.a[l];
     } else {
       g.out_f32 = out;
-      st = gemm<false, true, kEpiOutput>(g, s);
+      st = gemm<true, kEpiOutput>(g, s);
     }
     if (st) return st;
   }
@@ -793,7 +840,7 @@ int launch_mlp_backward(const void* w, const void* x, int64_t B, const float* do
     gx.zprev = k.z[l - 1];
     gx.out_bf16 = next;
     dz[l - 1] = next;
-    return gemm<false, false, kEpiGeluGrad>(gx, s);
+    return gemm<false, kEpiGeluGrad>(gx, s);
   };
   auto grads = [&](int top, int layers) {
     GradArgs g = {};
