@@ -246,9 +246,7 @@ int rrt_relight_prepare(const rrt_light* L, unsigned flags, void* ws, size_t ws_
   char* base = static_cast<char*>(ws);
   float* dense = reinterpret_cast<float*>(base + w.dense_off);
   float* src = reinterpret_cast<float*>(base + w.src_off);
-  st = launch_scatter_light(L->idx, L->val, L->dtype, L->k, L->n, 6, dense, s);
-  if (st) return st;
-  st = launch_haar_inverse(dense, src, L->n, 6, s, true);
+  st = launch_source_map(L->idx, L->val, L->dtype, L->k, L->n, 6, dense, src, s, true);
   if (st || !(flags & RRT_CHAIN_RULE)) return st;
   // the staging buffer is free now: it takes the 2x2 block coefficients
   return launch_source_blocks(src, L->n, dense, s);
@@ -399,9 +397,7 @@ int rrt_relight_latlong(const rrt_light* L, const rrt_latlong_rotations* R, cons
   float* dense = reinterpret_cast<float*>(base + w.dense_off);
   float* src = reinterpret_cast<float*>(base + w.src_off);
   float* grid = reinterpret_cast<float*>(base + w.grid_off);
-  st = launch_scatter_light(L->idx, L->val, L->dtype, L->k, L->n, 2, dense, s);
-  if (st) return st;
-  st = launch_haar_inverse(dense, src, L->n, 2, s);
+  st = launch_source_map(L->idx, L->val, L->dtype, L->k, L->n, 2, dense, src, s, false);
   if (st) return st;
   st = launch_latlong_grid(L->n, grid, s);
   if (st || T->nvert == 0) return st;

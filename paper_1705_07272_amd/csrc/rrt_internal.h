@@ -49,6 +49,11 @@ size_t topk_workspace_bytes(int64_t rows, int64_t len, int k);
 int launch_topk(const float* x, int64_t rows, int64_t len, int k, int32_t* idx, float* val,
                 void* ws, hipStream_t s);
 
+// Source map pix of a sparse lighting: scatter and inverse transform, in one
+// launch where the map and the entries allow, else through the dense staging
+// map (haar.hip; squares and strips as below and above).
+int launch_source_map(const int32_t* idx, const void* val, int dtype, int k, int n, int squares,
+                      float* dense, float* pix, hipStream_t s, bool strips);
 // Coefficient scatter into a zeroed dense map (relight.hip).
 // squares: 6 (cube map) or 2 (longitude-latitude map)
 int launch_scatter_light(const int32_t* idx, const void* val, int dtype, int k, int n, int squares,
