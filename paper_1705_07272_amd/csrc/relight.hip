@@ -22,7 +22,8 @@
 //   * the transport entries are decoded once per vertex into an LDS list; the
 //     entries inside the block read the image, the coarser ones read the FP64
 //     block-sum grid after the levels above the blocks; products are
-//     accumulated per lane and reduced with lane shuffles;
+//     accumulated per lane and reduced with lane shuffles (a dense row has no
+//     list: each image and grid position reads its own entry);
 //   * a block that holds no listed entry only contributes its sum to the
 //     levels above it and skips the image, the levels and the entry scan.
 //
@@ -655,6 +656,19 @@ __device__ __forceinline__ float4 chain_block(float4 c, int sf, float3 d, float3
   return make_float4(2.0f * c.x, -2.0f * gx, -2.0f * gy, gxy);
 }
 
+// Flat index of the coefficient at in-place position (pr, pc) of a face (the
+// inverse of decode_slot; (0, 0) is the face's scaling coefficient): its block
+// side is twice the lowest set bit of pr | pc.
+__device__ __forceinline__ int slot_index(int face, int pr, int pc, int logn) {
+  const int m = pr | pc;
+  if (m == 0) return face << (2 * logn);
+  const int tz = __builtin_ctz(unsigned(m));
+  const int q = (1 << logn) >> (tz + 1);
+  const int r = (pr >> (tz + 1)) + (((pr >> tz) & 1) ? q : 0);
+  const int c = (pc >> (tz + 1)) + (((pc >> tz) & 1) ? q : 0);
+  return (face << (2 * logn)) + (r << logn) + c;
+}
+
 // Where a transport entry is consumed when the faces of rank [g0, g0 + FG)
 // among `faces` are processed together.  Block gi = (face rank - g0) G^2 +
 // block row * G + block column holds every coefficient of a block at most Q
@@ -694,7 +708,8 @@ __device__ __forceinline__ int classify(int idx, int logn, int G, unsigned faces
 // slower, so it keeps its 5.
 // LOGN: log2 n where the block is gathered in quarters (cube map, exact
 // rotation, n >= 32), else 0 and n is a parameter.
-template <int Q, bool CHAIN, bool BRDF, bool LL, int LOGN>
+// DENSE: rows hold every coefficient in order (no index rows, no list).
+template <int Q, bool CHAIN, bool BRDF, bool LL, int LOGN, bool DENSE>
 __global__ __launch_bounds__(kThreads, CHAIN || LOGN ? 5 : 1) void relight_kernel(RelightParams p) {
   constexpr int NF = LL ? 2 : 6;  // faces (squares) of the map
   constexpr bool QUARTERS = LOGN > 0;
@@ -739,7 +754,7 @@ __global__ __launch_bounds__(kThreads, CHAIN || LOGN ? 5 : 1) void relight_kerne
   // index row of this vertex: its own, or its cluster's support row
   const int32_t* idx_row = nullptr;
   bool row_valid = true;
-  if (p.tidx) {
+  if constexpr (!DENSE) {
     if (p.cluster) {
       const int c = p.cluster[v];
       row_valid = c >= 0 && c < p.nclusters;
@@ -760,12 +775,16 @@ __global__ __launch_bounds__(kThreads, CHAIN || LOGN ? 5 : 1) void relight_kerne
   const int nnz = row_valid ? p.nnz : 0;
   const int listed = row_valid ? p.listed : 0;
 
-  // faces touched by this vertex's transport row
+  // faces touched by this vertex's transport row (a dense row: all)
   unsigned m = 0;
+  if constexpr (!DENSE) {
 #pragma unroll 4
-  for (int e = lane; e < nnz; e += kThreads) {
-    const int idx = idx_row ? idx_row[e] : e;
-    if (idx >= 0 && idx < NF * (n << logn)) m |= 1u << (idx >> (2 * logn));
+    for (int e = lane; e < nnz; e += kThreads) {
+      const int idx = idx_row[e];
+      if (idx >= 0 && idx < NF * (n << logn)) m |= 1u << (idx >> (2 * logn));
+    }
+  } else if (nnz > 0) {
+    m = (1u << NF) - 1u;
   }
   unsigned faces = 0;
 #pragma unroll
@@ -794,7 +813,8 @@ __global__ __launch_bounds__(kThreads, CHAIN || LOGN ? 5 : 1) void relight_kerne
     wave_sync();
   }
 
-  for (int f = 0; f < p.nframes; ++f) {
+  // this wave's frames: every gridDim.y-th
+  for (int f = blockIdx.y; f < p.nframes; f += gridDim.y) {
     IRot R = {};
     if constexpr (!LL) {
       R = frame_vertex_rotation(p.vrot + v * 9, p.frot ? p.frot + f * 9 : nullptr, scale_bits(logn));
@@ -815,7 +835,7 @@ __global__ __launch_bounds__(kThreads, CHAIN || LOGN ? 5 : 1) void relight_kerne
       const int g0 = grp * FG;
       const int nfg = min(FG, nf - g0);
 
-      if (f == 0 || ngroups > 1) {
+      if (!DENSE && (f == int(blockIdx.y) || ngroups > 1)) {
         // List the first `listed` entries in entry order: block entries from
         // the front, coarse entries from the back.
         nfine = 0;
@@ -833,7 +853,7 @@ __global__ __launch_bounds__(kThreads, CHAIN || LOGN ? 5 : 1) void relight_kerne
 #pragma unroll
           for (int u = 0; u < kListChunks; ++u) {
             const int e = c0 + u * kThreads + lane;
-            ix[u] = e < listed ? (idx_row ? idx_row[e] : e) : -1;
+            ix[u] = e < listed ? idx_row[e] : -1;
             vx[u] = e < listed ? transport_value(p.tval, p.tscale, p.dtype, v, p.nnz, e) : 0.0f;
           }
 #pragma unroll
@@ -1101,10 +1121,23 @@ __global__ __launch_bounds__(kThreads, CHAIN || LOGN ? 5 : 1) void relight_kerne
                           ldexpf(img[key & ((1 << kOffBits) - 1)], -(key >> kLogbShift)), comp);
               }
             }
+            // a dense row has one entry for every position of the image (the
+            // block's corner belongs to the levels above); looking through the
+            // row for each block instead took 196 us for 1,000 vertices at
+            // n = 32, this 55
+            if constexpr (DENSE) {
+              for (int e = lane == 0 ? kThreads : lane; e < Q * Q && nnz > 0; e += kThreads) {
+                const int pr = e >> LOGQ, pc = e & (Q - 1);
+                const int at = slot_index(face, by * Q + pr, bx * Q + pc, logn);
+                const int logb = __builtin_ctz(unsigned(pr | pc)) + 1;
+                acc_add(acc, transport_value(p.tval, p.tscale, p.dtype, v, p.nnz, at),
+                        ldexpf(img[pr * STRIDE + pc], -logb), comp);
+              }
+            }
             // entries past the list
-            for (int e = listed + lane; e < nnz; e += kThreads) {
+            for (int e = listed + lane; !DENSE && e < nnz; e += kThreads) {
               int key = 0;
-              const int kind = classify<Q, NF>(idx_row ? idx_row[e] : e, logn, G, faces, g0, FG, key);
+              const int kind = classify<Q, NF>(idx_row[e], logn, G, faces, g0, FG, key);
               if (kind == 0 && ((key >> kOffBits) & ((1 << kBlockBits) - 1)) == gi)
                 acc_add(acc, transport_value(p.tval, p.tscale, p.dtype, v, p.nnz, e),
                         ldexpf(img[key & ((1 << kOffBits) - 1)], -(key >> kLogbShift)), comp);
@@ -1138,9 +1171,18 @@ __global__ __launch_bounds__(kThreads, CHAIN || LOGN ? 5 : 1) void relight_kerne
         const int at = listed - 1 - k;
         acc_add(acc, lval[at], float(gS[lkey[at]]), comp);
       }
-      for (int e = listed + lane; e < nnz; e += kThreads) {
+      if constexpr (DENSE) {
+        // dense row: the face's scaling coefficient and the levels above the blocks
+        for (int k = lane; k < nfg * G2 && nnz > 0; k += kThreads) {
+          const int at = k & (G2 - 1);
+          const int idx = slot_index(nth_face(faces, g0 + (k >> (2 * (logn - LOGQ)))),
+                                     (at >> (logn - LOGQ)) * Q, (at & (G - 1)) * Q, logn);
+          acc_add(acc, transport_value(p.tval, p.tscale, p.dtype, v, p.nnz, idx), float(gS[k]), comp);
+        }
+      }
+      for (int e = listed + lane; !DENSE && e < nnz; e += kThreads) {
         int key = 0;
-        if (classify<Q, NF>(idx_row ? idx_row[e] : e, logn, G, faces, g0, FG, key) == 1)
+        if (classify<Q, NF>(idx_row[e], logn, G, faces, g0, FG, key) == 1)
           acc_add(acc, transport_value(p.tval, p.tscale, p.dtype, v, p.nnz, e), float(gS[key]),
                   comp);
       }
@@ -1330,6 +1372,9 @@ __global__ void rotate_pixels(const float* __restrict__ src, const float* __rest
   dst[int64_t(r) * 6 * per_face + q] = src[min(at, unsigned(6 * per_face - 1))];
 }
 
+// Waves of a full chip: 256 CUs x 4 SIMDs x 5.
+constexpr int64_t kRoundWaves = 5120;
+
 template <int Q, bool CHAIN = false, bool BRDF = false, bool LL = false, int LOGN = 0>
 int launch_q(const RelightParams& prm_in, int64_t nvert, hipStream_t s) {
   RelightParams prm = prm_in;
@@ -1340,8 +1385,22 @@ int launch_q(const RelightParams& prm_in, int64_t nvert, hipStream_t s) {
     prm.ll_tab_off = int(lds);
     lds += size_t(latlong_grid_floats(1 << prm.logn)) * 4;
   }
-  hipLaunchKernelGGL((relight_kernel<Q, CHAIN, BRDF, LL, LOGN>), dim3(unsigned(nvert)),
-                     dim3(kThreads), lds, s, prm);
+  // A vertex's frames share its entry list, but a wave per vertex can be too few
+  // of them, or leave the last round of the chip (kRoundWaves at a time) mostly
+  // empty: the frames are divided until there are eight rounds.
+  // 12,500 vertices x 64 frames at n = 128 (2.4 rounds undivided): 8.07 -> 7.33
+  // ms; the list is then built once for 16 frames.
+  int64_t split = nvert > 0 ? (8 * kRoundWaves + nvert - 1) / nvert : 1;
+  if (split > prm.nframes) split = prm.nframes;
+  if (split > 65535) split = 65535;
+  const dim3 grid(unsigned(nvert), static_cast<unsigned>(split));
+  if (prm.tidx) {
+    hipLaunchKernelGGL((relight_kernel<Q, CHAIN, BRDF, LL, LOGN, false>), grid, dim3(kThreads), lds, s,
+                       prm);
+  } else {
+    hipLaunchKernelGGL((relight_kernel<Q, CHAIN, BRDF, LL, LOGN, true>), grid, dim3(kThreads), lds, s,
+                       prm);
+  }
   return check_launch("relight_kernel");
 }
 
@@ -1398,7 +1457,8 @@ int launch_relight(const RelightLaunch& a, hipStream_t s) {
   p.logn = ilog2(a.n);
   p.dtype = a.t_dtype;
   p.comp = (a.flags & RRT_COMPENSATED) ? 1 : 0;
-  p.listed = a.nnz < kMaxListed ? a.nnz : kMaxListed;
+  // a dense row needs no list: its entries are found by position
+  p.listed = !a.t_idx ? 0 : (a.nnz < kMaxListed ? a.nnz : kMaxListed);
   const int G = a.n < kBlock ? 1 : a.n / kBlock;
   const int fit = kGroupBytes / (G * G * 8);
   const int nf = a.latlong ? 2 : 6;
