@@ -397,7 +397,7 @@ int rrt_relight_latlong(const rrt_light* L, const rrt_latlong_rotations* R, cons
   float* dense = reinterpret_cast<float*>(base + w.dense_off);
   float* src = reinterpret_cast<float*>(base + w.src_off);
   float* grid = reinterpret_cast<float*>(base + w.grid_off);
-  st = launch_source_map(L->idx, L->val, L->dtype, L->k, L->n, 2, dense, src, s, false);
+  st = launch_source_map(L->idx, L->val, L->dtype, L->k, L->n, 2, dense, src, s, true);
   if (st) return st;
   st = launch_latlong_grid(L->n, grid, s);
   if (st || T->nvert == 0) return st;

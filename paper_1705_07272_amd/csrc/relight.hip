@@ -144,6 +144,13 @@ __device__ __forceinline__ Slot decode_slot(int idx, int logn, int nf) {
   return s;
 }
 
+// Texel of a lane in an 8 x 8 patch, Morton order: 16 consecutive lanes take a
+// 4 x 4 block of texels.
+__device__ __forceinline__ int morton_x(int lane) {
+  return (lane & 1) | ((lane >> 1) & 2) | ((lane >> 2) & 4);
+}
+__device__ __forceinline__ int morton_y(int lane) { return morton_x(lane >> 1); }
+
 struct Acc {
   float s, c;
 };
@@ -242,41 +249,31 @@ __device__ __forceinline__ float sqrt_rn(float x) {
 // row = #{k < H : q_y <= C_k}, c = #{k < H : q_z <= C_k rho} (C_k =
 // cos(k pi / H), decreasing, so both counts are binary searches), column = c
 // for q_x >= 0, else W - 1 - c.
-// Returns the flat index over the two H x H squares.
+// Returns the flat index over the two H x H squares (latlong_index).
 struct LLTab {
   const float* rs;   // [H] sin of row centres
   const float* rc;   // [H] cos of row centres
   const float* cs;   // [2H] sin of column centres
   const float* cc;   // [2H] cos of column centres
-  const float* bnd;  // [H] cos(k pi / H)
+  const float* bnd;  // [H + 1] cos(k pi / H); +inf and -inf at both ends (never passed)
 };
 
-__device__ __forceinline__ unsigned latlong_source(const LLTab& t, int i, int jc, float cb,
-                                                   float sb, int logh, int sa) {
-#pragma clang fp contract(off)
-  const int H = 1 << logh;
-  const float px = t.rs[i] * t.cs[jc];
-  const float py = t.rc[i];
-  const float pz = t.rs[i] * t.cc[jc];
-  const float qy = cb * py - sb * pz;
-  const float qz = sb * py + cb * pz;
-  const float rho = sqrt_rn(px * px + qz * qz);
-  int row = 0, c = 0;
-  for (int step = H >> 1; step >= 1; step >>= 1) {
-    row += (qy <= t.bnd[row + step]) ? step : 0;
-    c += (qz <= t.bnd[c + step] * rho) ? step : 0;
+// Flat index of (row, column) over the two squares: strips of eight columns
+// (strip_offset; the squares' strips follow one another) for H >= 8.
+template <int LOGH>
+__device__ __forceinline__ unsigned latlong_index(int row, int col) {
+  constexpr int H = 1 << LOGH;
+  if constexpr (LOGH >= 3) {
+    const unsigned lo = bit_select(7u, unsigned(col), unsigned(row) << 3);
+    return ((unsigned(col) & ~7u) << LOGH) + lo;
+  } else {
+    return (unsigned(col >> LOGH) << (2 * LOGH)) + (unsigned(row) << LOGH) + unsigned(col & (H - 1));
   }
-  int col = px >= 0.0f ? c : 2 * H - 1 - c;
-  col = (col + sa) & (2 * H - 1);
-  return (unsigned(col >> logh) << (2 * logh)) + (unsigned(row) << logh) + unsigned(col & (H - 1));
 }
 
-// The same rule for a compile-time H = 2^LOGH: the two searches unroll, the
-// table offsets become immediates and the searches of a lane's texels can
-// be interleaved.
 template <int LOGH>
-__device__ __forceinline__ unsigned latlong_source_h(const LLTab& t, int i, int jc, float cb,
-                                                     float sb, int sa) {
+__device__ __forceinline__ unsigned latlong_source(const LLTab& t, int i, int jc, float cb,
+                                                   float sb, int sa) {
 #pragma clang fp contract(off)
   constexpr int H = 1 << LOGH;
   const float px = t.rs[i] * t.cs[jc];
@@ -286,32 +283,106 @@ __device__ __forceinline__ unsigned latlong_source_h(const LLTab& t, int i, int 
   const float qz = sb * py + cb * pz;
   const float rho = sqrt_rn(px * px + qz * qz);
   int row = 0, c = 0;
-#pragma unroll
+#pragma unroll 1
   for (int step = H >> 1; step >= 1; step >>= 1) {
     row += (qy <= t.bnd[row + step]) ? step : 0;
     c += (qz <= t.bnd[c + step] * rho) ? step : 0;
   }
   int col = px >= 0.0f ? c : 2 * H - 1 - c;
   col = (col + sa) & (2 * H - 1);
-  return (unsigned(col >> LOGH) << (2 * LOGH)) + (unsigned(row) << LOGH) + unsigned(col & (H - 1));
+  return latlong_index<LOGH>(row, col);
+}
+
+// The same rule without the searches, for a unit (cb, sb).  A count #{k : x <=
+// C_k} is the angle acos x in rows (or columns) but for the boundary it rounds
+// to: an estimate of the angle less than half a texel off names that boundary,
+// and one comparison with it decides, as the search would.  acos x =
+// sqrt(1 - |x|) (c0 + c1 |x| + c2 x^2), mirrored for x < 0: a minimax fit (3.3e-4, 0.054
+// rows at H = 512); next to the poles the binary32 roundings of x add less than
+// 7e-4 (0.11 rows).
+// The azimuth's comparison takes rho = s rsq(s), s = q_x^2 + q_z^2, within 1.8e-7 of the
+// square root of s; correctly rounded, rho and C_k rho differ from it by at
+// most 3.6e-7 rho, so a comparison closer than 4e-7 rho is made again with the
+// rounded rho (EXACT): `gap` gets the smallest distance beyond that.
+//
+// What bounds it: vector issue.  Two binary searches take 7 log2 H operations
+// and dependent LDS reads per texel, the estimates 48 instructions in all and
+// two independent reads.  50,000 vertices at H = 128: 3.26 -> 2.01 ms (the rounded rho
+// for every texel 2.15; the whole search again for a close one 2.69).
+template <int LOGH, bool EXACT>
+__device__ __forceinline__ unsigned latlong_fast(const LLTab& t, int i, int jc, float cb, float sb,
+                                                 int sa, float& gap) {
+#pragma clang fp contract(off)
+  constexpr int H = 1 << LOGH;
+  constexpr float kRows = float(H) * 0.318309886f;  // H / pi
+  constexpr float kMagic = 12582912.0f;              // 1.5 2^23: rounds to an integer
+  const float px = t.rs[i] * t.cs[jc];
+  const float py = t.rc[i];
+  const float pz = t.rs[i] * t.cc[jc];
+  const float qy = cb * py - sb * pz;
+  const float qz = sb * py + cb * pz;
+  const float s = px * px + qz * qz;
+  const float rr = __builtin_amdgcn_rsqf(s);
+  const float rho = EXACT ? sqrt_rn(s) : s * rr;
+  // nearest boundary of the angle of x in texels
+  auto boundary = [](float x) {
+    const float ax = fabsf(x);
+    const float root = __builtin_amdgcn_sqrtf(fabsf(1.0f - ax));
+    const float poly = __builtin_fmaf(
+        __builtin_fmaf(0.05139111f * kRows, ax, -0.20549912f * kRows), ax, 1.57047056f * kRows);
+    const float from_equator = __builtin_fmaf(-root, poly, 0.5f * float(H));
+    const float est = (kMagic + 0.5f * float(H)) - copysignf(from_equator, x);
+    return int(__float_as_uint(est) & 0xffffu);
+  };
+  const int kr = boundary(qy), kc = boundary(qz * rr);
+  const int row = kr - int(qy > t.bnd[kr]);
+  const float edge = t.bnd[kc] * rho;
+  const int c = kc - int(qz > edge);
+  if (!EXACT) gap = fminf(gap, __builtin_fmaf(-4e-7f, rho, fabsf(qz - edge)));
+  // c for q_x >= 0, else 2H - 1 - c (q_x is never zero: column centres)
+  int col = c ^ ((__float_as_int(px) >> 31) & (2 * H - 1));
+  col = (col + sa) & (2 * H - 1);
+  return latlong_index<LOGH>(row, col);
 }
 
 // A lane's T x T gathered texels of block (by, bx) of square `face` through
-// the longitude-latitude rule at H = 2^LOGH.
+// the longitude-latitude rule at H = 2^LOGH; lane (gy, gx) of a patch.
 template <int LOGH, int Q, int TS, int T>
 __device__ __forceinline__ void latlong_gather(float (&val)[T][T], const LLTab& tab,
                                                __amdgpu_buffer_rsrc_t src, int face, int by,
-                                               int bx, int ty, int tx, float cb, float sb, int sa,
-                                               int sc) {
+                                               int bx, int gy, int gx, float cb, float sb, int sa,
+                                               int sc, bool unit) {
   constexpr int n = 1 << LOGH;
+  const int i0 = by * Q + gy, j0 = face * n + bx * Q + gx + sc;
+  if (unit) {
 #pragma unroll
-  for (int a = 0; a < T; ++a)
+    for (int a = 0; a < T; ++a) {
+      float gap = 1.0f;
 #pragma unroll
-    for (int b = 0; b < T; ++b) {
-      const int i = by * Q + TS * a + ty;
-      const int jc = (face * n + bx * Q + TS * b + tx + sc) & (2 * n - 1);
-      val[a][b] = load_src(src, latlong_source_h<LOGH>(tab, i, jc, cb, sb, sa));
+      for (int b = 0; b < T; ++b)
+        val[a][b] = load_src(src, latlong_fast<LOGH, false>(tab, i0 + TS * a, (j0 + TS * b) & (2 * n - 1),
+                                                            cb, sb, sa, gap));
+      if (gap > 0.0f) continue;
+#pragma unroll 1
+      for (int b = 0; b < T; ++b) {
+        const float x = load_src(src, latlong_fast<LOGH, true>(tab, i0 + TS * a, (j0 + TS * b) & (2 * n - 1),
+                                                               cb, sb, sa, gap));
+#pragma unroll
+        for (int j = 0; j < T; ++j) val[a][j] = j == b ? x : val[a][j];
+      }
     }
+  } else {
+    // not a rotation: the searches
+#pragma unroll 1
+    for (int e = 0; e < T * T; ++e) {
+      const float x = load_src(src, latlong_source<LOGH>(tab, i0 + TS * (e / T),
+                                                         (j0 + TS * (e % T)) & (2 * n - 1), cb, sb, sa));
+#pragma unroll
+      for (int a = 0; a < T; ++a)
+#pragma unroll
+        for (int b = 0; b < T; ++b) val[a][b] = a * T + b == e ? x : val[a][b];
+    }
+  }
 }
 
 // Unscaled 2x2 levels with block side 2..T inside a thread's T x T tile, in
@@ -413,13 +484,6 @@ __device__ __forceinline__ void tile_level_above(float& s, float* img, int lane,
 // 8.07 ms.
 // ---------------------------------------------------------------------------
 constexpr int kMixed = 6;  // quarter_face: several faces
-
-// Texel of a lane in an 8 x 8 patch, Morton order: 16 consecutive lanes take a
-// 4 x 4 block of texels.
-__device__ __forceinline__ int morton_x(int lane) {
-  return (lane & 1) | ((lane >> 1) & 2) | ((lane >> 2) & 4);
-}
-__device__ __forceinline__ int morton_y(int lane) { return morton_x(lane >> 1); }
 
 // Source face of quarter q (2 x 2) of block kb of a face, or kMixed: a source
 // face is a convex cone, so four corner texels in one face put every texel of
@@ -707,12 +771,12 @@ __device__ __forceinline__ int classify(int idx, int logn, int G, unsigned faces
 // unspilled; the lat-long variant held to 6 waves spills more and runs
 // slower, so it keeps its 5.
 // LOGN: log2 n where the block is gathered in quarters (cube map, exact
-// rotation, n >= 32), else 0 and n is a parameter.
+// rotation, n >= 32) and for the lat-long map, else 0 and n is a parameter.
 // DENSE: rows hold every coefficient in order (no index rows, no list).
 template <int Q, bool CHAIN, bool BRDF, bool LL, int LOGN, bool DENSE>
 __global__ __launch_bounds__(kThreads, CHAIN || LOGN ? 5 : 1) void relight_kernel(RelightParams p) {
   constexpr int NF = LL ? 2 : 6;  // faces (squares) of the map
-  constexpr bool QUARTERS = LOGN > 0;
+  constexpr bool QUARTERS = LOGN > 0 && !LL;
   // Blocks holding no listed entry of their own only feed the levels above
   // them through their sum: with SUM_ONLY such a block skips the image, the
   // levels inside it and the entry scan (with CHAIN it also skips the chain
@@ -731,13 +795,13 @@ __global__ __launch_bounds__(kThreads, CHAIN || LOGN ? 5 : 1) void relight_kerne
   const int lane = threadIdx.x;
   const int64_t v = p.order ? int64_t(p.order[blockIdx.x]) : int64_t(blockIdx.x);
   if (v < 0 || v >= p.nvert) return;  // not a permutation entry: skipped (uniform)
-  const int logn = QUARTERS ? LOGN : p.logn;
+  const int logn = LOGN ? LOGN : p.logn;
   const int n = 1 << logn;
   const int G = n >> LOGQ;  // blocks per face side
   const int G2 = G * G;
   const int FG = p.group_faces;
-  // the cube map's source map is in strips of eight columns for n >= 8 (Q >= 8)
-  constexpr bool STRIPS = Q >= 8 && !LL;
+  // the source map is in strips of eight columns for n >= 8 (Q >= 8)
+  constexpr bool STRIPS = Q >= 8;
   const __amdgpu_buffer_rsrc_t src = source_resource(
       p.src, NF * (n << logn),
       LL ? 0u : (STRIPS ? strip_bias(logn) : texel_bias(logn)));
@@ -802,12 +866,19 @@ __global__ __launch_bounds__(kThreads, CHAIN || LOGN ? 5 : 1) void relight_kerne
   LLTab tab = {};
   float llcb = 0.0f, llsb = 0.0f;
   int llsa = 0, llsc = 0;
+  [[maybe_unused]] bool unit = false;  // (cos b, sin b) as it should be
   if constexpr (LL) {
     float* t = reinterpret_cast<float*>(dyn_lds + p.ll_tab_off);
     for (int k = lane; k < 7 * n; k += kThreads) t[k] = p.ll_grid[k];
+    wave_sync();
+    if (lane == 0) {
+      t[6 * n] = __builtin_inff();
+      t[7 * n] = -__builtin_inff();
+    }
     tab = {t, t + n, t + 2 * n, t + 4 * n, t + 6 * n};
     llcb = __int_as_float(__builtin_amdgcn_readfirstlane(__float_as_int(p.ll_elev[2 * v])));
     llsb = __int_as_float(__builtin_amdgcn_readfirstlane(__float_as_int(p.ll_elev[2 * v + 1])));
+    unit = fabsf(llcb * llcb + llsb * llsb - 1.0f) <= 1e-6f;
     llsa = __builtin_amdgcn_readfirstlane(p.ll_shift[2 * v]) & (2 * n - 1);
     llsc = __builtin_amdgcn_readfirstlane(p.ll_shift[2 * v + 1]) & (2 * n - 1);
     wave_sync();
@@ -912,43 +983,18 @@ __global__ __launch_bounds__(kThreads, CHAIN || LOGN ? 5 : 1) void relight_kerne
                      ((__builtin_amdgcn_readfirstlane(bmask[gi >> 5]) >> (gi & 31)) & 1u) != 0u;
             float lane_sum = 0.0f;  // sum-only blocks: this lane's gathered texels
             if constexpr (LL) {
-              // the same compact patches, through the lat-long rule
+              // the same compact patches, through the lat-long rule; lanes in
+              // Morton order where a patch is 8 x 8
+              const int gy = TS == 8 ? morton_y(lane) : ty, gx = TS == 8 ? morton_x(lane) : tx;
               if (owns_tile) {
                 float val[T][T];
-                // H below 32 has Q = H; from 32 on, Q = 32 and H = 32 .. 512
-                if constexpr (Q < 32) {
-                  latlong_gather<LOGQ, Q, TS, T>(val, tab, src, face, by, bx, ty, tx, llcb,
-                                                       llsb, llsa, llsc);
-                } else {
-                  switch (logn) {
-#define RRT_LL_CASE(L)                                                                         \
-  case L:                                                                                      \
-    latlong_gather<L, Q, TS, T>(val, tab, src, face, by, bx, ty, tx, llcb, llsb, llsa, \
-                                      llsc);                                                   \
-    break;
-                    RRT_LL_CASE(5)
-                    RRT_LL_CASE(6)
-                    RRT_LL_CASE(7)
-                    RRT_LL_CASE(8)
-                    RRT_LL_CASE(9)
-#undef RRT_LL_CASE
-                    default:
-#pragma unroll
-                      for (int a = 0; a < T; ++a)
-#pragma unroll
-                        for (int b = 0; b < T; ++b) {
-                          const int i = by * Q + TS * a + ty;
-                          const int jc = (face * n + bx * Q + TS * b + tx + llsc) & (2 * n - 1);
-                          val[a][b] = load_src(
-                              src, latlong_source(tab, i, jc, llcb, llsb, logn, llsa));
-                        }
-                  }
-                }
+                latlong_gather<LOGN, Q, TS, T>(val, tab, src, face, by, bx, gy, gx, llcb, llsb, llsa,
+                                               llsc, unit);
                 if (full) {
 #pragma unroll
                   for (int a = 0; a < T; ++a)
 #pragma unroll
-                    for (int b = 0; b < T; ++b) img[(TS * a + ty) * STRIDE + TS * b + tx] = val[a][b];
+                    for (int b = 0; b < T; ++b) img[(TS * a + gy) * STRIDE + TS * b + gx] = val[a][b];
                 } else {
                   lane_sum = tile_sum<T>(val);
                 }
@@ -1383,7 +1429,7 @@ int launch_q(const RelightParams& prm_in, int64_t nvert, hipStream_t s) {
                size_t(prm.group_faces) * G * G * 8 + kBlockMaskBytes;
   if (LL) {
     prm.ll_tab_off = int(lds);
-    lds += size_t(latlong_grid_floats(1 << prm.logn)) * 4;
+    lds += (size_t(latlong_grid_floats(1 << prm.logn)) + 1) * 4;
   }
   // A vertex's frames share its entry list, but a wave per vertex can be too few
   // of them, or leave the last round of the chip (kRoundWaves at a time) mostly
@@ -1421,11 +1467,15 @@ int launch_size(const RelightParams& prm, int n, int64_t nvert, hipStream_t s) {
 }
 
 int launch_latlong(const RelightParams& prm, int n, int64_t nvert, hipStream_t s) {
-  switch (n < kBlock ? n : kBlock) {
-    case 4: return launch_q<4, false, false, true>(prm, nvert, s);
-    case 8: return launch_q<8, false, false, true>(prm, nvert, s);
-    case 16: return launch_q<16, false, false, true>(prm, nvert, s);
-    default: return launch_q<kBlock, false, false, true>(prm, nvert, s);
+  switch (n) {
+    case 4: return launch_q<4, false, false, true, 2>(prm, nvert, s);
+    case 8: return launch_q<8, false, false, true, 3>(prm, nvert, s);
+    case 16: return launch_q<16, false, false, true, 4>(prm, nvert, s);
+    case 32: return launch_q<kBlock, false, false, true, 5>(prm, nvert, s);
+    case 64: return launch_q<kBlock, false, false, true, 6>(prm, nvert, s);
+    case 128: return launch_q<kBlock, false, false, true, 7>(prm, nvert, s);
+    case 256: return launch_q<kBlock, false, false, true, 8>(prm, nvert, s);
+    default: return launch_q<kBlock, false, false, true, 9>(prm, nvert, s);
   }
 }
 

@@ -63,8 +63,8 @@ int launch_rotate_pixels(const float* src, const float* rot, int nrot, int n, fl
                          hipStream_t s);
 
 struct RelightLaunch {
-  const float* src;         // [6][n][n] source map, in strips of eight columns for n >= 8
-                            // (row-major for n < 8 and for the [2][n][n] lat-long map)
+  const float* src;         // [6][n][n] (lat-long [2][n][n]) source map, in strips of
+                            // eight columns for n >= 8, row-major below
   const float* vert_rot;    // [V][9]
   const float* frame_rot;   // [F][9] or nullptr
   const int32_t* t_idx;     // [V][nnz] or nullptr (dense)
