@@ -162,7 +162,11 @@ __global__ __launch_bounds__(kThreads) void topk_rows(const float* __restrict__ 
 constexpr int kSelBits = 11;
 constexpr int kSelBins = 1 << kSelBits;
 constexpr int kSelShift = 31 - kSelBits;
-constexpr int kSelCand = kSelBins / 2;        // candidates (key, position) in the bins' place
+// Candidates (key, position) listed in the bins' place and ranked against each
+// other: more take ten more bits first (936 zeros around the threshold of short
+// rows took 400 us to rank).
+constexpr int kSelCand = 384;
+static_assert(2 * kSelCand <= kSelBins, "the list fits the bins");
 constexpr int64_t kSelMaxLen = 6 * 256 * 256;  // 48 KiB of bits
 
 // f(position, value) for every value of the row, 16 bytes at a time where its
@@ -231,7 +235,7 @@ __global__ __launch_bounds__(kThreads) void topk_select(const float* __restrict_
                                                         int32_t* __restrict__ oidx,
                                                         float* __restrict__ oval) {
   constexpr int kWaves = kThreads / 64;
-  extern __shared__ unsigned lds[];
+  extern __shared__ __align__(8) unsigned lds[];
   unsigned* hist = lds;             // kSelBins; later the candidates
   unsigned* bits = lds + kSelBins;  // one bit per position
   __shared__ int sh[kWaves];
@@ -259,14 +263,33 @@ __global__ __launch_bounds__(kThreads) void topk_select(const float* __restrict_
   block_scan<kWaves>(nonzero, &total, sh);
   const unsigned zeros = unsigned(len - total);
   find_bin<kThreads>(hist, kSelBins, zeros, unsigned(k), &s_bin, &s_need, sh);
-  const unsigned bin = unsigned(s_bin);
   unsigned need = unsigned(s_need);
-  const unsigned in_bin = hist[bin] + (bin == 0 ? zeros : 0u);
+  // the bits above `shift` of the keys in the bin
+  int shift = kSelShift;
+  unsigned bin = unsigned(s_bin);
+  unsigned in_bin = hist[bin] + (bin == 0 ? zeros : 0u);
   __syncthreads();
+  // more candidates than the list holds: ten more bits (at most twice)
+  while (in_bin > unsigned(kSelCand) && shift > 0) {
+    for (int b = tid; b < 1024; b += kThreads) hist[b] = 0u;
+    __syncthreads();
+    for_row<kThreads>(row, len, wide, [&](int, float v) {
+      const unsigned u = key_of(v);
+      if (u && u >> shift == bin) atomicAdd(&hist[(u >> (shift - 10)) & 1023u], 1u);
+    });
+    __syncthreads();
+    const unsigned extra = bin == 0 ? zeros : 0u;
+    find_bin<kThreads>(hist, 1024, extra, need, &s_bin, &s_need, sh);
+    need = unsigned(s_need);
+    in_bin = hist[s_bin] + (s_bin == 0 ? extra : 0u);
+    bin = bin << 10 | unsigned(s_bin);
+    shift -= 10;
+    __syncthreads();
+  }
   if (in_bin <= unsigned(kSelCand)) {
     // keys above the bin are kept, the bin's are listed ...
     for_row<kThreads>(row, len, wide, [&](int i, float v) {
-      const unsigned u = key_of(v), b = u >> kSelShift;
+      const unsigned u = key_of(v), b = u >> shift;
       if (b > bin) {
         atomicOr(&bits[i >> 5], 1u << (i & 31));
       } else if (b == bin) {
@@ -278,33 +301,20 @@ __global__ __launch_bounds__(kThreads) void topk_select(const float* __restrict_
     __syncthreads();
     // ... and those of a rank (larger key, then lower position) below `need` kept
     const int m = int(in_bin);
+    const uint2* list = reinterpret_cast<const uint2*>(hist);
     for (int c = tid; c < m; c += kThreads) {
-      const unsigned u = hist[2 * c], i = hist[2 * c + 1];
+      const unsigned u = list[c].x, i = list[c].y;
       unsigned rank = 0;
+#pragma unroll 8
       for (int j = 0; j < m; ++j) {
-        const unsigned v = hist[2 * j];
-        rank += (v > u || (v == u && hist[2 * j + 1] < i)) ? 1u : 0u;
+        const uint2 o = list[j];
+        rank += (o.x > u || (o.x == u && o.y < i)) ? 1u : 0u;
       }
       if (rank < need) atomicOr(&bits[i >> 5], 1u << (i & 31));
     }
   } else {
-    // many equal or nearly equal keys: the threshold from the remaining bits
-    // in two steps, then the first `need` keys equal to it in position order
-    unsigned prefix = bin << kSelShift, mask = ~((1u << kSelShift) - 1u) & 0x7fffffffu;
-    for (int shift = kSelShift - 10; shift >= 0; shift -= 10) {
-      for (int b = tid; b < 1024; b += kThreads) hist[b] = 0u;
-      __syncthreads();
-      for_row<kThreads>(row, len, wide, [&](int, float v) {
-        const unsigned u = key_of(v);
-        if (u && (u & mask) == prefix) atomicAdd(&hist[(u >> shift) & 1023u], 1u);
-      });
-      __syncthreads();
-      find_bin<kThreads>(hist, 1024, prefix == 0 ? zeros : 0u, need, &s_bin, &s_need, sh);
-      prefix |= unsigned(s_bin) << shift;
-      need = unsigned(s_need);
-      mask |= 1023u << shift;
-      __syncthreads();
-    }
+    // many equal keys: the first `need` of them in position order
+    const unsigned prefix = bin;
     int base = 0;
     for (int c0 = 0; c0 < len; c0 += kThreads * kItems) {
       unsigned keep = 0, eq = 0;

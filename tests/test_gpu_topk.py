@@ -27,6 +27,8 @@ def rows_of(kind, rows, length, g):
         x = np.where(g.random(x.shape) < 0.5, -1.5, 1.5).astype(np.float32)
     elif kind == "near":                    # one top-bits bin, ties among its keys
         x = (np.float32(1.0) + g.integers(0, 50, x.shape).astype(np.float32) * np.float32(2.0 ** -23))
+    elif kind == "few":                     # a few hundred different keys, many times
+        x = (g.integers(1, 300, x.shape).astype(np.float32) * np.float32(2.0 ** -20)) * np.sign(x)
     elif kind == "extreme":
         x[:, 0::5] = np.inf
         x[:, 1::5] = -np.finfo(np.float32).max
@@ -40,6 +42,7 @@ def rows_of(kind, rows, length, g):
     (2, 131072, 1024, "normal"), (2, 131076, 1024, "near"), (1, 393216, 2048, "sparse"),
     (1, 393217, 2048, "sparse"), (9, 393220, 300, "normal"), (3, 1536, 300, "extreme"),
     (12, 9000, 4000, "extreme"), (70, 384, 383, "normal"), (70, 384, 384, "normal"),
+    (200, 1536, 600, "sparse"), (12, 1536, 1200, "few"), (12, 98304, 20000, "few"),
     (4, 31, 30, "near"), (1, 98304, 98304, "normal"), (1, 98304, 98303, "sparse"),
 ])
 def test_topk_ways(rrt, rows, length, k, kind):
