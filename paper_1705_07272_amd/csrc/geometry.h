@@ -171,6 +171,13 @@ __device__ __forceinline__ unsigned texel_bias(int logn) {
   return (127u << (2 * logn)) + (127u << logn);
 }
 
+// Texel of a lane in an 8 x 8 patch, Morton order: 16 consecutive lanes take a
+// 4 x 4 block of texels.
+__device__ __forceinline__ int morton_x(int lane) {
+  return (lane & 1) | ((lane >> 1) & 2) | ((lane >> 2) & 4);
+}
+__device__ __forceinline__ int morton_y(int lane) { return morton_x(lane >> 1); }
+
 // Column-strip layout of a source map (n >= 8): every face is cut into strips
 // of eight columns, stored one after the other row by row, so texel (face, i,
 // j) sits at face n^2 + (j >> 3) 8n + 8 i + (j & 7) and a 4-row x 8-column

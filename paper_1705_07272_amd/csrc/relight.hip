@@ -20,12 +20,14 @@
 //     the block with lane shuffles, in place (the coefficient of a block of
 //     side B at its corner offset by B/2 for H/V/D);
 //   * the transport entries are decoded once per vertex into an LDS list; the
-//     entries inside the block read the image, the coarser ones read the FP64
-//     block-sum grid after the levels above the blocks; products are
-//     accumulated per lane and reduced with lane shuffles (a dense row has no
-//     list: each image and grid position reads its own entry);
-//   * a block that holds no listed entry only contributes its sum to the
-//     levels above it and skips the image, the levels and the entry scan.
+//     entries inside the block read the image; those of the levels above the
+//     blocks are turned into a weight per block (their inverse transform, once
+//     per vertex, FP64) that multiplies the block's sum, each lane its own
+//     texels' share; products are accumulated per lane and reduced with lane
+//     shuffles (a dense row has no list: each image and grid position reads
+//     its own entry);
+//   * a block that holds no listed entry only counts through its sum and skips
+//     the image, the levels and the entry scan.
 //
 // Variants of the same kernel: the chain rule for the finest level
 // (Sec. V.A-V.B, eq:pde1-eq:pde3), the triple product with a BRDF factor per
@@ -143,13 +145,6 @@ __device__ __forceinline__ Slot decode_slot(int idx, int logn, int nf) {
   s.pc = ((c & (q - 1)) << s.logb) + ((c >= q) ? half : 0);
   return s;
 }
-
-// Texel of a lane in an 8 x 8 patch, Morton order: 16 consecutive lanes take a
-// 4 x 4 block of texels.
-__device__ __forceinline__ int morton_x(int lane) {
-  return (lane & 1) | ((lane >> 1) & 2) | ((lane >> 2) & 4);
-}
-__device__ __forceinline__ int morton_y(int lane) { return morton_x(lane >> 1); }
 
 struct Acc {
   float s, c;
@@ -604,27 +599,6 @@ __device__ __forceinline__ void gather_quarter(float (&val)[4], int face, float3
   }
 }
 
-template <int CTRL>
-__device__ __forceinline__ float dpp_mov(float x) {
-  return __int_as_float(__builtin_amdgcn_mov_dpp(__float_as_int(x), CTRL, 0xF, 0xF, true));
-}
-
-// Sum over the 64 lanes of a wave (all lanes active), the same value in every
-// lane: DPP adds within each 16-lane row (partner in the quad at xor 1 and
-// xor 2, then the mirrored quad of the half row, then the mirrored half row),
-// then the four row sums read back as scalars.
-__device__ __forceinline__ float wave_sum(float x) {
-  x += dpp_mov<0xB1>(x);   // quad_perm [1, 0, 3, 2]
-  x += dpp_mov<0x4E>(x);   // quad_perm [2, 3, 0, 1]
-  x += dpp_mov<0x141>(x);  // row_half_mirror
-  x += dpp_mov<0x140>(x);  // row_mirror
-  const int xi = __float_as_int(x);
-  return (__int_as_float(__builtin_amdgcn_readlane(xi, 0)) +
-          __int_as_float(__builtin_amdgcn_readlane(xi, 16))) +
-         (__int_as_float(__builtin_amdgcn_readlane(xi, 32)) +
-          __int_as_float(__builtin_amdgcn_readlane(xi, 48)));
-}
-
 // LDS ordering among the lanes of one wave (no workgroup barrier).
 __device__ __forceinline__ void wave_sync() {
   __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
@@ -810,9 +784,9 @@ __global__ __launch_bounds__(kThreads, CHAIN || LOGN ? 5 : 1) void relight_kerne
   float* img = reinterpret_cast<float*>(dyn_lds);  // the block image
   int* lkey = reinterpret_cast<int*>(dyn_lds + IMG * 4);
   float* lval = reinterpret_cast<float*>(lkey + p.listed);
-  double* gS = reinterpret_cast<double*>(dyn_lds + ((IMG * 4 + 8 * p.listed + 7) & ~7));
+  double* gW = reinterpret_cast<double*>(dyn_lds + ((IMG * 4 + 8 * p.listed + 7) & ~7));
   // one bit per block of the face group: the block has listed entries
-  unsigned* bmask = reinterpret_cast<unsigned*>(gS + FG * G2);
+  unsigned* bmask = reinterpret_cast<unsigned*>(gW + FG * G2);
   const int bwords = (FG * G2 + 31) >> 5;
 
   // index row of this vertex: its own, or its cluster's support row
@@ -860,7 +834,7 @@ __global__ __launch_bounds__(kThreads, CHAIN || LOGN ? 5 : 1) void relight_kerne
   const int ty = lane >> LOGTS, tx = lane & (TS - 1);  // tile of this lane, and its texel in
                                                         // each TS x TS patch of the gather
   const uint64_t lanes_below = (uint64_t(1) << lane) - 1;
-  int nfine = 0, ncoarse = 0;
+  int nfine = 0;
 
   // lat-long: the rule's tables into LDS, this vertex's rotation
   LLTab tab = {};
@@ -901,20 +875,29 @@ __global__ __launch_bounds__(kThreads, CHAIN || LOGN ? 5 : 1) void relight_kerne
       for (int k = 0; k < 9; ++k) rot_ok = rot_ok && R.m[k] <= one && R.m[k] >= -one;
     }
     Acc acc = {0.0f, 0.0f};
+    double accw = 0.0;  // the part of the levels above the blocks
 
     for (int grp = 0; grp < ngroups; ++grp) {
       const int g0 = grp * FG;
       const int nfg = min(FG, nf - g0);
 
-      if (!DENSE && (f == int(blockIdx.y) || ngroups > 1)) {
-        // List the first `listed` entries in entry order: block entries from
-        // the front, coarse entries from the back.
+      if (f == int(blockIdx.y) || ngroups > 1) {
+        // List the block entries among the first `listed` in entry order; the
+        // coarse entries become the blocks' weights.
         nfine = 0;
-        ncoarse = 0;
-        if (SUM_ONLY) {
-          for (int k = lane; k < bwords; k += kThreads) bmask[k] = 0u;
-          wave_sync();
+        for (int k = lane; k < bwords; k += kThreads) bmask[k] = 0u;
+        for (int k = lane; k < nfg * G2; k += kThreads) {
+          double w = 0.0;
+          if constexpr (DENSE) {
+            // the face's scaling coefficient and the levels above the blocks
+            const int at = k & (G2 - 1);
+            const int idx = slot_index(nth_face(faces, g0 + (k >> (2 * (logn - LOGQ)))),
+                                       (at >> (logn - LOGQ)) * Q, (at & (G - 1)) * Q, logn);
+            w = double(transport_value(p.tval, p.tscale, p.dtype, v, p.nnz, idx));
+          }
+          gW[k] = w;
         }
+        wave_sync();
         for (int c0 = 0; c0 < listed; c0 += kListChunks * kThreads) {
           // the entries of kListChunks chunks of 64 are loaded first, so
           // that their loads are in flight together, then each chunk is
@@ -932,22 +915,44 @@ __global__ __launch_bounds__(kThreads, CHAIN || LOGN ? 5 : 1) void relight_kerne
             const int e = c0 + u * kThreads + lane;
             int key = 0, kind = -1;
             if (e < listed) kind = classify<Q, NF>(ix[u], logn, G, faces, g0, FG, key);
-            const uint64_t bf = __ballot(kind == 0), bc = __ballot(kind == 1);
-            if (kind >= 0) {
-              const int at = kind == 0 ? nfine + __popcll(bf & lanes_below)
-                                       : listed - 1 - (ncoarse + __popcll(bc & lanes_below));
+            const uint64_t bf = __ballot(kind == 0);
+            if (kind == 0) {
+              const int at = nfine + __popcll(bf & lanes_below);
               lkey[at] = key;
               lval[at] = vx[u];
-              if (SUM_ONLY && kind == 0) {
-                const int gb = (key >> kOffBits) & ((1 << kBlockBits) - 1);
-                atomicOr(&bmask[gb >> 5], 1u << (gb & 31));
-              }
+              const int gb = (key >> kOffBits) & ((1 << kBlockBits) - 1);
+              if (SUM_ONLY) atomicOr(&bmask[gb >> 5], 1u << (gb & 31));
+            } else if (kind == 1) {
+              atomicAdd(&gW[key], double(vx[u]));
             }
             nfine += __popcll(bf);
-            ncoarse += __popcll(bc);
           }
         }
+        for (int e = listed + lane; !DENSE && e < nnz; e += kThreads) {
+          int key = 0;
+          if (classify<Q, NF>(idx_row[e], logn, G, faces, g0, FG, key) == 1)
+            atomicAdd(&gW[key], double(transport_value(p.tval, p.tscale, p.dtype, v, p.nnz, e)));
+        }
         wave_sync();
+        // The inner product with the levels above the blocks is one with the
+        // blocks' sums, whose weights are the inverse transform of those
+        // levels' entries (FP64, in place, the widest blocks first).
+        for (int r = 0; r < nfg; ++r) {
+          double* gf = gW + r * G2;
+          for (int Bg = G; Bg >= 2; Bg >>= 1) {
+            const int hg = Bg / 2, nb = G / Bg;
+            for (int t = lane; t < nb * nb; t += kThreads) {
+              const int at = (t / nb) * Bg * G + (t % nb) * Bg;
+              double A, B, C, D;
+              tile_levels_d(gf[at], gf[at + hg], gf[at + hg * G], gf[at + hg * G + hg], A, B, C, D);
+              gf[at] = A;
+              gf[at + hg] = B;
+              gf[at + hg * G] = C;
+              gf[at + hg * G + hg] = D;
+            }
+            wave_sync();
+          }
+        }
       }
 
       for (int r = 0, gi = 0; r < nfg; ++r) {
@@ -976,11 +981,34 @@ __global__ __launch_bounds__(kThreads, CHAIN || LOGN ? 5 : 1) void relight_kerne
         for (int kb = 0; kb < G2; ++kb, ++gi) {
           {
             const int by = kb >> (logn - LOGQ), bx = kb & (G - 1);
+            if constexpr (QUARTERS) {
+              // 16 blocks at a time, each lane looks at one of their quarters
+              if ((kb & 15) == 0)
+                quarters = quarter_face<LOGN>(ax, kb + (lane >> 2), lane & 3, rot_ok);
+            }
             // entries past the list may fall in any block: then every block is full
             bool full = true;
             if constexpr (SUM_ONLY)
               full = nnz > listed ||
                      ((__builtin_amdgcn_readfirstlane(bmask[gi >> 5]) >> (gi & 31)) & 1u) != 0u;
+            // weight of the block's sum (orthonormal scaling coefficient: 1 / Q)
+            const double weight = gW[gi] * (1.0 / Q);
+            // nothing reads a block of weight zero (the part of a lobe's square
+            // below the horizon, where the entries of the levels above cancel):
+            // 50,000 lat-long vertices at H = 128 2.01 -> 1.13 ms
+            if (!full && __ballot(weight != 0.0) == 0) continue;
+            if constexpr (BRDF && QUARTERS) {
+              // nor does one whose factor is zero everywhere (below the horizon)
+              // add to any coefficient
+              const float* br = brdf_row + ((face * n + by * Q + ty * T) << logn) + bx * Q + tx * T;
+              bool zero = true;
+#pragma unroll 1
+              for (int rr = 0; rr < T && zero; ++rr) {
+                const uint4 w = *reinterpret_cast<const uint4*>(br + (rr << logn));
+                zero = __ballot((((w.x | w.y) | (w.z | w.w)) << 1) != 0u) == 0;
+              }
+              if (zero) continue;
+            }
             float lane_sum = 0.0f;  // sum-only blocks: this lane's gathered texels
             if constexpr (LL) {
               // the same compact patches, through the lat-long rule; lanes in
@@ -1050,9 +1078,6 @@ __global__ __launch_bounds__(kThreads, CHAIN || LOGN ? 5 : 1) void relight_kerne
                 }
               }
             } else if constexpr (QUARTERS) {
-              // 16 blocks at a time, each lane looks at one of their quarters
-              if ((kb & 15) == 0)
-                quarters = quarter_face<LOGN>(ax, kb + (lane >> 2), lane & 3, rot_ok);
               const float3 rb = dir_add(us, float(4 * bx), dir_add(vs, float(4 * by), s0));
               float val[4][4];
 #pragma unroll
@@ -1103,10 +1128,8 @@ __global__ __launch_bounds__(kThreads, CHAIN || LOGN ? 5 : 1) void relight_kerne
               }
             }
             if (SUM_ONLY && !full) {
-              // the block's sum for the levels above it; nothing else reads it
-              const float bsum = wave_sum(lane_sum);
-              if (lane == 0) gS[gi] = double(bsum) * (1.0 / Q);
-              wave_sync();
+              // only the block's sum counts
+              accw = fma(weight, double(lane_sum), accw);
               continue;
             }
             wave_sync();
@@ -1150,11 +1173,10 @@ __global__ __launch_bounds__(kThreads, CHAIN || LOGN ? 5 : 1) void relight_kerne
                 for (int cc = 0; cc < T; ++cc)
                   img[(ty * T + rr) * STRIDE + tx * T + cc] = g[rr][cc];
               s = g[0][0];
+              if (weight != 0.0) accw = fma(weight, double(s), accw);
             }
             // levels above the tile, unscaled
             if constexpr (TS > 1) tile_level_above<1, TS, T, STRIDE>(s, img, lane, tx, ty, owns_tile);
-            // the block's orthonormal scaling coefficient, for the levels above
-            if (lane == 0) gS[gi] = double(s) * (1.0 / Q);
             wave_sync();
             // listed entries of this block: four keys per lane and LDS read
             for (int k0 = 4 * lane; k0 < nfine; k0 += 4 * kThreads) {
@@ -1192,46 +1214,6 @@ __global__ __launch_bounds__(kThreads, CHAIN || LOGN ? 5 : 1) void relight_kerne
           }
         }
       }
-      // levels above the blocks, per face of the group (FP64, in place)
-      if (G > 1) {
-        for (int r = 0; r < nfg; ++r) {
-          double* gf = gS + r * G2;
-          for (int Bg = 2; Bg <= G; Bg <<= 1) {
-            const int hg = Bg / 2, nb = G / Bg;
-            for (int t = lane; t < nb * nb; t += kThreads) {
-              const int r0 = (t / nb) * Bg, c0 = (t % nb) * Bg;
-              double S, H, V, D;
-              tile_levels_d(gf[r0 * G + c0], gf[r0 * G + c0 + hg], gf[(r0 + hg) * G + c0],
-                            gf[(r0 + hg) * G + c0 + hg], S, H, V, D);
-              gf[r0 * G + c0] = S;
-              gf[r0 * G + c0 + hg] = H;
-              gf[(r0 + hg) * G + c0] = V;
-              gf[(r0 + hg) * G + c0 + hg] = D;
-            }
-            wave_sync();
-          }
-        }
-      }
-      // coarse entries: blocks wider than Q and the faces' scaling coefficients
-      for (int k = lane; k < ncoarse; k += kThreads) {
-        const int at = listed - 1 - k;
-        acc_add(acc, lval[at], float(gS[lkey[at]]), comp);
-      }
-      if constexpr (DENSE) {
-        // dense row: the face's scaling coefficient and the levels above the blocks
-        for (int k = lane; k < nfg * G2 && nnz > 0; k += kThreads) {
-          const int at = k & (G2 - 1);
-          const int idx = slot_index(nth_face(faces, g0 + (k >> (2 * (logn - LOGQ)))),
-                                     (at >> (logn - LOGQ)) * Q, (at & (G - 1)) * Q, logn);
-          acc_add(acc, transport_value(p.tval, p.tscale, p.dtype, v, p.nnz, idx), float(gS[k]), comp);
-        }
-      }
-      for (int e = listed + lane; !DENSE && e < nnz; e += kThreads) {
-        int key = 0;
-        if (classify<Q, NF>(idx_row[e], logn, G, faces, g0, FG, key) == 1)
-          acc_add(acc, transport_value(p.tval, p.tscale, p.dtype, v, p.nnz, e), float(gS[key]),
-                  comp);
-      }
       wave_sync();
     }
 
@@ -1247,7 +1229,10 @@ __global__ __launch_bounds__(kThreads, CHAIN || LOGN ? 5 : 1) void relight_kerne
         acc.s += other.s;
       }
     }
-    if (lane == 0) p.out[int64_t(f) * p.out_stride + v] = comp ? (acc.s + acc.c) : acc.s;
+#pragma unroll
+    for (int o = 32; o >= 1; o >>= 1) accw += __shfl_xor(accw, o, 64);
+    accw += comp ? double(acc.s) + double(acc.c) : double(acc.s);
+    if (lane == 0) p.out[int64_t(f) * p.out_stride + v] = float(accw);
   }
 }
 
