@@ -195,14 +195,10 @@ int rrt_haar_phase_shift(const float* coef_in, int n, const float* rot, int nrot
     return fail(RRT_ERR_WORKSPACE, "phase_shift: workspace %zu < %zu bytes", ws_bytes, need);
   if (reinterpret_cast<uintptr_t>(ws) & 255u) return fail(RRT_ERR_INVALID, "phase_shift: workspace not 256-byte aligned");
   hipStream_t s = static_cast<hipStream_t>(stream);
-  const size_t cells = size_t(6) * n * n;
   float* pix = static_cast<float*>(ws);
-  float* rotated = reinterpret_cast<float*>(static_cast<char*>(ws) + align256(cells * sizeof(float)));
-  int st = launch_haar_inverse(coef_in, pix, n, 6, s);
+  const int st = launch_haar_inverse(coef_in, pix, n, 6, s, true);
   if (st) return st;
-  st = launch_rotate_pixels(pix, rot, nrot, n, rotated, s);
-  if (st) return st;
-  return launch_haar_forward(rotated, coef_out, n, int64_t(6) * nrot, s);
+  return launch_haar_rotated(pix, rot, nrot, n, coef_out, s);
 }
 
 int rrt_relight_workspace(const rrt_light* L, const rrt_rotations* R, const rrt_transport* T,

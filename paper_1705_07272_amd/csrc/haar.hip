@@ -13,6 +13,7 @@
 // first texel of each output tile (inverse), positions no other coefficient
 // or texel of the first launch uses.
 
+#include "geometry.h"
 #include "rrt_internal.h"
 
 namespace rrt {
@@ -38,8 +39,60 @@ __device__ __forceinline__ void inverse_butterfly(float S, float H, float V, flo
   d = 0.5f * ((S - H) - (V - D));
 }
 
+// Tile of a rotated map: destination texel (row, col) of a face takes the
+// source texel of its direction; in patches of 8 x 8 texels with the lanes in
+// Morton order and the map in strips of eight columns (n >= 8) as the relight
+// gathers them, a wave of the workgroup taking every fourth patch.
+__device__ __forceinline__ void rotated_tile(const float* __restrict__ map,
+                                             const float* __restrict__ rot, int face, int logn,
+                                             int logq, int row0, int col0, float* lds) {
+  const int n = 1 << logn, Q = 1 << logq;
+  const IRot R = frame_vertex_rotation(rot, nullptr, scale_bits(logn));
+  const FaceAxes ax = face_axes(R, face);
+  const float3 centre = dir_add(ax.mN, float(n), make_float3(0.0f, 0.0f, 0.0f));
+  const unsigned last = unsigned(6 << (2 * logn)) - 1u;
+  if (n < 8) {
+    for (int e = threadIdx.x; e < Q * Q; e += kThreads) {
+      const float3 d = dir_mad(ax.mU, float(2 * (col0 + (e & (Q - 1))) + 1 - n), ax.mV,
+                               float(2 * (row0 + (e >> logq)) + 1 - n), centre);
+      lds[e] = map[min(unsigned(source_texel(d, logn)), last)];
+    }
+    return;
+  }
+  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+  const int gx = morton_x(lane), gy = morton_y(lane);
+  const int across = logq - 3;  // log2 patches per tile side
+  constexpr int kWaves = kThreads / 64, kAhead = 4;  // patches in flight per wave
+  const int patches = 1 << (2 * across);
+  for (int k0 = wave; k0 < patches; k0 += kAhead * kWaves) {
+    float v[kAhead];
+#pragma unroll
+    for (int j = 0; j < kAhead; ++j) {
+      const int k = min(k0 + j * kWaves, patches - 1);
+      const int r = 8 * (k >> across) + gy, c = 8 * (k & ((1 << across) - 1)) + gx;
+      const float3 d = dir_mad(ax.mU, float(2 * (col0 + c) + 1 - n), ax.mV,
+                               float(2 * (row0 + r) + 1 - n), centre);
+      // the index stays in the map by construction; the bound keeps this plain
+      // pointer read in it whatever the rotation holds
+      v[j] = map[min(source_texel_strip(d.x, d.y, d.z, logn) - strip_bias(logn), last)];
+    }
+#pragma unroll
+    for (int j = 0; j < kAhead; ++j) {
+      const int k = k0 + j * kWaves;
+      if (k < patches)
+        lds[((8 * (k >> across) + gy) << logq) + 8 * (k & ((1 << across) - 1)) + gx] = v[j];
+    }
+  }
+}
+
 // grid: count * 6 * G * G workgroups (G = n / Q); LDS: Q * Q floats.
+// ROTATE: the squares are the faces of the map `pix` (in strips for n >= 8)
+// under the rotations `rot`, gathered here instead of read (the rotated maps
+// went through memory in a launch of their own: 64 rotations at n = 128 took
+// 25 us for it, of 48 in all, 27.7 now).
+template <bool ROTATE>
 __global__ __launch_bounds__(kThreads) void haar_fwd_tiles(const float* __restrict__ pix,
+                                                           const float* __restrict__ rot,
                                                            float* __restrict__ coef, int n,
                                                            int logq, int G) {
   extern __shared__ float lds[];
@@ -48,12 +101,16 @@ __global__ __launch_bounds__(kThreads) void haar_fwd_tiles(const float* __restri
   const int tile = int(blk % (G * G));
   const int64_t face = blk / (G * G);
   const int ty = tile / G, tx = tile % G;
-  const float* src = pix + face * int64_t(n) * n;
   float* dst = coef + face * int64_t(n) * n;
   const int row0 = ty * Q, col0 = tx * Q;
-  for (int e = threadIdx.x; e < Q * Q; e += kThreads) {
-    const int r = e >> logq, c = e & (Q - 1);
-    lds[e] = src[int64_t(row0 + r) * n + col0 + c];
+  if constexpr (ROTATE) {
+    rotated_tile(pix, rot + face / 6 * 9, int(face % 6), __builtin_ctz(unsigned(n)), logq, row0, col0, lds);
+  } else {
+    const float* src = pix + face * int64_t(n) * n;
+    for (int e = threadIdx.x; e < Q * Q; e += kThreads) {
+      const int r = e >> logq, c = e & (Q - 1);
+      lds[e] = src[int64_t(row0 + r) * n + col0 + c];
+    }
   }
   __syncthreads();
   for (int B = 2; B <= Q; B <<= 1) {
@@ -287,17 +344,33 @@ int launch_source_map(const int32_t* idx, const void* val, int dtype, int k, int
   return st ? st : launch_haar_inverse(dense, pix, n, squares, s, strips);
 }
 
-int launch_haar_forward(const float* pix, float* coef, int n, int64_t squares, hipStream_t s) {
+static int launch_forward(const float* pix, const float* rot, float* coef, int n, int64_t squares,
+                          hipStream_t s) {
   if (squares == 0) return RRT_OK;
   const int Q = n < kTile ? n : kTile;
   const int G = n / Q;
   const int64_t grid = squares * G * G;
-  hipLaunchKernelGGL(haar_fwd_tiles, dim3(unsigned(grid)), dim3(kThreads),
-                     size_t(Q) * Q * sizeof(float), s, pix, coef, n, ilog2(Q), G);
+  const size_t lds = size_t(Q) * Q * sizeof(float);
+  if (rot) {
+    hipLaunchKernelGGL(haar_fwd_tiles<true>, dim3(unsigned(grid)), dim3(kThreads), lds, s, pix, rot,
+                       coef, n, ilog2(Q), G);
+  } else {
+    hipLaunchKernelGGL(haar_fwd_tiles<false>, dim3(unsigned(grid)), dim3(kThreads), lds, s, pix, rot,
+                       coef, n, ilog2(Q), G);
+  }
   int st = check_launch("haar_fwd_tiles");
   if (st || G == 1) return st;
   hipLaunchKernelGGL(haar_fwd_coarse, dim3(unsigned(squares)), dim3(64), 0, s, coef, n, G);
   return check_launch("haar_fwd_coarse");
+}
+
+int launch_haar_forward(const float* pix, float* coef, int n, int64_t squares, hipStream_t s) {
+  return launch_forward(pix, nullptr, coef, n, squares, s);
+}
+
+int launch_haar_rotated(const float* map, const float* rot, int nrot, int n, float* coef,
+                        hipStream_t s) {
+  return launch_forward(map, rot, coef, n, int64_t(6) * nrot, s);
 }
 
 int launch_haar_inverse(const float* coef, float* pix, int n, int64_t squares, hipStream_t s,

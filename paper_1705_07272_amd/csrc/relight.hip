@@ -1382,27 +1382,6 @@ __global__ void coarsen_indices(const int32_t* __restrict__ idx, int64_t count, 
   out[i] = r;
 }
 
-// dst[r][q] = src[pi_r(q)] for every texel q of the local map, r < nrot.
-__global__ void rotate_pixels(const float* __restrict__ src, const float* __restrict__ rot,
-                              int logn, float* __restrict__ dst) {
-  const int n = 1 << logn;
-  const int per_face = n << logn;
-  const int q = blockIdx.x * blockDim.x + threadIdx.x;
-  const int r = blockIdx.y;
-  if (q >= 6 * per_face) return;
-  const IRot R = frame_vertex_rotation(rot + int64_t(r) * 9, nullptr, scale_bits(logn));
-  const int face = q >> (2 * logn);
-  const int i = (q >> logn) & (n - 1), j = q & (n - 1);
-  const FaceAxes ax = face_axes(R, face);
-  const int U = 2 * j + 1 - n, V = 2 * i + 1 - n;
-  const float3 d = dir_mad(ax.mU, float(U), ax.mV, float(V),
-                           dir_add(ax.mN, float(n), make_float3(0.0f, 0.0f, 0.0f)));
-  // the map stays in [0, 6 n^2) by construction; the clamp keeps this plain
-  // pointer read in bounds whatever the rotation holds
-  const unsigned at = unsigned(source_texel(d, logn));
-  dst[int64_t(r) * 6 * per_face + q] = src[min(at, unsigned(6 * per_face - 1))];
-}
-
 // Waves of a full chip: 256 CUs x 4 SIMDs x 5.
 constexpr int64_t kRoundWaves = 5120;
 
@@ -1571,14 +1550,6 @@ int launch_coarsen_indices(const int32_t* idx, int64_t count, int n, int levels,
   hipLaunchKernelGGL(coarsen_indices, dim3(unsigned((count + 255) / 256)), dim3(256), 0, s, idx,
                      count, ilog2(n), levels, out);
   return check_launch("coarsen_indices");
-}
-
-int launch_rotate_pixels(const float* src, const float* rot, int nrot, int n, float* dst,
-                         hipStream_t s) {
-  const int total = 6 * n * n;
-  hipLaunchKernelGGL(rotate_pixels, dim3(unsigned((total + 255) / 256), unsigned(nrot)), dim3(256),
-                     0, s, src, rot, ilog2(n), dst);
-  return check_launch("rotate_pixels");
 }
 
 }  // namespace rrt

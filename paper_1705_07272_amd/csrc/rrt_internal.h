@@ -58,9 +58,10 @@ int launch_source_map(const int32_t* idx, const void* val, int dtype, int k, int
 // squares: 6 (cube map) or 2 (longitude-latitude map)
 int launch_scatter_light(const int32_t* idx, const void* val, int dtype, int k, int n, int squares,
                          float* dense, hipStream_t s);
-// Pixel-domain rotation of one map for a batch of rotations (relight.hip).
-int launch_rotate_pixels(const float* src, const float* rot, int nrot, int n, float* dst,
-                         hipStream_t s);
+// Haar transform of one map [6][n][n] (in strips for n >= 8) under a batch of
+// rotations (haar.hip).
+int launch_haar_rotated(const float* map, const float* rot, int nrot, int n, float* coef,
+                        hipStream_t s);
 
 struct RelightLaunch {
   const float* src;         // [6][n][n] (lat-long [2][n][n]) source map, in strips of
