@@ -463,23 +463,36 @@ __global__ void to_bf16_kernel(const float* __restrict__ in, uint16_t* __restric
 
 // Weight and bias gradients of up to three layers: dW_l[m][n] = sum_b dz_l[b][m]
 // a_l[b][n] and db_l[m] = sum_b dz_l[b][m], over the batch rows b, which both
-// operands store row by row.  A 256-thread workgroup takes a 64 x 64 tile of one
-// dW over one range of rows, 128 rows at a time: each thread loads an 8 x 8
-// block of one operand (eight 16-byte loads, the next 128 rows' under way while
+// operands store row by row.  The batch is cut into at most 16 ranges of
+// g.rows rows whose sums are added in order of the range, the bias in ranges of
+// 64 rows, so the result does not depend on the launch.  A workgroup takes a
+// 32 x 32 tile of one dW, each of its waves one range: a lane loads an 8 x 8
+// block of one operand (eight 16-byte loads, the next 64 rows' under way while
 // the matrix cores consume these), transposes it in registers (32 byte
-// permutes) and stores it as eight 16-byte LDS rows of 8 consecutive k, which
-// is how the MFMA reads them.  The workgroups of the first column tile also add
-// up their dz for the bias.  Row ranges leave partial sums that grad_sum_kernel
-// adds in order; with one range the results go straight out.
+// permutes) and stores it as eight rows of 8 consecutive k in the wave's own
+// part of LDS, which is how the MFMA reads them; no wave waits for another
+// until their tiles are added up.  Eight more workgroups per layer add up the
+// columns of dz, a range of 64 rows and two columns per thread.
 //
-// What bounds it: latency, at 16 workgroups per layer and range, so the layers
-// whose operands are ready share a launch.  It replaces a GEMM that stored
-// transposed slices two bytes at a time, and column sums in launches of their own:
-// 4,096 rows, all five layers 177 -> 38 us (a training step
-// 287 -> 139).
-constexpr int kGradRows = 128;
-constexpr int kGradStride = kGradRows + 8;  // bf16 per LDS row
+// Layer li is blockIdx.y.  A chip's eight L2s get the workgroups in turn
+// (blockIdx.x % 8): each takes a part of 128 x 64 of dW, so that it reads half
+// of dz and a quarter of the activations.
+//
+// What bounds it: the latency of a range's four slices, at 72 workgroups a
+// layer, so the layers whose operands are ready share a launch.  4,096 rows: a
+// GEMM that stored transposed slices two bytes at a time, with its partial sums
+// in memory and the column sums in launches of their own, took 177 us for all
+// five layers and the training step 287 us; 64 x 64 tiles with partial sums in
+// memory 38 us and 114 us; this way the step takes 110 us, with the sums of the
+// first to the bit (training carries a last place of a weight gradient into the
+// weights' BF16 roundings).
+constexpr int kGradRows = 64;               // rows of a wave's slice
+constexpr int kGradStride = kGradRows + 8;  // bf16 per LDS row (16-byte rows, staggered banks)
 constexpr int kGradLayers = 3;
+constexpr int kGradTiles = 64;              // 32 x 32 tiles of a 256 x 256 dW
+constexpr int kGradBias = RRT_MLP_HIDDEN / 32;
+constexpr int kMaxSplits = 16;
+constexpr int kBiasPass = 64;               // bias ranges added up at a time
 
 struct GradLayer {
   const uint16_t* dz;  // [B][256]
@@ -491,28 +504,77 @@ struct GradLayer {
 struct GradArgs {
   GradLayer layer[kGradLayers];
   int64_t B;
-  int splits;          // row ranges per layer
-  int64_t rows;        // rows of a range (a multiple of kGradRows)
-  float* part;         // [layers][splits][kGradPart], unused with one range
+  int64_t rows;        // rows of a range (a multiple of 32); one wave each
 };
-constexpr int64_t kGradPart = int64_t(RRT_MLP_HIDDEN) * RRT_MLP_HIDDEN + RRT_MLP_HIDDEN;
 
-__global__ __launch_bounds__(256) void grad_kernel(GradArgs g) {
-  __shared__ __align__(16) uint16_t lds[2][64 * kGradStride];
-  const int li = int(blockIdx.z) / g.splits, split = int(blockIdx.z) % g.splits;
-  const GradLayer L = g.layer[li];
-  const int m0 = blockIdx.y * 64, n0 = blockIdx.x * 64;
+__device__ __forceinline__ void wave_lds_order() {
+  __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+  __builtin_amdgcn_wave_barrier();
+  __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+}
+
+// Columns 32 cb .. of one layer's bias gradient.
+__device__ void bias_gradient(const GradLayer& L, int64_t B, int cb, float* red) {
+  const int tid = threadIdx.x, pair = tid & 15, slots = int(blockDim.x) >> 4;
+  const uint16_t* col = L.dz + 32 * cb + 2 * pair;
+  const int64_t ranges = (B + 63) / 64;
+  float total = 0.0f;
+  for (int64_t c0 = 0; c0 < ranges; c0 += kBiasPass) {
+    const int nc = int(ranges - c0 < kBiasPass ? ranges - c0 : kBiasPass);
+    for (int c = tid >> 4; c < nc; c += slots) {
+      const int64_t r0 = (c0 + c) * 64;
+      const int64_t left = B - r0;
+      float s0 = 0.0f, s1 = 0.0f;
+      for (int r = 0; r < 64 && r < left; r += 16) {
+        unsigned v[16];
+#pragma unroll
+        for (int i = 0; i < 16; ++i)
+          v[i] = r + i < left ? *reinterpret_cast<const unsigned*>(col + (r0 + r + i) * RRT_MLP_HIDDEN) : 0u;
+#pragma unroll
+        for (int i = 0; i < 16; ++i) {
+          s0 += __uint_as_float(v[i] << 16);
+          s1 += __uint_as_float(v[i] & 0xffff0000u);
+        }
+      }
+      red[c * 32 + 2 * pair] = s0;
+      red[c * 32 + 2 * pair + 1] = s1;
+    }
+    __syncthreads();
+    if (tid < 32) {
+      float s = 0.0f;
+      for (int c = 0; c < nc; ++c) s += red[c * 32 + tid];
+      total = c0 == 0 ? s : total + s;
+    }
+    __syncthreads();
+  }
+  if (tid < 32) L.db[32 * cb + tid] = total;
+}
+
+__global__ __launch_bounds__(64 * kMaxSplits) void grad_kernel(GradArgs g) {
+  __shared__ __align__(16) uint16_t lds[kMaxSplits][2][32 * kGradStride];
+  static_assert(sizeof(lds) >= kMaxSplits * 1024 * sizeof(float), "the waves' tiles");
+  static_assert(sizeof(lds) >= kBiasPass * 32 * sizeof(float), "a pass of bias ranges");
+  float* red = reinterpret_cast<float*>(&lds[0][0][0]);
+  const GradLayer L = g.layer[blockIdx.y];
+  const int t = blockIdx.x;
+  if (t >= kGradTiles) {
+    bias_gradient(L, g.B, t - kGradTiles, red);
+    return;
+  }
+  const int part = t & 7, in = t >> 3;
+  const int m0 = 128 * (part & 1) + 32 * (in & 3);
+  const int n0 = 64 * (part >> 1) + 32 * (in >> 2);
   if (n0 >= L.n) return;
-  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
-  const int64_t b0 = int64_t(split) * g.rows;
+  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+  const int64_t b0 = int64_t(wave) * g.rows;
   const int64_t b1 = b0 + g.rows < g.B ? b0 + g.rows : g.B;
-  // threads 0..127 load dz, 128..255 the activations: block kb (8 rows) x mb
-  // (8 columns) of the 128 x 64 slice
-  const bool acts = tid >= 128;
-  const int kb = (tid & 127) >> 3, mb = tid & 7;
+  // lanes 0..31 load dz, 32..63 the activations: block kb (8 rows) x mb (8
+  // columns) of the 64 x 32 slice
+  const bool acts = lane >= 32;
+  const int kb = (lane & 31) >> 2, mb = lane & 3;
   const int width = acts ? L.n : RRT_MLP_HIDDEN;
   const uint16_t* from = (acts ? L.a + n0 : L.dz + m0) + 8 * mb;
-  uint16_t* to = lds[acts ? 1 : 0] + 8 * mb * kGradStride + 8 * kb;
+  uint16_t* to = lds[wave][acts ? 1 : 0] + 8 * mb * kGradStride + 8 * kb;
   u32x4_t v[8];
   auto load = [&](int64_t b) {
 #pragma unroll
@@ -522,87 +584,40 @@ __global__ __launch_bounds__(256) void grad_kernel(GradArgs g) {
       if (r < b1) v[i] = *reinterpret_cast<const u32x4_t*>(from + r * width);
     }
   };
-  const bool bias = blockIdx.x == 0 && !acts;
-  float sum[8];
-#pragma unroll
-  for (int j = 0; j < 8; ++j) sum[j] = 0.0f;
   float16_t acc = {};
-  const int wm = (wave >> 1) * 32, wn = (wave & 1) * 32;
-  const uint16_t* ar = lds[0] + (wm + (lane & 31)) * kGradStride + 8 * (lane >> 5);
-  const uint16_t* br = lds[1] + (wn + (lane & 31)) * kGradStride + 8 * (lane >> 5);
+  const uint16_t* ar = lds[wave][0] + (lane & 31) * kGradStride + 8 * (lane >> 5);
+  const uint16_t* br = lds[wave][1] + (lane & 31) * kGradStride + 8 * (lane >> 5);
   load(b0);
   for (int64_t b = b0; b < b1; b += kGradRows) {
 #pragma unroll
     for (int j = 0; j < 8; ++j) {
-      u32x4_t t;
+      u32x4_t w;
 #pragma unroll
       for (int p = 0; p < 4; ++p)
-        t[p] = __builtin_amdgcn_perm(v[2 * p + 1][j / 2], v[2 * p][j / 2],
+        w[p] = __builtin_amdgcn_perm(v[2 * p + 1][j / 2], v[2 * p][j / 2],
                                      (j & 1) ? 0x07060302u : 0x05040100u);
-      *reinterpret_cast<u32x4_t*>(to + j * kGradStride) = t;
-      if (bias) {
-#pragma unroll
-        for (int p = 0; p < 4; ++p)
-          sum[j] += __uint_as_float(t[p] << 16) + __uint_as_float(t[p] & 0xffff0000u);
-      }
+      *reinterpret_cast<u32x4_t*>(to + j * kGradStride) = w;
     }
-    __syncthreads();
+    wave_lds_order();
     if (b + kGradRows < b1) load(b + kGradRows);
 #pragma unroll
     for (int s = 0; s < kGradRows / 16; ++s)
       acc = __builtin_amdgcn_mfma_f32_32x32x16_bf16(
           *reinterpret_cast<const bf16x8_t*>(ar + 16 * s),
           *reinterpret_cast<const bf16x8_t*>(br + 16 * s), acc, 0, 0, 0);
-    __syncthreads();
+    wave_lds_order();
   }
-  float* dw = L.dw;
-  float* db = L.db;
-  if (g.splits > 1) {
-    dw = g.part + (int64_t(li) * g.splits + split) * kGradPart;
-    db = dw + int64_t(RRT_MLP_HIDDEN) * RRT_MLP_HIDDEN;
+  __syncthreads();
+#pragma unroll
+  for (int r = 0; r < 16; ++r)
+    red[wave * 1024 + (8 * (r >> 2) + 4 * (lane >> 5) + (r & 3)) * 32 + (lane & 31)] = acc[r];
+  __syncthreads();
+  const int waves = int(blockDim.x) >> 6;
+  for (int e = threadIdx.x; e < 1024; e += int(blockDim.x)) {
+    float s = 0.0f;
+    for (int z = 0; z < waves; ++z) s += red[z * 1024 + e];
+    L.dw[int64_t(m0 + (e >> 5)) * L.n + n0 + (e & 31)] = s;
   }
-#pragma unroll
-  for (int r = 0; r < 16; ++r) {
-    const int m = m0 + wm + 8 * (r >> 2) + 4 * (lane >> 5) + (r & 3);
-    dw[int64_t(m) * L.n + n0 + wn + (lane & 31)] = acc[r];
-  }
-  if (blockIdx.x == 0) {  // (uniform) bias: the 16 row blocks' sums, in order
-    float* red = reinterpret_cast<float*>(lds[0]);
-    if (!acts) {
-#pragma unroll
-      for (int j = 0; j < 8; ++j) red[kb * 64 + 8 * mb + j] = sum[j];
-    }
-    __syncthreads();
-    if (tid < 64) {
-      float s = 0.0f;
-#pragma unroll
-      for (int k = 0; k < 16; ++k) s += red[k * 64 + tid];
-      db[m0 + tid] = s;
-    }
-  }
-}
-
-// Sums of the row ranges' partial gradients, in order (all loads of a chunk of
-// ranges are in flight together).
-__global__ __launch_bounds__(256) void grad_sum_kernel(GradArgs g) {
-  const int64_t i = int64_t(blockIdx.x) * 256 + threadIdx.x;
-  const GradLayer L = g.layer[blockIdx.y];
-  const int64_t nw = int64_t(RRT_MLP_HIDDEN) * L.n;
-  constexpr int64_t kBias = int64_t(RRT_MLP_HIDDEN) * RRT_MLP_HIDDEN;
-  if (i >= nw + RRT_MLP_HIDDEN) return;
-  const float* p = g.part + int64_t(blockIdx.y) * g.splits * kGradPart + (i < nw ? i : kBias + i - nw);
-  float s = 0.0f;
-  for (int z0 = 0; z0 < g.splits; z0 += 8) {
-    float v[8];
-#pragma unroll
-    for (int z = 0; z < 8; ++z) v[z] = z0 + z < g.splits ? p[(z0 + z) * kGradPart] : 0.0f;
-#pragma unroll
-    for (int z = 0; z < 8; ++z) s += v[z];
-  }
-  if (i < nw)
-    L.dw[i] = s;
-  else
-    L.db[i - nw] = s;
 }
 
 // dout = 2 (out - target) / count; loss += sum (out - target)^2 / count (FP64).
@@ -680,30 +695,21 @@ int gemm(const GemmArgs& a, hipStream_t s) {
 
 inline unsigned blocks(int64_t n, int per = 256) { return unsigned((n + per - 1) / per); }
 
-// Partial weight gradients the workspace holds (256 x 256 floats each): one
-// per 256 rows, at most kMaxSplits.
-constexpr int kMaxSplits = 16;
+// Row ranges of the weight gradients' sums over a batch of B rows: one per 256
+// rows, at most kMaxSplits.
 inline int dw_splits(int64_t B) {
   const int64_t s = (B + 255) / 256;
   return int(s < 1 ? 1 : (s > kMaxSplits ? kMaxSplits : s));
 }
 
-// Gradients of `layers` layers over the batch, in as many row ranges as their
-// partials have room for (one: written straight out).
+// Gradients of `layers` layers over the batch.
 int launch_grads(GradArgs g, int layers, hipStream_t s) {
-  const int64_t room = int64_t(dw_splits(g.B)) * RRT_MLP_HIDDEN * RRT_MLP_HIDDEN;
-  int64_t splits = room / (layers * kGradPart);
-  const int64_t most = (g.B + kGradRows - 1) / kGradRows;
-  if (splits > most) splits = most;
-  if (splits < 1) splits = 1;
-  g.rows = ((g.B + splits - 1) / splits + kGradRows - 1) / kGradRows * kGradRows;
-  g.splits = int((g.B + g.rows - 1) / g.rows);
-  hipLaunchKernelGGL(grad_kernel, dim3(4, 4, unsigned(layers * g.splits)), dim3(256), 0, s, g);
-  int st = check_launch("grad");
-  if (st || g.splits == 1) return st;
-  hipLaunchKernelGGL(grad_sum_kernel, dim3(unsigned((kGradPart + 255) / 256), unsigned(layers)),
-                     dim3(256), 0, s, g);
-  return check_launch("grad_sum");
+  const int64_t splits = dw_splits(g.B);
+  g.rows = ((g.B + splits - 1) / splits + 31) / 32 * 32;
+  const int waves = int((g.B + g.rows - 1) / g.rows);
+  hipLaunchKernelGGL(grad_kernel, dim3(kGradTiles + kGradBias, unsigned(layers)), dim3(64 * waves), 0,
+                     s, g);
+  return check_launch("grad");
 }
 
 }  // namespace
@@ -730,7 +736,8 @@ int64_t mlp_bias_offset(int l) {
 //   a_l  BF16 [B][256] for the 4 hidden layers,
 //   dz   BF16 [B][256] x 2 (ping-pong, backward only),
 //   dout BF16 [B][256] (backward only),
-//   the weight-gradient GEMM's split partial sums, FP32 [S][256][256].
+//   256 KiB per row range (FP32 [S][256][256]), which callers provide and the
+//   gradients no longer need.
 size_t mlp_workspace_bytes(int64_t B) {
   const size_t rows = size_t(B) * RRT_MLP_HIDDEN;
   return align256(rows * 4) * 4 + align256(rows * 2) * 4 + align256(rows * 2) * 2 +
@@ -743,7 +750,6 @@ struct MlpWs {
   uint16_t* a[4];
   uint16_t* dz[2];
   uint16_t* dout_bf16;
-  float* dw_part;
 };
 
 static MlpWs carve(void* ws, int64_t B) {
@@ -763,8 +769,6 @@ static MlpWs carve(void* ws, int64_t B) {
     p += align256(rows * 2);
   }
   w.dout_bf16 = reinterpret_cast<uint16_t*>(p);
-  p += align256(size_t(B) * RRT_MLP_OUT * 2);
-  w.dw_part = reinterpret_cast<float*>(p);
   return w;
 }
 
@@ -845,7 +849,6 @@ int launch_mlp_backward(const void* w, const void* x, int64_t B, const float* do
   auto grads = [&](int top, int layers) {
     GradArgs g = {};
     g.B = B;
-    g.part = k.dw_part;
     for (int i = 0; i < layers; ++i) {
       const int l = top - i;
       g.layer[i] = {dz[l], l == 0 ? static_cast<const uint16_t*>(x) : k.a[l - 1], kIn[l],

@@ -49,6 +49,32 @@ def test_gradients_row_ranges(rrt, B):
         bo += o
 
 
+@pytest.mark.parametrize("B", [1, 63, 65, 4096, 4500, 9000])
+def test_bias_gradient_order(rrt, B):
+    """The output layer's bias gradient is the binary32 sum of ranges of 64
+    rows, added in order, at most 64 ranges at a time: the same bits."""
+    _, _, w_dev, b_dev = _net(5)
+    g = np.random.default_rng(B)
+    x = _bf16(ref.encode(g.uniform(-1, 1, size=(B, 6)))).cuda()
+    dout = g.normal(size=(B, ref.OUT)).astype(np.float32)
+    ws = rrt.mlp_workspace(B, "cuda")
+    rrt.mlp_forward(w_dev, b_dev, x, workspace=ws)
+    _, db = rrt.mlp_backward(w_dev, x, torch.from_numpy(dout).cuda(), ws)
+    dz = np.zeros((-(-B // 64) * 64, ref.OUT), np.float32)
+    dz[:B] = _bf16(dout).float().numpy()
+    dz = dz.reshape(-1, 64, ref.OUT)
+    ranges = np.zeros((len(dz), ref.OUT), np.float32)
+    for r in range(64):
+        ranges += dz[:, r]
+    total = None
+    for c0 in range(0, len(dz), 64):
+        s = np.zeros(ref.OUT, np.float32)
+        for part in ranges[c0:c0 + 64]:
+            s = s + part
+        total = s if total is None else total + s
+    assert np.array_equal(db[-ref.OUT:].cpu().numpy(), total)
+
+
 @pytest.mark.parametrize("count,offset", [(1, 0), (7, 0), (4096, 1), (300003, 0), (300004, 3)])
 def test_loss_alignment(rrt, count, offset):
     """dout is one subtraction, an exact doubling and one division (two
