@@ -1192,14 +1192,25 @@ __global__ __launch_bounds__(kThreads, CHAIN || LOGN ? 5 : 1) void relight_kerne
             // a dense row has one entry for every position of the image (the
             // block's corner belongs to the levels above); looking through the
             // row for each block instead took 196 us for 1,000 vertices at
-            // n = 32, this 55
+            // n = 32, this 55, and 52 with eight entries of a lane in flight
             if constexpr (DENSE) {
-              for (int e = lane == 0 ? kThreads : lane; e < Q * Q && nnz > 0; e += kThreads) {
-                const int pr = e >> LOGQ, pc = e & (Q - 1);
-                const int at = slot_index(face, by * Q + pr, bx * Q + pc, logn);
-                const int logb = __builtin_ctz(unsigned(pr | pc)) + 1;
-                acc_add(acc, transport_value(p.tval, p.tscale, p.dtype, v, p.nnz, at),
-                        ldexpf(img[pr * STRIDE + pc], -logb), comp);
+              constexpr int kAhead = Q == 32 ? 8 : 1;
+              for (int e0 = lane; e0 < Q * Q && nnz > 0; e0 += kAhead * kThreads) {
+                float tv[kAhead];
+#pragma unroll
+                for (int j = 0; j < kAhead; ++j) {
+                  const int e = e0 + j * kThreads;
+                  const int at = slot_index(face, by * Q + (e >> LOGQ), bx * Q + (e & (Q - 1)), logn);
+                  tv[j] = transport_value(p.tval, p.tscale, p.dtype, v, p.nnz, at);
+                }
+#pragma unroll
+                for (int j = 0; j < kAhead; ++j) {
+                  const int e = e0 + j * kThreads;
+                  const int pr = e >> LOGQ, pc = e & (Q - 1);
+                  if (e != 0)
+                    acc_add(acc, tv[j], ldexpf(img[pr * STRIDE + pc], -1 - __builtin_ctz(unsigned(pr | pc))),
+                            comp);
+                }
               }
             }
             // entries past the list
