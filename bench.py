@@ -38,8 +38,8 @@ PEAK_HBM_GBS = 8000.0
 # masks, their minimum, a compare: 4), the row-major flat index from the
 # significand bits (2 shifts, 2 shift-adds), the gather (1) and the share of
 # the 2x2 levels (4: twelve adds per four texels per level, x 4/3 over the
-# levels).  The strip layout of the source map costs 2 more instructions per
-# texel, counted as overhead.
+# levels).  The count is kept as the measure of the work; where a part of a
+# block lies inside one source face the kernel needs fewer.
 OPS_PER_TEXEL = 24
 # The same count for the chain-rule rotation of the finest level: per 2x2
 # destination block the map at n/2 without the levels (19), its 16-byte

@@ -67,7 +67,7 @@ extern "C" int rrt_relight_noalloc(const rrt_light* L, const rrt_rotations* R,
   void* ws = nullptr;
   st = scratch_address(&ws);
   if (st) return st;
-  // the staging part is cleared by a fill kernel inside, the source map is
-  // written whole: nothing depends on what an earlier call left behind
+  // the staging part is cleared by a fill kernel where it is used, the source map
+  // is written whole: nothing depends on what an earlier call left behind
   return rrt_relight(L, R, T, radiance, flags, ws, kScratchBytes, stream);
 }

@@ -15,7 +15,8 @@
 //   * the faces touched by the vertex's transport row are processed, each as
 //     G x G blocks of Q x Q texels (Q = min(n, 32));
 //   * per block, a lane gathers one texel of each 8 x 8 patch (a compact patch
-//     per load instruction) into an LDS image, then
+//     per load instruction, in four quarters that each may lie inside one
+//     source face) into an LDS image, then
 //     runs the levels of its own 4 x 4 tile in registers and the levels up to
 //     the block with lane shuffles, in place (the coefficient of a block of
 //     side B at its corner offset by B/2 for H/V/D);
@@ -50,7 +51,7 @@ constexpr int kBlock = 32;
 constexpr int kMaxListed = 512;
 // Chunks of 64 transport entries whose loads the listing issues together.
 constexpr int kListChunks = 4;
-// LDS for the FP64 block sums of the faces processed together.
+// LDS for the FP64 block weights of the faces processed together.
 constexpr int kGroupBytes = 4096;
 // LDS bit mask of the blocks of a face group that hold listed entries (at
 // most 1,024 blocks: kGroupBytes / 8, or one face of 32 x 32 blocks)
@@ -303,7 +304,8 @@ __device__ __forceinline__ unsigned latlong_source(const LLTab& t, int i, int jc
 // What bounds it: vector issue.  Two binary searches take 7 log2 H operations
 // and dependent LDS reads per texel, the estimates 48 instructions in all and
 // two independent reads.  50,000 vertices at H = 128: 3.26 -> 2.01 ms (the rounded rho
-// for every texel 2.15; the whole search again for a close one 2.69).
+// for every texel 2.15; the whole search again for a close one 2.69), and 1.13 ms
+// since blocks of weight zero are left out.
 template <int LOGH, bool EXACT>
 __device__ __forceinline__ unsigned latlong_fast(const LLTab& t, int i, int jc, float cb, float sb,
                                                  int sa, float& gap) {
@@ -476,7 +478,9 @@ __device__ __forceinline__ void tile_level_above(float& s, float* img, int lane,
 // Calls, before (one way for every texel, lanes row by row) and after: lighting
 // step with 50,000 vertices, n = 128, 256 coefficients, 0.639 -> 0.584 ms; 200,000
 // vertices, n = 256, 8.14 -> 7.21 ms; 12,500 vertices x 64 frames, n = 128, 9.03 ->
-// 8.07 ms.
+// 8.07 ms.  With the weights of the levels above the blocks and the frames divided
+// among waves these three take 0.541, 7.00 and 6.82 ms: 21.5 vector instructions per
+// texel in all (28.9 before), the texture data path busy 0.93 of the cycles.
 // ---------------------------------------------------------------------------
 constexpr int kMixed = 6;  // quarter_face: several faces
 
@@ -713,7 +717,7 @@ __device__ __forceinline__ int slot_index(int face, int pr, int pc, int logn) {
 // wide except the face's scaling coefficient: returns 0, key = block side,
 // gi and position in the block image (which holds unscaled coefficients).
 // The others (blocks wider than Q, and the face's scaling coefficient) are
-// "coarse": returns 1, key = index of the group's in-place block-sum grid.
+// "coarse": returns 1, key = index in the group's in-place weight grid.
 // Returns -1 for entries outside the group or invalid indices.
 template <int Q, int NF>
 __device__ __forceinline__ int classify(int idx, int logn, int G, unsigned faces, int g0, int FG,
@@ -742,7 +746,7 @@ __device__ __forceinline__ int classify(int idx, int logn, int G, unsigned faces
 // elevation-plus-shift rotation of latlong_source) instead of a cube map.
 // The chain-rule variant is held to 5 waves per SIMD (96 VGPRs, a few
 // spilled): 0.430 -> 0.411 ms on the benchmark launch against 4 waves
-// unspilled; the lat-long variant held to 6 waves spills more and runs
+// unspilled (0.370 now); the lat-long variant held to 6 waves spills more and runs
 // slower, so it keeps its 5.
 // LOGN: log2 n where the block is gathered in quarters (cube map, exact
 // rotation, n >= 32) and for the lat-long map, else 0 and n is a parameter.
@@ -994,7 +998,8 @@ __global__ __launch_bounds__(kThreads, CHAIN || LOGN ? 5 : 1) void relight_kerne
             // weight of the block's sum (orthonormal scaling coefficient: 1 / Q)
             const double weight = gW[gi] * (1.0 / Q);
             // nothing reads a block of weight zero (the part of a lobe's square
-            // below the horizon, where the entries of the levels above cancel):
+            // below the horizon, where the entries of the levels above cancel), so
+            // no texel of it reaches the result, an infinite one neither:
             // 50,000 lat-long vertices at H = 128 2.01 -> 1.13 ms
             if (!full && __ballot(weight != 0.0) == 0) continue;
             if constexpr (BRDF && QUARTERS) {
@@ -1409,8 +1414,8 @@ int launch_q(const RelightParams& prm_in, int64_t nvert, hipStream_t s) {
   // A vertex's frames share its entry list, but a wave per vertex can be too few
   // of them, or leave the last round of the chip (kRoundWaves at a time) mostly
   // empty: the frames are divided until there are eight rounds.
-  // 12,500 vertices x 64 frames at n = 128 (2.4 rounds undivided): 8.07 -> 7.33
-  // ms; the list is then built once for 16 frames.
+  // 12,500 vertices x 64 frames at n = 128 (2.4 rounds undivided): 8.07 -> 7.21
+  // ms (6.82 now); the list is then built once for 16 frames.
   int64_t split = nvert > 0 ? (8 * kRoundWaves + nvert - 1) / nvert : 1;
   if (split > prm.nframes) split = prm.nframes;
   if (split > 65535) split = 65535;
