@@ -1,17 +1,10 @@
-// Learned transport decoder (not part of the paper): positional encoding,
-// BF16 MFMA GEMMs with fused bias / GELU epilogues for the forward and
-// backward passes, MSE loss, bias-gradient column sums and Adam.
+// Learned transport decoder (not part of the paper): positional encoding, the
+// network for inference (decode_kernel) and for training (forward_kernel,
+// back_kernel, grad_kernel), MSE loss and Adam.
 //
-// GEMM: C[M][N] = sum_k A(m, k) B(k, n), A and B in bfloat16, FP32
-// accumulation on the matrix cores (v_mfma_f32_32x32x16_bf16, wave64).  A is
-// stored [M][K]; B is stored [K][N] or, transposed, [N][K]; the contiguous
-// dimension of each is a multiple of 8.  A 256-thread workgroup computes a
-// (64 TM) x (64 TM) tile of C, each of its four waves a TM x TM grid of 32 x 32
-// MFMA tiles.  Each k-slice of A and B is loaded with 16-byte vector loads (the
-// next slice is in flight while the matrix cores consume the current one) and
-// staged in LDS in k-contiguous rows, from which every lane reads its 8
-// k-consecutive operands with one 16-byte LDS read.  Rows, columns and k beyond
-// the matrix read as zero and are not stored.
+// Weights and the layers' inputs are bfloat16, products are summed in FP32 by
+// the matrix cores (v_mfma_f32_32x32x16_bf16, wave64) in steps of 16 of the
+// inner index, in order: the same value is the same bits in every kernel.
 #include <hip/hip_fp16.h>
 
 #include "rrt_internal.h"
@@ -53,161 +46,6 @@ __device__ __forceinline__ float gelu_grad_f(float z) {
   const float sg = gelu_sigma(z);
   const float du = kSqrt2OverPi * (1.0f + 3.0f * kGeluC * z * z);
   return sg + 2.0f * z * sg * (1.0f - sg) * du;
-}
-
-enum Epilogue {
-  kEpiHidden = 0,   // z = acc + bias -> store z (FP32) and gelu(z) (BF16)
-  kEpiOutput = 1,   // out = acc + bias -> FP32
-  kEpiGeluGrad = 2  // dz = acc * gelu'(zprev) -> BF16
-};
-
-struct GemmArgs {
-  const uint16_t* A;
-  const uint16_t* B;
-  int M, N, K;
-  const float* bias;   // [N] (kEpiHidden / kEpiOutput)
-  const float* zprev;  // [M][N] (kEpiGeluGrad)
-  float* out_f32;      // [M][N]
-  uint16_t* out_bf16;  // [M][N]
-};
-
-// 8 consecutive bf16 of a row-major [rows][cols] matrix from (r, c), or zeros
-// outside it (c and cols are multiples of 8).
-__device__ __forceinline__ u32x4_t load8(const uint16_t* base, int rows, int cols, int r, int c) {
-  u32x4_t v = {0u, 0u, 0u, 0u};
-  if (r < rows && c < cols) v = *reinterpret_cast<const u32x4_t*>(base + int64_t(r) * cols + c);
-  return v;
-}
-
-// One operand's k-slice: R rows x BK k, from a k-contiguous ([rows][K]) or
-// row-contiguous ([K][rows]) matrix.  K-contiguous: 16-byte pieces, R BK / 2048
-// per thread.  Row-contiguous: a thread takes an 8 x 8 block (eight 16-byte
-// loads), transposes it in registers (32 byte permutes) and stores eight
-// 16-byte LDS rows.
-template <int R, bool KCONTIG, int BK>
-struct Slice {
-  static constexpr int kStride = BK + 8;
-  static constexpr int kPer = KCONTIG ? R * BK / 8 / 256 : 8;
-  static_assert(KCONTIG || R * BK / 64 <= 256, "one block per thread");
-  u32x4_t v[kPer];
-  __device__ __forceinline__ void load(const uint16_t* base, int rows, int K, int r0, int k0) {
-    if (KCONTIG) {
-#pragma unroll
-      for (int i = 0; i < kPer; ++i) {
-        const int e = i * 256 + int(threadIdx.x);
-        v[i] = load8(base, rows, K, r0 + e / (BK / 8), k0 + e % (BK / 8) * 8);
-      }
-    } else if (int(threadIdx.x) < R * BK / 64) {
-      const int kb = int(threadIdx.x) / (R / 8), rb = int(threadIdx.x) % (R / 8);
-#pragma unroll
-      for (int i = 0; i < 8; ++i) v[i] = load8(base, K, rows, k0 + 8 * kb + i, r0 + 8 * rb);
-    }
-  }
-  __device__ __forceinline__ void store(uint16_t* lds) const {
-    if (KCONTIG) {
-#pragma unroll
-      for (int i = 0; i < kPer; ++i) {
-        const int e = i * 256 + int(threadIdx.x);
-        *reinterpret_cast<u32x4_t*>(lds + e / (BK / 8) * kStride + e % (BK / 8) * 8) = v[i];
-      }
-    } else if (int(threadIdx.x) < R * BK / 64) {
-      const int kb = int(threadIdx.x) / (R / 8), rb = int(threadIdx.x) % (R / 8);
-#pragma unroll
-      for (int j = 0; j < 8; ++j) {
-        u32x4_t t;
-#pragma unroll
-        for (int p = 0; p < 4; ++p)
-          t[p] = __builtin_amdgcn_perm(v[2 * p + 1][j / 2], v[2 * p][j / 2],
-                                       (j & 1) ? 0x07060302u : 0x05040100u);
-        *reinterpret_cast<u32x4_t*>(lds + (8 * rb + j) * kStride + 8 * kb) = t;
-      }
-    }
-  }
-};
-
-// k per slice: 64 x 64 tiles (TM = 1) are for batches that leave each CU a
-// workgroup or two, where every slice's load and barrier latency counts:
-// 128 of k at a time; 128 x 128 tiles keep 32.
-constexpr int slice_k(int TM) { return TM == 1 ? 128 : 32; }
-
-template <bool BT, int EPI, int TM>
-__global__ __launch_bounds__(256) void gemm_bf16(GemmArgs g) {
-  constexpr int BM = 64 * TM, BN = 64 * TM;
-  constexpr int BK = slice_k(TM), kStride = BK + 8;  // bf16 elements per LDS row (16-byte rows, staggered banks)
-  __shared__ __align__(16) uint16_t As[BM * kStride];
-  __shared__ __align__(16) uint16_t Bs[BN * kStride];
-  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-  const int m0 = blockIdx.y * BM, n0 = blockIdx.x * BN;
-  const int wm = (wave >> 1) * 32 * TM, wn = (wave & 1) * 32 * TM;
-  float16_t acc[TM][TM];
-#pragma unroll
-  for (int i = 0; i < TM; ++i)
-#pragma unroll
-    for (int j = 0; j < TM; ++j) acc[i][j] = float16_t{};
-
-  Slice<BM, true, BK> sa;
-  Slice<BN, BT, BK> sb;
-  sa.load(g.A, g.M, g.K, m0, 0);
-  sb.load(g.B, g.N, g.K, n0, 0);
-  for (int k0 = 0; k0 < g.K; k0 += BK) {
-    sa.store(As);
-    sb.store(Bs);
-    __syncthreads();
-    if (k0 + BK < g.K) {
-      sa.load(g.A, g.M, g.K, m0, k0 + BK);
-      sb.load(g.B, g.N, g.K, n0, k0 + BK);
-    }
-#pragma unroll
-    for (int kk = 0; kk < BK; kk += 16) {
-      // lane l: operand row l % 32, k = kk + 8 (l / 32) .. + 7
-      const int ko = kk + 8 * (lane >> 5);
-      bf16x8_t a[TM], b[TM];
-#pragma unroll
-      for (int i = 0; i < TM; ++i)
-        a[i] = *reinterpret_cast<const bf16x8_t*>(&As[(wm + 32 * i + (lane & 31)) * kStride + ko]);
-#pragma unroll
-      for (int j = 0; j < TM; ++j)
-        b[j] = *reinterpret_cast<const bf16x8_t*>(&Bs[(wn + 32 * j + (lane & 31)) * kStride + ko]);
-#pragma unroll
-      for (int i = 0; i < TM; ++i)
-#pragma unroll
-        for (int j = 0; j < TM; ++j)
-          acc[i][j] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a[i], b[j], acc[i][j], 0, 0, 0);
-    }
-    __syncthreads();
-  }
-  // D[m][n]: register r of lane l holds row 8 (r / 4) + 4 (l / 32) + r % 4, column l % 32.
-  // What the epilogue reads is loaded for all 16 registers before any is used or
-  // stored (one after the other, the 16 round trips took longer than the products).
-#pragma unroll
-  for (int i = 0; i < TM; ++i)
-#pragma unroll
-    for (int j = 0; j < TM; ++j) {
-      const int mb = m0 + wm + 32 * i + 4 * (lane >> 5), n = n0 + wn + 32 * j + (lane & 31);
-      if (n >= g.N) continue;
-      float add = 0.0f, z[16];
-      if (EPI != kEpiGeluGrad) add = g.bias[n];
-#pragma unroll
-      for (int r = 0; r < 16; ++r) {
-        const int m = mb + 8 * (r >> 2) + (r & 3);
-        if (EPI == kEpiGeluGrad) z[r] = g.zprev[int64_t(min(m, g.M - 1)) * g.N + n];
-      }
-#pragma unroll
-      for (int r = 0; r < 16; ++r) {
-        const int m = mb + 8 * (r >> 2) + (r & 3);
-        if (m >= g.M) continue;
-        const int64_t at = int64_t(m) * g.N + n;
-        const float x = acc[i][j][r];
-        if (EPI == kEpiHidden) {
-          g.out_f32[at] = x + add;
-          g.out_bf16[at] = bf16_bits(gelu_f(x + add));
-        } else if (EPI == kEpiOutput) {
-          g.out_f32[at] = x + add;
-        } else {
-          g.out_bf16[at] = bf16_bits(x * gelu_grad_f(z[r]));
-        }
-      }
-    }
 }
 
 // Band q of gamma(x) = (x, sin(2^k pi x), cos(2^k pi x), k = 0..7) of the 6
@@ -293,11 +131,11 @@ __global__ void pack_kernel(const uint16_t* __restrict__ w, uint16_t* __restrict
 // ends with four consecutive features of one vertex per register group and
 // stores them with one 8-byte LDS write.  The output layer goes through
 // LDS as float rows, 32 vertices at a time, so that each wave writes whole
-// 1 KiB rows of the result.  The k steps, the products and their order are those of gemm_bf16
+// 1 KiB rows of the result.  The k steps, the products and their order are those of forward_kernel
 // (a product of two operands is the same either way round), and so are
 // the epilogues (bias + GELU rounded to bfloat16; bias, then the per-slot
 // scale of the vertex's cluster for the output): the values are
-// bit-identical to encode + five gemm_bf16 launches + the per-slot scaling
+// bit-identical to encode + forward_kernel + the per-slot scaling
 // in binary32.
 constexpr int kDecRows = 64;
 constexpr int kDecTiles = kDecRows / 32;  // 32-vertex MFMA tiles per workgroup
@@ -453,12 +291,6 @@ __global__ __launch_bounds__(64 * kDecWaves, 6) void decode_kernel(const float* 
     Wl += int64_t(K) * RRT_MLP_HIDDEN;
     bl += RRT_MLP_HIDDEN;
   }
-}
-
-__global__ void to_bf16_kernel(const float* __restrict__ in, uint16_t* __restrict__ out,
-                               int64_t n) {
-  const int64_t t = int64_t(blockIdx.x) * blockDim.x + threadIdx.x;
-  if (t < n) out[t] = bf16_bits(in[t]);
 }
 
 // Weight and bias gradients of up to three layers: dW_l[m][n] = sum_b dz_l[b][m]
@@ -620,6 +452,208 @@ __global__ __launch_bounds__(64 * kMaxSplits) void grad_kernel(GradArgs g) {
   }
 }
 
+// The layers of a training step for 32 rows of the batch in one 512-thread
+// workgroup: wave w computes the features [32 w, 32 w + 32) of every layer as
+// the transposed product W A^T, like the decoder, with the rows' values in LDS
+// from layer to layer.  Its 32 rows of the weights (row by row in memory) come
+// in whole cache lines through its own part of LDS; loaded as the matrix cores'
+// operands, 32 rows of 32 bytes at a time, they went through the L1 four times
+// (forward 27.8 us for 4,096 rows, this way 19.5).
+//
+// What bounds it: a layer's chain of weight load, LDS, products and barrier,
+// 4 us, with 128 workgroups for 4,096 rows.  A GEMM launch per layer, its
+// operands through memory, took 37.4 us forward and 63.8 back (55.1 now); for
+// 65,536 rows 216 and 657 (154 and 600), for 64 rows 29.9 and 37.3 (16.5 and
+// 30.7), so that way has no size left.  A training step at 4,096 rows 110 -> 86 us.
+constexpr int kRowTile = 32;
+// four floats of a caller's array, which need not start on 16 bytes
+typedef float float4_u __attribute__((ext_vector_type(4), aligned(4)));
+
+struct ForwardArgs {
+  const uint16_t* x;  // [B][128]
+  const uint16_t* W;  // row-major layers
+  const float* bias;
+  int64_t B;
+  float* z[4];
+  uint16_t* a[4];
+  float* out;
+};
+
+// The tile's rows of 256 bfloat16 from LDS to rows r0.. of a [B][256] array.
+__device__ __forceinline__ void store_rows(const uint16_t* act, int64_t r0, int64_t B,
+                                           uint16_t* __restrict__ to) {
+#pragma unroll
+  for (int i = 0; i < 2; ++i) {
+    const int e = int(threadIdx.x) + 512 * i, row = e >> 5, c = (e & 31) * 8;
+    if (r0 + row < B)
+      *reinterpret_cast<u32x4_t*>(to + (r0 + row) * RRT_MLP_HIDDEN + c) =
+          *reinterpret_cast<const u32x4_t*>(act + row * kActStride + c);
+  }
+}
+
+__global__ __launch_bounds__(512) void forward_kernel(ForwardArgs g) {
+  __shared__ __align__(16) uint16_t wt[8][32 * kActStride];
+  __shared__ __align__(16) uint16_t act[kRowTile * kActStride];
+  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+  const int n0 = 32 * wave, fl = 4 * (lane >> 5), ml = lane & 31;
+  const int64_t r0 = int64_t(blockIdx.x) * kRowTile, m = r0 + ml;
+  const uint16_t* Wl = g.W;
+  const float* bl = g.bias;
+  uint16_t* own = wt[wave];
+  // the wave's 32 rows of a layer, 1 KiB per load (4 rows of 128 or 2 of 256)
+  u32x4_t v[16];
+  constexpr int kIn8 = RRT_MLP_IN / 8, kHid8 = RRT_MLP_HIDDEN / 8;
+#pragma unroll
+  for (int i = 0; i < kIn8 / 2; ++i)
+    v[i] = *reinterpret_cast<const u32x4_t*>(Wl + n0 * RRT_MLP_IN + (64 * i + lane) * 8);
+  {
+    const int row = threadIdx.x >> 4, c = (threadIdx.x & 15) * 8;
+    u32x4_t t = {0u, 0u, 0u, 0u};
+    if (r0 + row < g.B) t = *reinterpret_cast<const u32x4_t*>(g.x + (r0 + row) * RRT_MLP_IN + c);
+    *reinterpret_cast<u32x4_t*>(act + row * kActStride + c) = t;
+  }
+  __syncthreads();
+  const uint16_t* wr = own + ml * kActStride + 8 * (lane >> 5);
+  const uint16_t* ar = act + ml * kActStride + 8 * (lane >> 5);
+#pragma unroll
+  for (int l = 0; l < RRT_MLP_WEIGHTS; ++l) {
+    const int K = l == 0 ? RRT_MLP_IN : RRT_MLP_HIDDEN, k8 = K / 8;
+#pragma unroll
+    for (int i = 0; i < k8 / 2; ++i) {
+      const int e = 64 * i + lane;
+      *reinterpret_cast<u32x4_t*>(own + e / k8 * kActStride + e % k8 * 8) = v[i];
+    }
+    wave_lds_order();
+    // the next layer's weights are under way during this one's products
+    Wl += int64_t(K) * RRT_MLP_HIDDEN;
+    if (l + 1 < RRT_MLP_WEIGHTS) {
+#pragma unroll
+      for (int i = 0; i < kHid8 / 2; ++i)
+        v[i] = *reinterpret_cast<const u32x4_t*>(Wl + n0 * RRT_MLP_HIDDEN + (64 * i + lane) * 8);
+    }
+    float16_t acc = {};
+#pragma unroll
+    for (int s = 0; s < K / 16; ++s)
+      acc = __builtin_amdgcn_mfma_f32_32x32x16_bf16(
+          *reinterpret_cast<const bf16x8_t*>(wr + 16 * s),
+          *reinterpret_cast<const bf16x8_t*>(ar + 16 * s), acc, 0, 0, 0);
+    __syncthreads();  // every wave has read its operands: the buffer is free
+#pragma unroll
+    for (int q = 0; q < 4; ++q) {
+      const int n = n0 + 8 * q + fl;
+      const float4_u x = {acc[4 * q] + bl[n], acc[4 * q + 1] + bl[n + 1],
+                          acc[4 * q + 2] + bl[n + 2], acc[4 * q + 3] + bl[n + 3]};
+      float* to = l + 1 < RRT_MLP_WEIGHTS ? g.z[l < 4 ? l : 0] : g.out;
+      if (m < g.B) *reinterpret_cast<float4_u*>(to + m * RRT_MLP_HIDDEN + n) = x;
+      if (l + 1 < RRT_MLP_WEIGHTS) {
+        uint2 o;
+        o.x = bf16x2_bits(gelu_f(x[0]), gelu_f(x[1]));
+        o.y = bf16x2_bits(gelu_f(x[2]), gelu_f(x[3]));
+        *reinterpret_cast<uint2*>(act + ml * kActStride + n) = o;
+      }
+    }
+    bl += RRT_MLP_HIDDEN;
+    if (l + 1 < RRT_MLP_WEIGHTS) {
+      __syncthreads();
+      store_rows(act, r0, g.B, g.a[l < 4 ? l : 0]);
+    }
+  }
+}
+
+// Two layers back: dz_{l-1} = (dz_l W_l) * gelu'(z_{l-1}), from dout (also
+// stored as bfloat16) or from a dz.  The weights are needed with 8 consecutive
+// rows per lane: a wave loads its 32 columns in 8 x 8 blocks, two per lane,
+// transposes them in registers and puts them into its own part of LDS.
+struct BackArgs {
+  const float* dout;      // [B][256], or null: dz_in
+  const uint16_t* dz_in;
+  uint16_t* dz_top;       // bfloat16 dout
+  const uint16_t* W[2];
+  const float* z[2];
+  uint16_t* dz[2];
+  int64_t B;
+};
+
+__global__ __launch_bounds__(512) void back_kernel(BackArgs g) {
+  __shared__ __align__(16) uint16_t wt[8][32 * kActStride];
+  __shared__ __align__(16) uint16_t act[kRowTile * kActStride];
+  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+  const int n0 = 32 * wave, fl = 4 * (lane >> 5), ml = lane & 31;
+  const int64_t r0 = int64_t(blockIdx.x) * kRowTile, m = r0 + ml;
+  const int kb = lane >> 2, nb = lane & 3;
+  u32x4_t v[2][8];
+  auto load = [&](const uint16_t* W) {
+#pragma unroll
+    for (int h = 0; h < 2; ++h)
+#pragma unroll
+      for (int i = 0; i < 8; ++i)
+        v[h][i] = *reinterpret_cast<const u32x4_t*>(
+            W + (8 * (kb + 16 * h) + i) * RRT_MLP_HIDDEN + n0 + 8 * nb);
+  };
+  load(g.W[0]);
+  {
+    const int row = threadIdx.x >> 4, c = (threadIdx.x & 15) * 8;
+    const int64_t at = (r0 + row) * RRT_MLP_HIDDEN + c;
+#pragma unroll
+    for (int i = 0; i < 2; ++i) {
+      u32x4_t t = {0u, 0u, 0u, 0u};
+      if (r0 + row < g.B) {
+        if (g.dout) {
+          const float4_u a = *reinterpret_cast<const float4_u*>(g.dout + at + 128 * i);
+          const float4_u b = *reinterpret_cast<const float4_u*>(g.dout + at + 128 * i + 4);
+          t = u32x4_t{bf16x2_bits(a[0], a[1]), bf16x2_bits(a[2], a[3]), bf16x2_bits(b[0], b[1]),
+                      bf16x2_bits(b[2], b[3])};
+          *reinterpret_cast<u32x4_t*>(g.dz_top + at + 128 * i) = t;
+        } else {
+          t = *reinterpret_cast<const u32x4_t*>(g.dz_in + at + 128 * i);
+        }
+      }
+      *reinterpret_cast<u32x4_t*>(act + row * kActStride + c + 128 * i) = t;
+    }
+  }
+  __syncthreads();
+  const int64_t mz = m < g.B ? m : g.B - 1;
+  uint16_t* own = wt[wave];
+#pragma unroll
+  for (int t = 0; t < 2; ++t) {
+    float4 z[4];
+#pragma unroll
+    for (int q = 0; q < 4; ++q)
+      z[q] = *reinterpret_cast<const float4*>(g.z[t] + mz * RRT_MLP_HIDDEN + n0 + 8 * q + fl);
+#pragma unroll
+    for (int h = 0; h < 2; ++h)
+#pragma unroll
+      for (int j = 0; j < 8; ++j) {
+        u32x4_t x;
+#pragma unroll
+        for (int p = 0; p < 4; ++p)
+          x[p] = __builtin_amdgcn_perm(v[h][2 * p + 1][j / 2], v[h][2 * p][j / 2],
+                                       (j & 1) ? 0x07060302u : 0x05040100u);
+        *reinterpret_cast<u32x4_t*>(own + (8 * nb + j) * kActStride + 8 * (kb + 16 * h)) = x;
+      }
+    wave_lds_order();
+    if (t == 0) load(g.W[1]);
+    const uint16_t* wr = own + ml * kActStride + 8 * (lane >> 5);
+    const uint16_t* ar = act + ml * kActStride + 8 * (lane >> 5);
+    float16_t acc = {};
+#pragma unroll
+    for (int s = 0; s < RRT_MLP_HIDDEN / 16; ++s)
+      acc = __builtin_amdgcn_mfma_f32_32x32x16_bf16(
+          *reinterpret_cast<const bf16x8_t*>(wr + 16 * s),
+          *reinterpret_cast<const bf16x8_t*>(ar + 16 * s), acc, 0, 0, 0);
+    __syncthreads();  // every wave has read its operands: the buffers are free
+#pragma unroll
+    for (int q = 0; q < 4; ++q) {
+      uint2 o;
+      o.x = bf16x2_bits(acc[4 * q] * gelu_grad_f(z[q].x), acc[4 * q + 1] * gelu_grad_f(z[q].y));
+      o.y = bf16x2_bits(acc[4 * q + 2] * gelu_grad_f(z[q].z), acc[4 * q + 3] * gelu_grad_f(z[q].w));
+      *reinterpret_cast<uint2*>(act + ml * kActStride + n0 + 8 * q + fl) = o;
+    }
+    __syncthreads();
+    store_rows(act, r0, g.B, g.dz[t]);
+  }
+}
+
 // dout = 2 (out - target) / count; loss += sum (out - target)^2 / count (FP64).
 // A grid-stride loop over at most 256 workgroups: one FP64 atomic each.
 __global__ void mse_kernel(const float* __restrict__ out, const float* __restrict__ tgt,
@@ -675,22 +709,6 @@ __global__ void adam_kernel(float* __restrict__ p, uint16_t* __restrict__ p_bf16
   const float pt = p[t] - lr * (mt / c1) / (sqrtf(vt / c2) + eps);
   p[t] = pt;
   if (p_bf16) p_bf16[t] = bf16_bits(pt);
-}
-
-// 128 x 128 tiles when they still give every CU a workgroup, else 64 x 64.
-template <bool BT, int EPI>
-int gemm(const GemmArgs& a, hipStream_t s) {
-  // the contiguous dimension of each stored operand must allow 16-byte loads
-  if (a.K % 8 || (BT ? a.K : a.N) % 8) return RRT_ERR_UNSUPPORTED;
-  const int64_t big = int64_t((a.N + 127) / 128) * ((a.M + 127) / 128);
-  if (big >= 512) {
-    const dim3 grid(unsigned((a.N + 127) / 128), unsigned((a.M + 127) / 128));
-    hipLaunchKernelGGL((gemm_bf16<BT, EPI, 2>), grid, dim3(256), 0, s, a);
-  } else {
-    const dim3 grid(unsigned((a.N + 63) / 64), unsigned((a.M + 63) / 64));
-    hipLaunchKernelGGL((gemm_bf16<BT, EPI, 1>), grid, dim3(256), 0, s, a);
-  }
-  return check_launch("gemm_bf16");
 }
 
 inline unsigned blocks(int64_t n, int per = 256) { return unsigned((n + per - 1) / per); }
@@ -796,55 +814,47 @@ int launch_mlp_encode(const float* in, int64_t B, void* out, hipStream_t s) {
 
 int launch_mlp_forward(const void* w, const float* b, const void* x, int64_t B, float* out,
                        void* ws, hipStream_t s) {
-  const uint16_t* W = static_cast<const uint16_t*>(w);
   MlpWs k = carve(ws, B);
-  const uint16_t* a_in = static_cast<const uint16_t*>(x);
-  for (int l = 0; l < RRT_MLP_WEIGHTS; ++l) {
-    GemmArgs g = {};
-    g.A = a_in;
-    g.B = W + mlp_weight_offset(l);
-    g.M = int(B);
-    g.N = kOut[l];
-    g.K = kIn[l];
-    g.bias = b + mlp_bias_offset(l);
-    int st;
-    if (l < RRT_MLP_WEIGHTS - 1) {
-      g.out_bf16 = k.a[l];
-      g.out_f32 = k.z[l];
-      st = gemm<true, kEpiHidden>(g, s);
-      a_in = k.a[l];
-    } else {
-      g.out_f32 = out;
-      st = gemm<true, kEpiOutput>(g, s);
-    }
-    if (st) return st;
+  ForwardArgs f = {};
+  f.x = static_cast<const uint16_t*>(x);
+  f.W = static_cast<const uint16_t*>(w);
+  f.bias = b;
+  f.B = B;
+  for (int l = 0; l < 4; ++l) {
+    f.z[l] = k.z[l];
+    f.a[l] = k.a[l];
   }
-  return RRT_OK;
+  f.out = out;
+  hipLaunchKernelGGL(forward_kernel, dim3(unsigned((B + kRowTile - 1) / kRowTile)), dim3(512), 0, s, f);
+  return check_launch("forward");
 }
 
 int launch_mlp_backward(const void* w, const void* x, int64_t B, const float* dout, float* dw,
                         float* db, void* ws, hipStream_t s) {
   const uint16_t* W = static_cast<const uint16_t*>(w);
   MlpWs k = carve(ws, B);
-  const int64_t nout = B * RRT_MLP_OUT;
-  hipLaunchKernelGGL(to_bf16_kernel, dim3(blocks(nout)), dim3(256), 0, s, dout, k.dout_bf16, nout);
-  int st = check_launch("to_bf16");
-  if (st) return st;
   // dz_{l-1} = (dz_l W_l) * gelu'(z_{l-1}): the buffers of dz hold three layers'
   // at a time, so the gradients are taken in two launches
   const uint16_t* dz[RRT_MLP_WEIGHTS];
   dz[4] = k.dout_bf16;
-  auto step_back = [&](int l, uint16_t* next) {
-    GemmArgs gx = {};
-    gx.A = dz[l];                        // [B][out]
-    gx.B = W + mlp_weight_offset(l);     // [out][in] = [K][N]
-    gx.M = int(B);
-    gx.N = kIn[l];
-    gx.K = kOut[l];
-    gx.zprev = k.z[l - 1];
-    gx.out_bf16 = next;
-    dz[l - 1] = next;
-    return gemm<false, kEpiGeluGrad>(gx, s);
+  // layers l and l - 1
+  auto two_back = [&](int l, uint16_t* next, uint16_t* last) {
+    BackArgs a = {};
+    if (l == RRT_MLP_WEIGHTS - 1) {
+      a.dout = dout;
+      a.dz_top = k.dout_bf16;
+    } else {
+      a.dz_in = dz[l];
+    }
+    for (int i = 0; i < 2; ++i) {
+      a.W[i] = W + mlp_weight_offset(l - i);
+      a.z[i] = k.z[l - 1 - i];
+    }
+    dz[l - 1] = a.dz[0] = next;
+    dz[l - 2] = a.dz[1] = last;
+    a.B = B;
+    hipLaunchKernelGGL(back_kernel, dim3(unsigned((B + kRowTile - 1) / kRowTile)), dim3(512), 0, s, a);
+    return check_launch("back");
   };
   auto grads = [&](int top, int layers) {
     GradArgs g = {};
@@ -856,11 +866,10 @@ int launch_mlp_backward(const void* w, const void* x, int64_t B, const float* do
     }
     return launch_grads(g, layers, s);
   };
-  if ((st = step_back(4, k.dz[0]))) return st;
-  if ((st = step_back(3, k.dz[1]))) return st;
+  int st;
+  if ((st = two_back(4, k.dz[0], k.dz[1]))) return st;
   if ((st = grads(4, 3))) return st;
-  if ((st = step_back(2, k.dout_bf16))) return st;
-  if ((st = step_back(1, k.dz[0]))) return st;
+  if ((st = two_back(2, k.dout_bf16, k.dz[0]))) return st;
   return grads(1, 2);
 }
 
