@@ -39,19 +39,28 @@ def s11_words(nnz):
 
 
 def _stream():
-    return ctypes.c_void_p(torch.cuda.current_stream().cuda_stream)
+    # the current stream of the current device, without the Stream object that
+    # torch.cuda.current_stream() makes for it (host time is what the smallest
+    # calls take)
+    return ctypes.c_void_p(torch._C._cuda_getCurrentRawStream(torch.cuda.current_device()))
 
 
-def _dev(t, name, dtype=None):
+def _address(t, name, dtype=None):
     if not isinstance(t, torch.Tensor):
         raise TypeError(f"{name} must be a torch.Tensor")
     if not t.is_cuda:
         raise ValueError(f"{name} must be a device tensor")
     if not t.is_contiguous():
         raise ValueError(f"{name} must be contiguous")
-    if dtype is not None and t.dtype not in (dtype if isinstance(dtype, tuple) else (dtype,)):
+    if dtype is not None and t.dtype is not dtype and not (isinstance(dtype, tuple) and t.dtype in dtype):
         raise TypeError(f"{name} has dtype {t.dtype}, expected {dtype}")
-    return ctypes.c_void_p(t.data_ptr())
+    # a structure's pointer field reads back as None where it is null, and so
+    # does this for an empty tensor
+    return t.data_ptr() or None
+
+
+def _dev(t, name, dtype=None):
+    return ctypes.c_void_p(_address(t, name, dtype))
 
 
 def _numel(t, name, count):
@@ -127,8 +136,12 @@ def _light_shapes(light_idx, light_val):
                          f"{tuple(light_val.shape)} must be the same 1-D shape")
 
 
+def _address_or_null(t, name, dtype=None):
+    return None if t is None else _address(t, name, dtype)
+
+
 def _ptr_or_null(t, name, dtype=None):
-    return ctypes.c_void_p(0) if t is None else _dev(t, name, dtype)
+    return ctypes.c_void_p(_address_or_null(t, name, dtype))
 
 
 def _workspace(nbytes, device):
@@ -231,23 +244,21 @@ def _descriptors(n, light_idx, light_val, vert_rot, t_idx, t_val, frame_rot, blo
     nframes = 1 if frame_rot is None else _rotations(frame_rot, "frame_rot")
     _numel(out, "out", nframes * nvert)
     nnz = _transport_shapes(nvert, t_idx, t_val, block_scale, cluster, brdf, material, order, n)
-    L = Light(n, light_idx.numel(), _dev(light_idx, "light_idx", torch.int32).value,
-              _dev(light_val, "light_val", (torch.float32, torch.float16)).value,
+    L = Light(n, light_idx.numel(), _address(light_idx, "light_idx", torch.int32),
+              _address(light_val, "light_val", (torch.float32, torch.float16)),
               _DTYPES[light_val.dtype])
-    nframes = 1 if frame_rot is None else frame_rot.shape[0]
-    R = Rotations(nframes, _ptr_or_null(frame_rot, "frame_rot", torch.float32).value,
-                  _dev(vert_rot, "vert_rot", torch.float32).value)
-    nvert = vert_rot.shape[0]
-    T = Transport(nvert, nnz, _ptr_or_null(t_idx, "transport_idx", torch.int32).value,
-                  _dev(t_val, "transport_val", _TRANSPORT_DTYPES).value,
+    R = Rotations(nframes, _address_or_null(frame_rot, "frame_rot", torch.float32),
+                  _address(vert_rot, "vert_rot", torch.float32))
+    T = Transport(nvert, nnz, _address_or_null(t_idx, "transport_idx", torch.int32),
+                  _address(t_val, "transport_val", _TRANSPORT_DTYPES),
                   _DTYPES[t_val.dtype],
-                  _ptr_or_null(block_scale, "block_scale", torch.float32).value,
-                  _ptr_or_null(cluster, "cluster", torch.int32).value,
+                  _address_or_null(block_scale, "block_scale", torch.float32),
+                  _address_or_null(cluster, "cluster", torch.int32),
                   0 if cluster is None else t_idx.shape[0],
-                  _ptr_or_null(brdf, "brdf", torch.float32).value,
-                  _ptr_or_null(material, "material", torch.int32).value,
+                  _address_or_null(brdf, "brdf", torch.float32),
+                  _address_or_null(material, "material", torch.int32),
                   0 if brdf is None else brdf.shape[0],
-                  _ptr_or_null(order, "order", torch.int32).value)
+                  _address_or_null(order, "order", torch.int32))
     return L, R, T
 
 
