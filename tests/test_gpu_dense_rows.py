@@ -90,3 +90,16 @@ def test_latlong_dense_rows(rrt, H):
     out = rrt.relight_latlong(H, dev(li), dev(lv), dev(elev), dev(shift), None, dev(rows))
     check_frames(out.cpu().numpy()[None], relight_latlong(li, lv, H, elev, shift, None, rows,
                                                           return_scale=True), rel_l2=False)
+
+
+@pytest.mark.parametrize("n,V", [(4, 5120), (4, 5121), (16, 5121)])
+@pytest.mark.parametrize("compensated", [False, True])
+def test_faces_among_waves(rrt, n, V, compensated):
+    """Up to 5,120 waves a vertex's faces are divided among six waves, above
+    one wave takes them all."""
+    from oracle.relight import relight
+    li, lv, rot, _, rows = scene(n, V, 1, n + V)
+    out = rrt.relight(n, dev(li), dev(lv), dev(rot), None, dev(rows), compensated=compensated)
+    for at in (slice(0, 40), slice(V - 40, V)):
+        ref = relight(li, lv, n, rot[at], None, None, rows[at], return_scale=True)
+        check_frames(out[:, at].cpu().numpy(), ref, rel_l2=False)
