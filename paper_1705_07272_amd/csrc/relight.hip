@@ -11,7 +11,8 @@
 // source map reconstructed once per lighting.  The coarser levels are the
 // paper's recursive averaging, done as in-place 2x2 butterflies.
 //
-// Work decomposition (one wave per vertex, all frames; no workgroup barrier):
+// Work decomposition (one wave per vertex, all frames, or up to a round of waves
+// several per vertex, whose results are added at the end):
 //   * the faces touched by the vertex's transport row are processed, each as
 //     G x G blocks of Q x Q texels (Q = min(n, 32));
 //   * per block, a lane gathers one texel of each 8 x 8 patch (a compact patch
@@ -35,6 +36,8 @@
 // material (Sec. III, eq:tripleSum), and the longitude-latitude map with its
 // elevation rotation and exact azimuth shifts (Sec. V.A).
 #include <hip/hip_fp16.h>
+
+#include <algorithm>
 
 #include "geometry.h"
 #include "rrt_internal.h"
@@ -213,7 +216,7 @@ struct RelightParams {
   const int32_t* order;     // [V] processing order, or NULL
   const float* ll_grid;     // lat-long: the rule's binary32 tables (7 H floats)
   int ll_tab_off;           // lat-long: byte offset of the tables in LDS
-  int lds_wave;             // dense rows: bytes of LDS per wave of a workgroup
+  int lds_wave;             // bytes of LDS per wave of a workgroup
 };
 
 // Correctly rounded binary32 square root of x, for x >= 2^-96 (the lat-long
@@ -751,10 +754,17 @@ __device__ __forceinline__ int classify(int idx, int logn, int G, unsigned faces
 // slower, so it keeps its 5.
 // LOGN: log2 n where the block is gathered in quarters (cube map, exact
 // rotation, n >= 32) and for the lat-long map, else 0 and n is a parameter.
-// DENSE: rows hold every coefficient in order (no index rows, no list).
-template <int Q, bool CHAIN, bool BRDF, bool LL, int LOGN, bool DENSE>
-__global__ __launch_bounds__((DENSE ? 6 : 1) * kThreads, CHAIN || LOGN ? 5 : 1) void relight_kernel(
+// MODE: kOneWave, one wave per vertex; kManyWaves, a vertex's blocks in turn
+// among the waves of a workgroup, each with a list of its own; kDense, rows
+// that hold every coefficient in order (no index rows, no list), whose faces
+// may be divided among six waves.
+enum Mode { kOneWave = 0, kManyWaves = 1, kDense = 2 };
+constexpr int kMostWaves = 8;
+
+template <int Q, bool CHAIN, bool BRDF, bool LL, int LOGN, int MODE>
+__global__ __launch_bounds__((MODE ? kMostWaves : 1) * kThreads, CHAIN || LOGN ? 5 : 1) void relight_kernel(
     RelightParams p) {
+  constexpr bool DENSE = MODE == kDense;
   constexpr int NF = LL ? 2 : 6;  // faces (squares) of the map
   constexpr bool QUARTERS = LOGN > 0 && !LL;
   // Blocks holding no listed entry of their own only feed the levels above
@@ -772,12 +782,11 @@ __global__ __launch_bounds__((DENSE ? 6 : 1) * kThreads, CHAIN || LOGN ? 5 : 1) 
   constexpr int IMG = Q * STRIDE;
   extern __shared__ __align__(16) unsigned char dyn_lds[];
 
-  // a dense row's faces may be divided among the workgroup's waves, each with
-  // an LDS part of its own
-  const int wave = DENSE ? __builtin_amdgcn_readfirstlane(int(threadIdx.x) >> 6) : 0;
-  const int waves = DENSE ? int(blockDim.x) >> 6 : 1;
-  unsigned char* const wave_lds = dyn_lds + (DENSE ? wave * p.lds_wave : 0);
-  const int lane = DENSE ? int(threadIdx.x) & (kThreads - 1) : int(threadIdx.x);
+  // the waves of a workgroup have an LDS part of their own each
+  const int wave = MODE ? __builtin_amdgcn_readfirstlane(int(threadIdx.x) >> 6) : 0;
+  const int waves = MODE ? int(blockDim.x) >> 6 : 1;
+  unsigned char* const wave_lds = dyn_lds + (MODE ? wave * p.lds_wave : 0);
+  const int lane = MODE ? int(threadIdx.x) & (kThreads - 1) : int(threadIdx.x);
   const int64_t v = p.order ? int64_t(p.order[blockIdx.x]) : int64_t(blockIdx.x);
   if (v < 0 || v >= p.nvert) return;  // not a permutation entry: skipped (uniform)
   const int logn = LOGN ? LOGN : p.logn;
@@ -996,6 +1005,9 @@ __global__ __launch_bounds__((DENSE ? 6 : 1) * kThreads, CHAIN || LOGN ? 5 : 1) 
               // 16 blocks at a time, each lane looks at one of their quarters
               if ((kb & 15) == 0)
                 quarters = quarter_face<LOGN>(ax, kb + (lane >> 2), lane & 3, rot_ok);
+            }
+            if constexpr (MODE == kManyWaves) {
+              if ((gi & (waves - 1)) != wave) continue;
             }
             // entries past the list may fall in any block: then every block is full
             bool full = true;
@@ -1255,7 +1267,7 @@ __global__ __launch_bounds__((DENSE ? 6 : 1) * kThreads, CHAIN || LOGN ? 5 : 1) 
 #pragma unroll
     for (int o = 32; o >= 1; o >>= 1) accw += __shfl_xor(accw, o, 64);
     accw += comp ? double(acc.s) + double(acc.c) : double(acc.s);
-    if (DENSE && waves > 1) {
+    if (MODE && waves > 1) {
       double* part = reinterpret_cast<double*>(dyn_lds + waves * p.lds_wave);
       if (lane == 0) part[wave] = accw;
       __syncthreads();
@@ -1435,19 +1447,40 @@ int launch_q(const RelightParams& prm_in, int64_t nvert, hipStream_t s) {
   if (split > prm.nframes) split = prm.nframes;
   if (split > 65535) split = 65535;
   const dim3 grid(unsigned(nvert), static_cast<unsigned>(split));
-  // Each face of a dense row has the same work: up to a round of waves (one of
-  // them per vertex leaves the chip idle and waiting for its own loads) the
-  // faces are divided among six.  1,000 vertices at n = 32: relight 49 -> 29 us,
-  // the whole step 69.5 -> 45.1.
+  // Up to a round of waves (one of them per vertex leaves the chip idle and
+  // waiting for its own loads) a vertex is divided among the waves of a
+  // workgroup: a dense row by faces, which have the same work; other rows by
+  // blocks, at most as many waves as one face (both squares) has blocks, whatever
+  // the factors: a triple product with ones is the double product bit for bit.
+  // Every wave lists the row for itself, which only pays while the chip is not
+  // full (of registers; of LDS where every wave copies the lat-long tables, too:
+  // 2,560 vertices at H = 256 took 412 us in two waves each, 373 in one, while
+  // 1,280 rows of 600 at n = 128, whose lists fill the LDS, gain: 131 -> 82).
+  // A call with 300 vertices, one wave each and eight: n = 128 88 -> 33 us, n = 256
+  // 294 -> 104, triple product at n = 128 146 -> 54, lat-long at H = 128 86 -> 41,
+  // chain rule at n = 128 71 -> 35; 2,560 vertices at n = 128, one and two: 90 -> 61.
+  // 1,000 dense rows at n = 32: relight 49 -> 29 us, the whole step 69.5 -> 45.1.
   prm.lds_wave = int((lds + 15) & ~size_t(15));
-  int waves = nvert * split <= kRoundWaves ? (LL ? 2 : 6) : 1;
-  if (size_t(waves) * prm.lds_wave + 6 * sizeof(double) > 64 * 1024) waves = 1;
-  if (prm.tidx) {
-    hipLaunchKernelGGL((relight_kernel<Q, CHAIN, BRDF, LL, LOGN, false>), grid, dim3(kThreads), lds, s,
-                       prm);
+  const int64_t round =
+      LL ? std::min(kRoundWaves, 256 * (int64_t(160 * 1024) / prm.lds_wave)) : kRoundWaves;
+  auto fits = [&](int waves) { return size_t(waves) * prm.lds_wave + 64 <= 64 * 1024; };
+  int waves = 1;
+  if (!prm.tidx) {
+    if (nvert * split <= round && fits(LL ? 2 : 6)) waves = LL ? 2 : 6;
+    hipLaunchKernelGGL((relight_kernel<Q, CHAIN, BRDF, LL, LOGN, kDense>), grid,
+                       dim3(waves * kThreads), size_t(waves) * prm.lds_wave + 64, s, prm);
+    return check_launch("relight_kernel");
+  }
+  const int blocks = G * G * (LL ? 2 : 1);
+  while (waves < kMostWaves && 2 * waves <= blocks && nvert * split * 2 * waves <= round &&
+         fits(2 * waves))
+    waves *= 2;
+  if (waves > 1) {
+    hipLaunchKernelGGL((relight_kernel<Q, CHAIN, BRDF, LL, LOGN, kManyWaves>), grid,
+                       dim3(waves * kThreads), size_t(waves) * prm.lds_wave + 64, s, prm);
   } else {
-    hipLaunchKernelGGL((relight_kernel<Q, CHAIN, BRDF, LL, LOGN, true>), grid, dim3(waves * kThreads),
-                       size_t(waves) * prm.lds_wave + 6 * sizeof(double), s, prm);
+    hipLaunchKernelGGL((relight_kernel<Q, CHAIN, BRDF, LL, LOGN, kOneWave>), grid, dim3(kThreads), lds,
+                       s, prm);
   }
   return check_launch("relight_kernel");
 }
