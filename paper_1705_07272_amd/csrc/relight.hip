@@ -751,7 +751,8 @@ __device__ __forceinline__ int classify(int idx, int logn, int G, unsigned faces
 // The chain-rule variant is held to 5 waves per SIMD (96 VGPRs, a few
 // spilled): 0.430 -> 0.411 ms on the benchmark launch against 4 waves
 // unspilled (0.370 now); the lat-long variant held to 6 waves spills more and runs
-// slower, so it keeps its 5.
+// slower, so it keeps its 5.  Sizes below 32 are held to 6 (80 VGPRs): 24,510
+// vertices x 12 frames at n = 16 680 -> 556 us against 4 waves.
 // LOGN: log2 n where the block is gathered in quarters (cube map, exact
 // rotation, n >= 32) and for the lat-long map, else 0 and n is a parameter.
 // MODE: kOneWave, one wave per vertex; kManyWaves, a vertex's blocks in turn
@@ -762,7 +763,7 @@ enum Mode { kOneWave = 0, kManyWaves = 1, kDense = 2 };
 constexpr int kMostWaves = 8;
 
 template <int Q, bool CHAIN, bool BRDF, bool LL, int LOGN, int MODE>
-__global__ __launch_bounds__((MODE ? kMostWaves : 1) * kThreads, CHAIN || LOGN ? 5 : 1) void relight_kernel(
+__global__ __launch_bounds__((MODE ? kMostWaves : 1) * kThreads, CHAIN || LOGN ? 5 : 6) void relight_kernel(
     RelightParams p) {
   constexpr bool DENSE = MODE == kDense;
   constexpr int NF = LL ? 2 : 6;  // faces (squares) of the map
@@ -1442,8 +1443,15 @@ int launch_q(const RelightParams& prm_in, int64_t nvert, hipStream_t s) {
   // of them, or leave the last round of the chip (kRoundWaves at a time) mostly
   // empty: the frames are divided until there are eight rounds.
   // 12,500 vertices x 64 frames at n = 128 (2.4 rounds undivided): 8.07 -> 7.21
-  // ms (6.82 now); the list is then built once for 16 frames.
+  // ms (6.82 now); the list is then built once for 16 frames.  Listing an entry
+  // takes about as long as 14 texels, so past the chip's first round a wave keeps
+  // frames of 64 texels per listed entry: 24,510 vertices x 12 frames at n = 16 with 238
+  // entries took 709 us in two waves each, 680 in one.
   int64_t split = nvert > 0 ? (8 * kRoundWaves + nvert - 1) / nvert : 1;
+  if (prm.listed > 0)
+    split = std::min(split, (int64_t(prm.nframes) << (2 * prm.logn)) / (64 * int64_t(prm.listed)));
+  if (nvert > 0) split = std::max(split, kRoundWaves / nvert);
+  if (split < 1) split = 1;
   if (split > prm.nframes) split = prm.nframes;
   if (split > 65535) split = 65535;
   const dim3 grid(unsigned(nvert), static_cast<unsigned>(split));
