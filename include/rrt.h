@@ -158,7 +158,8 @@ typedef struct {
   int n;                 /* face side, 2 <= n <= 1024, power of two */
   int k;                 /* kept lighting coefficients, 1 <= k <= 6 n^2 */
   const int32_t* idx;    /* [k] flat coefficient indices (any order; out-of-range
-                            entries ignored; duplicates: one of them wins) */
+                            entries ignored; duplicates: one of them wins,
+                            the same one in the whole map) */
   const void* val;       /* [k] values, dtype RRT_F32 or RRT_F16 */
   int dtype;             /* rrt_dtype of val (the source map reconstructed
                             from the coefficients is binary32 either way) */

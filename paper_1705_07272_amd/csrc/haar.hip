@@ -239,12 +239,17 @@ __global__ __launch_bounds__(kThreads) void haar_inv_tiles(const float* coef, co
 // (the whole square below) looks through all entries, keeps those of its own
 // levels and of its square's levels above the tiles in LDS and inverts both,
 // with the arithmetic of the kernels above (the same values bit for bit).
+// Of a repeated index the last entry counts: the tiles of a square each keep
+// the square's coarse coefficients and have to keep the same ones, so a cell
+// holds (entry number + 1, value) as 64 bits and takes the largest.
 //
 // What bounds it: latency (one round of loads, about 5 + log2 of the tiles
 // per side barriers); the staged way clears, scatters and inverts a dense map in
-// three or four launches.  12 KiB of LDS and few registers, to run beside relight waves.
-// The call that prepares a lighting of 1,024 entries at n = 128 takes 10.7 us
-// (host-bound) instead of 18.7, at n = 16 10.1 instead of 14.9.
+// three or four launches.  13 KiB of LDS and few registers, to run beside relight waves.
+// The call that prepares a lighting of 1,024 entries at n = 128 takes 7.2 us
+// (the host's time; 4.7 us in a graph) instead of 18.7, at n = 16 7.4 instead of
+// 14.9.  (Plain stores without the entry number: 4.6 us in a graph, 11.3 for
+// 16,384 entries at n = 64 against 11.5.)
 constexpr int kMapTile = 32;
 constexpr int kMapMost = 16384;                    // entries
 constexpr int64_t kMapEntries = int64_t(1) << 22;  // tiles x entries of the one-launch way
@@ -253,32 +258,37 @@ __global__ __launch_bounds__(kThreads) void source_map_kernel(const int32_t* __r
                                                               const void* __restrict__ val, int f16,
                                                               int k, int logn, int total,
                                                               float* __restrict__ pix, bool strips) {
-  extern __shared__ float lds[];
+  extern __shared__ __align__(8) float lds[];
   const int n = 1 << logn, Q = n < kMapTile ? n : kMapTile, logq = __builtin_ctz(Q);
   const int G = n >> logq;
-  float* tile = lds;               // Q x Q
-  float* coef = tile + Q * Q;      // the tile's own levels, Mallat layout
-  float* top = coef + Q * Q;       // G x G: the levels above, Mallat layout
-  float* sums = top + G * G;       // G x G: tile sums
+  // cells (value, entry number + 1): the tile's own levels, then G x G of the
+  // levels above, each in Mallat layout
+  unsigned long long* cells = reinterpret_cast<unsigned long long*>(lds);
+  const float* coef = lds;
+  const float* top = lds + 2 * Q * Q;
+  float* tile = lds + 2 * (Q * Q + G * G);  // Q x Q
+  float* sums = tile + Q * Q;               // G x G: tile sums
   const int blk = blockIdx.x;
   const int face = blk / (G * G), t = blk % (G * G);
   const int ty = t / G, tx = t % G;
-  for (int e = threadIdx.x; e < Q * Q + G * G; e += kThreads) coef[e] = 0.0f;
+  for (int e = threadIdx.x; e < Q * Q + G * G; e += kThreads) cells[e] = 0;
   __syncthreads();
   auto place = [&](int v, int i) {
     if (v < 0 || v >= total || (v >> (2 * logn)) != face) return;
     const int r = (v >> logn) & (n - 1), c = v & (n - 1);
-    float* to;
+    int to;
     if (r < G && c < G) {
-      to = top + r * G + c;
+      to = Q * Q + r * G + c;
     } else {
       const int q = 1 << (31 - __builtin_clz(unsigned(r | c)));  // blocks per side of the level
       const int nb = q >> (logn - logq);                         // those of a tile
       const int br = r & (q - 1), bc = c & (q - 1);
       if (br / nb != ty || bc / nb != tx) return;
-      to = coef + ((r >= q ? nb : 0) + (br & (nb - 1))) * Q + (c >= q ? nb : 0) + (bc & (nb - 1));
+      to = ((r >= q ? nb : 0) + (br & (nb - 1))) * Q + (c >= q ? nb : 0) + (bc & (nb - 1));
     }
-    *to = f16 ? __half2float(static_cast<const __half*>(val)[i]) : static_cast<const float*>(val)[i];
+    const float x = f16 ? __half2float(static_cast<const __half*>(val)[i])
+                        : static_cast<const float*>(val)[i];
+    atomicMax(cells + to, static_cast<unsigned long long>(i + 1) << 32 | __float_as_uint(x));
   };
   for (int i = threadIdx.x; i < k; i += 4 * kThreads) {
     int v[4];
@@ -288,15 +298,15 @@ __global__ __launch_bounds__(kThreads) void source_map_kernel(const int32_t* __r
     for (int j = 0; j < 4; ++j) place(v[j], i + j * kThreads);
   }
   __syncthreads();
-  // one inverse level of block side B of an S x S grid, in place
+  // one inverse level of block side B of an S x S grid, in place (m: cells)
   auto level = [&](float* g, const float* m, int S, int B) {
     const int nb = S / B, h = B >> 1;
     for (int e = threadIdx.x; e < nb * nb; e += kThreads) {
       const int br = e / nb, bc = e - br * nb;
       const int at = br * B * S + bc * B;
       float a, b, c, d;
-      inverse_butterfly(g[at], m[br * S + nb + bc], m[(nb + br) * S + bc],
-                        m[(nb + br) * S + nb + bc], a, b, c, d);
+      inverse_butterfly(g[at], m[2 * (br * S + nb + bc)], m[2 * ((nb + br) * S + bc)],
+                        m[2 * ((nb + br) * S + nb + bc)], a, b, c, d);
       g[at] = a;
       g[at + h] = b;
       g[at + h * S] = c;
@@ -335,7 +345,7 @@ int launch_source_map(const int32_t* idx, const void* val, int dtype, int k, int
   // the tiles' reads together are bounded, too.
   if (k <= kMapMost && grid * k <= kMapEntries) {
     if (n < 8) strips = false;
-    const size_t lds = (2 * size_t(Q) * Q + 2 * size_t(G) * G) * sizeof(float);
+    const size_t lds = 3 * (size_t(Q) * Q + size_t(G) * G) * sizeof(float);
     hipLaunchKernelGGL(source_map_kernel, dim3(unsigned(grid)), dim3(kThreads), lds, s, idx, val,
                        dtype == RRT_F16 ? 1 : 0, k, ilog2(n), squares * n * n, pix, strips);
     return check_launch("source_map");
