@@ -153,6 +153,9 @@ int rrt_haar_phase_shift(const float* coef_in, int n, const float* rot, int nrot
  * Relighting: radiance[f][v] = sum_k T_v[k] (W S(R_fv) W^T L)[k]
  * (Sec. III transfer-function inner product with the lighting rotated into
  * the vertex frame, Sec. V.A-V.C; rotate, recurse, integrate).
+ * A radiance is not finite where any entry of its row, one of value zero and
+ * entries that cancel among them, reaches an infinite or NaN texel of the
+ * source map; the others are as without those texels.
  * --------------------------------------------------------------------- */
 typedef struct {
   int n;                 /* face side, 2 <= n <= 1024, power of two */

@@ -413,7 +413,7 @@ int rrt_relight_latlong(const rrt_light* L, const rrt_latlong_rotations* R, cons
   a.n = L->n;
   a.flags = flags;
   a.out = radiance;
-  a.blocks = nullptr;
+  a.blocks = dense;
   a.brdf = nullptr;
   a.material = nullptr;
   a.nmaterials = 0;

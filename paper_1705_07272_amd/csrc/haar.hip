@@ -247,17 +247,28 @@ __global__ __launch_bounds__(kThreads) void haar_inv_tiles(const float* coef, co
 // per side barriers); the staged way clears, scatters and inverts a dense map in
 // three or four launches.  13 KiB of LDS and few registers, to run beside relight waves.
 // The call that prepares a lighting of 1,024 entries at n = 128 takes 7.2 us
-// (the host's time; 4.7 us in a graph) instead of 18.7, at n = 16 7.4 instead of
-// 14.9.  (Plain stores without the entry number: 4.6 us in a graph, 11.3 for
-// 16,384 entries at n = 64 against 11.5.)
+// (the host's time; 4.9 us in a graph) instead of 18.7, at n = 16 7.2 instead of
+// 14.9.  (Plain stores without the entry number and no flags: 4.6 us in a graph,
+// 11.3 for 16,384 entries at n = 64 against 11.6.)
 constexpr int kMapTile = 32;
 constexpr int kMapMost = 16384;                    // entries
 constexpr int64_t kMapEntries = int64_t(1) << 22;  // tiles x entries of the one-launch way
 
+// The flag of a tile, a byte from each of the workgroup's four waves (without a
+// barrier, which takes 0.6 us here).
+__device__ __forceinline__ void flag_tile(unsigned* flag, bool finite) {
+  static_assert(kThreads == 256, "four waves");
+  const bool all = __ballot(!finite) == 0;
+  const int wave = threadIdx.x >> 6;
+  if ((threadIdx.x & 63) == 0)
+    reinterpret_cast<uint8_t*>(flag)[wave] = all ? uint8_t(kMapFinite >> (8 * wave)) : uint8_t(0);
+}
+
 __global__ __launch_bounds__(kThreads) void source_map_kernel(const int32_t* __restrict__ idx,
                                                               const void* __restrict__ val, int f16,
                                                               int k, int logn, int total,
-                                                              float* __restrict__ pix, bool strips) {
+                                                              float* __restrict__ pix, bool strips,
+                                                              unsigned* __restrict__ flags) {
   extern __shared__ __align__(8) float lds[];
   const int n = 1 << logn, Q = n < kMapTile ? n : kMapTile, logq = __builtin_ctz(Q);
   const int G = n >> logq;
@@ -322,15 +333,27 @@ __global__ __launch_bounds__(kThreads) void source_map_kernel(const int32_t* __r
   for (int B = Q; B >= 2; B >>= 1) level(tile, coef, Q, B);
   float* dst = pix + (int64_t(face) << (2 * logn));
   const int row0 = ty * Q, col0 = tx * Q;
+  bool finite = true;
   for (int e = threadIdx.x; e < Q * Q; e += kThreads) {
-    if (strips) {
-      const int r = (e >> 3) & (Q - 1), c = ((e >> (logq + 3)) << 3) + (e & 7);
-      dst[int64_t((col0 + c) >> 3) * 8 * n + 8 * (row0 + r) + (c & 7)] = tile[r * Q + c];
-    } else {
-      const int r = e >> logq, c = e & (Q - 1);
-      dst[int64_t(row0 + r) * n + col0 + c] = tile[r * Q + c];
-    }
+    const int r = strips ? (e >> 3) & (Q - 1) : e >> logq;
+    const int c = strips ? ((e >> (logq + 3)) << 3) + (e & 7) : e & (Q - 1);
+    const float x = tile[r * Q + c];
+    finite = finite && __builtin_isfinite(x);
+    dst[strips ? int64_t((col0 + c) >> 3) * 8 * n + 8 * (row0 + r) + (c & 7)
+               : int64_t(row0 + r) * n + col0 + c] = x;
   }
+  flag_tile(flags + blk, finite);
+}
+
+// The flags of a finished map (its layout does not matter: a tile is that many
+// consecutive texels), in a launch after those that read dense: 2.7 us of the
+// 13.6 that 24,576 entries at n = 64 take.  grid: tiles.
+__global__ __launch_bounds__(kThreads) void map_flags_kernel(const float* __restrict__ pix, int texels,
+                                                             unsigned* __restrict__ flags) {
+  const float* t = pix + int64_t(blockIdx.x) * texels;
+  bool finite = true;
+  for (int e = threadIdx.x; e < texels; e += kThreads) finite = finite && __builtin_isfinite(t[e]);
+  flag_tile(flags + blockIdx.x, finite);
 }
 
 }  // namespace
@@ -347,11 +370,16 @@ int launch_source_map(const int32_t* idx, const void* val, int dtype, int k, int
     if (n < 8) strips = false;
     const size_t lds = 3 * (size_t(Q) * Q + size_t(G) * G) * sizeof(float);
     hipLaunchKernelGGL(source_map_kernel, dim3(unsigned(grid)), dim3(kThreads), lds, s, idx, val,
-                       dtype == RRT_F16 ? 1 : 0, k, ilog2(n), squares * n * n, pix, strips);
+                       dtype == RRT_F16 ? 1 : 0, k, ilog2(n), squares * n * n, pix, strips,
+                       reinterpret_cast<unsigned*>(dense));
     return check_launch("source_map");
   }
-  const int st = launch_scatter_light(idx, val, dtype, k, n, squares, dense, s);
-  return st ? st : launch_haar_inverse(dense, pix, n, squares, s, strips);
+  int st = launch_scatter_light(idx, val, dtype, k, n, squares, dense, s);
+  if (st) return st;
+  if ((st = launch_haar_inverse(dense, pix, n, squares, s, strips))) return st;
+  hipLaunchKernelGGL(map_flags_kernel, dim3(unsigned(grid)), dim3(kThreads), 0, s, pix, Q * Q,
+                     reinterpret_cast<unsigned*>(dense));
+  return check_launch("map_flags");
 }
 
 static int launch_forward(const float* pix, const float* rot, float* coef, int n, int64_t squares,

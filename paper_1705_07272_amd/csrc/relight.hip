@@ -188,6 +188,37 @@ __device__ __forceinline__ void tile_levels_d(double a, double b, double c, doub
   D = 0.5 * ((a - b) - (c - d));
 }
 
+// Weights of blocks while the entries of the levels above them are collected: -0
+// where there is none.  Where entries cancel (or are zero) the block adds nothing
+// to the result of a finite map, but an infinite or NaN texel of it does, since
+// the entries multiply it: such a weight is kReached, which is below every
+// rounding of a finite sum.  Weights up to kSkipped count as zero where the map
+// is known to be finite.
+constexpr double kReached = 0x1p-1000, kSkipped = 0x1p-900;
+__device__ __forceinline__ bool uncovered(double w) {
+  return __double_as_longlong(w) == __double_as_longlong(-0.0);
+}
+__device__ __forceinline__ double reached(double w) { return w == 0.0 ? kReached : w; }
+
+// This lane's share of the TILES flags of the source map is finite (they start
+// on 256 bytes; a multiple of four, or a face or square each).
+template <int TILES>
+__device__ __forceinline__ bool tiles_finite(const void* flags, int lane) {
+  unsigned bad = 0;
+  if constexpr (TILES % 4 == 0) {
+#pragma unroll
+    for (int k = 0; k < TILES; k += 4 * kThreads) {
+      if (k + 4 * lane < TILES) {
+        const uint4 w = static_cast<const uint4*>(flags)[k / 4 + lane];
+        bad |= (w.x ^ kMapFinite) | (w.y ^ kMapFinite) | (w.z ^ kMapFinite) | (w.w ^ kMapFinite);
+      }
+    }
+  } else if (lane < TILES) {
+    bad = static_cast<const unsigned*>(flags)[lane] ^ kMapFinite;
+  }
+  return bad == 0;
+}
+
 struct RelightParams {
   const float* src;       // source map (binary32)
   const float* vrot;
@@ -207,7 +238,8 @@ struct RelightParams {
   int comp;
   int listed;       // entries of each row listed in LDS: min(nnz, kMaxListed)
   int group_faces;  // faces whose block sums fit in LDS together
-  const float4* blocks;  // chain rule: (S, H, V, D) of every 2x2 source block
+  const float4* blocks;  // chain rule: (S, H, V, D) of every 2x2 source block;
+                         // else kMapFinite per tile of the source map (rrt_internal.h)
   const float* brdf;        // triple product: [nmat][6 n^2] texel factor, or NULL
   const int32_t* material;  // [V] row of brdf, or NULL (row 0)
   int nmat;
@@ -834,6 +866,12 @@ __global__ __launch_bounds__((MODE ? kMostWaves : 1) * kThreads, CHAIN || LOGN ?
   const int nnz = row_valid ? p.nnz : 0;
   const int listed = row_valid ? p.listed : 0;
 
+  // the source map's flags (where the chain rule has its blocks, which no flag
+  // looks like; a dense row reaches every texel of its faces)
+  [[maybe_unused]] bool finite = false;
+  if constexpr (!CHAIN && (!DENSE || BRDF))
+    finite = tiles_finite<NF << (LOGN > 5 ? 2 * (LOGN - 5) : 0)>(p.blocks, lane);
+
   // faces touched by this vertex's transport row (a dense row: all)
   unsigned m = 0;
   if constexpr (!DENSE) {
@@ -856,6 +894,7 @@ __global__ __launch_bounds__((MODE ? kMostWaves : 1) * kThreads, CHAIN || LOGN ?
                                                         // each TS x TS patch of the gather
   const uint64_t lanes_below = (uint64_t(1) << lane) - 1;
   int nfine = 0;
+  const double skipped = __ballot(!finite) == 0 ? kSkipped : 0.0;
 
   // lat-long: the rule's tables into LDS, this vertex's rotation
   LLTab tab = {};
@@ -908,7 +947,7 @@ __global__ __launch_bounds__((MODE ? kMostWaves : 1) * kThreads, CHAIN || LOGN ?
         nfine = 0;
         for (int k = lane; k < bwords; k += kThreads) bmask[k] = 0u;
         for (int k = lane; k < nfg * G2; k += kThreads) {
-          double w = 0.0;
+          double w = -0.0;  // no entry (any value that is added makes it another)
           if constexpr (DENSE) {
             // the face's scaling coefficient and the levels above the blocks
             const int at = k & (G2 - 1);
@@ -944,7 +983,7 @@ __global__ __launch_bounds__((MODE ? kMostWaves : 1) * kThreads, CHAIN || LOGN ?
               const int gb = (key >> kOffBits) & ((1 << kBlockBits) - 1);
               if (SUM_ONLY) atomicOr(&bmask[gb >> 5], 1u << (gb & 31));
             } else if (kind == 1) {
-              atomicAdd(&gW[key], double(vx[u]));
+              atomicAdd(&gW[key], double(vx[u]) + 0.0);
             }
             nfine += __popcll(bf);
           }
@@ -952,27 +991,33 @@ __global__ __launch_bounds__((MODE ? kMostWaves : 1) * kThreads, CHAIN || LOGN ?
         for (int e = listed + lane; !DENSE && e < nnz; e += kThreads) {
           int key = 0;
           if (classify<Q, NF>(idx_row[e], logn, G, faces, g0, FG, key) == 1)
-            atomicAdd(&gW[key], double(transport_value(p.tval, p.tscale, p.dtype, v, p.nnz, e)));
+            atomicAdd(&gW[key],
+                      double(transport_value(p.tval, p.tscale, p.dtype, v, p.nnz, e)) + 0.0);
         }
         wave_sync();
         // The inner product with the levels above the blocks is one with the
         // blocks' sums, whose weights are the inverse transform of those
-        // levels' entries (FP64, in place, the widest blocks first).
-        for (int r = 0; r < nfg; ++r) {
-          double* gf = gW + r * G2;
-          for (int Bg = G; Bg >= 2; Bg >>= 1) {
-            const int hg = Bg / 2, nb = G / Bg;
-            for (int t = lane; t < nb * nb; t += kThreads) {
-              const int at = (t / nb) * Bg * G + (t % nb) * Bg;
-              double A, B, C, D;
-              tile_levels_d(gf[at], gf[at + hg], gf[at + hg * G], gf[at + hg * G + hg], A, B, C, D);
-              gf[at] = A;
-              gf[at + hg] = B;
-              gf[at + hg * G] = C;
-              gf[at + hg * G + hg] = D;
-            }
-            wave_sync();
+        // levels' entries (FP64, in place, the widest blocks of all faces first).
+        for (int ln = 0; ln < logn - LOGQ; ++ln) {
+          const int Bg = G >> ln, hg = Bg / 2;  // 2^ln blocks of side Bg per face side
+          for (int t = lane; t < nfg << (2 * ln); t += kThreads) {
+            const int r = (t >> ln) & ((1 << ln) - 1), c = t & ((1 << ln) - 1);
+            double* g = gW + (t >> (2 * ln)) * G2 + r * Bg * G + c * Bg;
+            const double S = g[0], H = g[hg], V = g[hg * G], X = g[hg * G + hg];
+            if (!DENSE && uncovered(S) && uncovered(H) && uncovered(V) && uncovered(X)) continue;
+            double A, B, C, D;
+            tile_levels_d(S, H, V, X, A, B, C, D);
+            g[0] = DENSE ? A : reached(A);
+            g[hg] = DENSE ? B : reached(B);
+            g[hg * G] = DENSE ? C : reached(C);
+            g[hg * G + hg] = DENSE ? D : reached(D);
           }
+          wave_sync();
+        }
+        if constexpr (!DENSE && (Q < kBlock || LOGN == 5)) {
+          // one block per face: no level that marks a zero weight
+          if (lane < nfg && !uncovered(gW[lane])) gW[lane] = reached(gW[lane]);
+          wave_sync();
         }
       }
 
@@ -1018,13 +1063,12 @@ __global__ __launch_bounds__((MODE ? kMostWaves : 1) * kThreads, CHAIN || LOGN ?
             // weight of the block's sum (orthonormal scaling coefficient: 1 / Q)
             const double weight = gW[gi] * (1.0 / Q);
             // nothing reads a block of weight zero (the part of a lobe's square
-            // below the horizon, where the entries of the levels above cancel), so
-            // no texel of it reaches the result, an infinite one neither:
+            // below the horizon, where the entries of the levels above cancel):
             // 50,000 lat-long vertices at H = 128 2.01 -> 1.13 ms
-            if (!full && __ballot(weight != 0.0) == 0) continue;
+            if (!full && __ballot(!(fabs(weight) <= skipped)) == 0) continue;
             if constexpr (BRDF && QUARTERS) {
               // nor does one whose factor is zero everywhere (below the horizon)
-              // add to any coefficient
+              // add to any coefficient of a finite map
               const float* br = brdf_row + ((face * n + by * Q + ty * T) << logn) + bx * Q + tx * T;
               bool zero = true;
 #pragma unroll 1
@@ -1032,7 +1076,7 @@ __global__ __launch_bounds__((MODE ? kMostWaves : 1) * kThreads, CHAIN || LOGN ?
                 const uint4 w = *reinterpret_cast<const uint4*>(br + (rr << logn));
                 zero = __ballot((((w.x | w.y) | (w.z | w.w)) << 1) != 0u) == 0;
               }
-              if (zero) continue;
+              if (zero && skipped > 0.0) continue;
             }
             float lane_sum = 0.0f;  // sum-only blocks: this lane's gathered texels
             if constexpr (LL) {
@@ -1198,7 +1242,7 @@ __global__ __launch_bounds__((MODE ? kMostWaves : 1) * kThreads, CHAIN || LOGN ?
                 for (int cc = 0; cc < T; ++cc)
                   img[(ty * T + rr) * STRIDE + tx * T + cc] = g[rr][cc];
               s = g[0][0];
-              if (weight != 0.0) accw = fma(weight, double(s), accw);
+              if (!(fabs(weight) <= skipped)) accw = fma(weight, double(s), accw);
             }
             // levels above the tile, unscaled
             if constexpr (TS > 1) tile_level_above<1, TS, T, STRIDE>(s, img, lane, tx, ty, owns_tile);
@@ -1276,7 +1320,8 @@ __global__ __launch_bounds__((MODE ? kMostWaves : 1) * kThreads, CHAIN || LOGN ?
       for (int w = 1; w < waves; ++w) accw += part[w];
       __syncthreads();
     }
-    if (threadIdx.x == 0) p.out[int64_t(f) * p.out_stride + v] = float(accw);
+    // (+ 0: a sum below every float is +0, whatever its sign)
+    if (threadIdx.x == 0) p.out[int64_t(f) * p.out_stride + v] = float(accw) + 0.0f;
   }
 }
 

@@ -25,7 +25,7 @@ inline size_t align256(size_t x) { return (x + 255) & ~size_t(255); }
 
 // Workspace of relight: [dense staging 6n^2 float][source map 6n^2 float]
 // (a binary32 map for either lighting dtype); after prepare the staging area
-// holds the chain rule's 6 (n/2)^2 float4 blocks.
+// holds the source map's flags, or the chain rule's 6 (n/2)^2 float4 blocks.
 struct RelightWs {
   size_t dense_off, src_off, total;
 };
@@ -49,9 +49,15 @@ size_t topk_workspace_bytes(int64_t rows, int64_t len, int k);
 int launch_topk(const float* x, int64_t rows, int64_t len, int k, int32_t* idx, float* val,
                 void* ws, hipStream_t s);
 
+// Flag of a tile of the source map (32 x 32 consecutive texels, a whole square
+// below n = 32) without an infinite or NaN texel: a signalling NaN, which no
+// arithmetic returns, so no word of the chain rule's blocks is taken for it.
+constexpr unsigned kMapFinite = 0x7fa5a5a5u;
+
 // Source map pix of a sparse lighting: scatter and inverse transform, in one
 // launch where the map and the entries allow, else through the dense staging
-// map (haar.hip; squares and strips as below and above).
+// map (haar.hip; squares and strips as below and above).  Leaves kMapFinite or
+// 0 in dense[t] for every tile t of the map.
 int launch_source_map(const int32_t* idx, const void* val, int dtype, int k, int n, int squares,
                       float* dense, float* pix, hipStream_t s, bool strips);
 // Coefficient scatter into a zeroed dense map (relight.hip).
@@ -81,7 +87,8 @@ struct RelightLaunch {
   unsigned flags;
   float* out;               // [F][out_stride]: out[f * out_stride + v]
   int64_t out_stride = 0;   // 0: nvert
-  const void* blocks;       // chain rule: float4 (S, H, V, D) per 2x2 source block
+  const void* blocks;       // the staging area after prepare: float4 (S, H, V, D) per 2x2
+                            // source block (chain rule), else the source map's flags
   const float* brdf;        // triple product: [M][6 n^2] texel factor, or NULL
   const int32_t* material;  // [V] row of brdf, or NULL (row 0)
   int nmaterials;

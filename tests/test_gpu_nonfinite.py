@@ -1,0 +1,153 @@
+"""Infinite and NaN lighting: a radiance is finite exactly where the FP64
+checker's is, i.e. where no entry of the row (of whatever value, a zero and
+entries that cancel among them) reaches a texel that is not, for blocks whose
+weight or factor is zero as for the others.
+"""
+import numpy as np
+import pytest
+import torch
+
+from test_gpu_parity import dev
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.fixture(scope="module")
+def rrt():
+    if not torch.cuda.is_available():
+        pytest.skip("no GPU")
+    import paper_1705_07272_amd as m
+    return m
+
+
+def lighting(n, squares, g, k=500):
+    """k finite coefficients, an infinite one of the finest level and a NaN
+    that covers 4 x 4 texels."""
+    cells, h = squares * n * n, n // 2
+    at = g.choice(cells, k, replace=False)
+    bad = [n * n + (h + h // 3) * n + 5, (squares - 1) * n * n + (n // 4 + 1) * n + n // 8]
+    at = np.concatenate([at[~np.isin(at, bad)], bad])
+    val = g.normal(size=at.size)
+    val[-2:] = np.inf, np.nan
+    order = np.argsort(at)
+    return at[order].astype(np.int32), val[order].astype(np.float32)
+
+
+def transport(n, squares, V, g):
+    """Rows of one face: the scaling and vertical top coefficients with equal
+    values (the weights cancel over half of the face), one fine entry alone,
+    a coarse entry of value zero, one quarter of the face, and both fine and
+    coarse entries; -1 fills the rows up."""
+    idx, val = np.full((V, 12), -1), np.zeros((V, 12))
+    for v in range(V):
+        f = int(g.integers(0, squares)) * n * n
+        fine = f + (n - 1 - int(g.integers(0, n // 2))) * n + int(g.integers(0, n // 2))
+        kind = v % 5
+        if kind == 0:
+            row = [(f, 0.75), (f + n, 0.75 * (-1) ** (v // 5)), (fine, 0.5)]
+        elif kind == 1:
+            row = [(fine, 1.0)]
+        elif kind == 2:
+            row = [(f + 1, -0.0 if v % 2 else 0.0), (fine, 0.5)]
+        elif kind == 3:
+            row = [(f + 2 + n, 1.0), (f + 2 + n, -1.0)]
+        else:
+            row = [(f + 3, 1.0), (f + 2 * n, -0.5)] + [(fine - j * n, 0.1) for j in range(8)]
+        idx[v, :len(row)] = [i for i, _ in row]
+        val[v, :len(row)] = [x for _, x in row]
+    return idx.astype(np.int32), val.astype(np.float32)
+
+
+def finite(P, rotate, idx, val):
+    """Which rows have a finite sum of val * (transform of the rotated map)."""
+    from oracle.haar import haar_forward
+    out = []
+    with np.errstate(all="ignore"):
+        for v in range(len(idx)):
+            ok = idx[v] >= 0
+            out.append(np.isfinite(np.sum(val[v, ok] * haar_forward(rotate(P, v)).ravel()[idx[v, ok]])))
+    return np.array(out)
+
+
+def check(out, want):
+    out = np.isfinite(out.cpu().numpy()).reshape(-1)
+    assert want.any() and not want.all()
+    want = np.tile(want, out.size // want.size)
+    assert np.array_equal(out, want), np.flatnonzero(out != want)
+
+
+def scene(n, k=500, V=60):
+    from oracle.relight import reconstruct_lighting
+    from scenes.scene import random_rotations
+    g = np.random.default_rng(n + k)
+    li, lv = lighting(n, 6, g, k)
+    ti, tv = transport(n, 6, V, g)
+    with np.errstate(all="ignore"):
+        P = reconstruct_lighting(li, lv, n)
+    return g, li, lv, P, random_rotations(n, V), ti, tv
+
+
+@pytest.mark.parametrize("n", [8, 32, 64, 128])
+@pytest.mark.parametrize("repeat", [1, 90])          # several waves per vertex, and one
+def test_double_product(rrt, n, repeat):
+    from oracle.sphere import quantise_rotation, rotate_pixels
+    _, li, lv, P, rot, ti, tv = scene(n, 200 if n == 8 else 500)
+    want = finite(P, lambda m, v: rotate_pixels(m, quantise_rotation(rot[v], n)), ti, tv)
+    a = [np.concatenate([x] * repeat) for x in (rot, ti, tv)]
+    check(rrt.relight(n, dev(li), dev(lv), *map(dev, a)), want)
+
+
+@pytest.mark.parametrize("way", ["staged", "after_chain"])
+def test_prepared(rrt, way):
+    """A lighting of more entries than the one-launch source map takes, and a
+    workspace that holds the chain rule's blocks."""
+    from oracle.sphere import quantise_rotation, rotate_pixels
+    n = 64
+    _, li, lv, P, rot, ti, tv = scene(n, 17000 if way == "staged" else 500)
+    want = finite(P, lambda m, v: rotate_pixels(m, quantise_rotation(rot[v], n)), ti, tv)
+    light = rrt.prepare_lighting(n, dev(li), dev(lv), chain_rule=way == "after_chain")
+    light.chain_rule = False
+    check(rrt.relight_prepared(light, dev(rot), dev(ti), dev(tv)), want)
+
+
+def test_chain_rule(rrt):
+    from oracle.chain import chain_rotate
+    from oracle.sphere import quantise_rotation
+    n = 64
+    _, li, lv, P, rot, ti, tv = scene(n)
+    want = finite(P, lambda m, v: chain_rotate(m, quantise_rotation(rot[v], n)), ti, tv)
+    check(rrt.relight(n, dev(li), dev(lv), dev(rot), dev(ti), dev(tv), chain_rule=True), want)
+
+
+@pytest.mark.parametrize("n", [32, 64, 128])
+def test_triple_product(rrt, n):
+    """The factor is zero on one half of every face and on whole faces."""
+    from oracle.sphere import quantise_rotation, rotate_pixels
+    g, li, lv, P, rot, ti, tv = scene(n)
+    brdf = np.abs(g.normal(size=(2, 6, n, n))).astype(np.float32)
+    brdf[0, :, n // 2:], brdf[1, 2:] = 0.0, -0.0
+    mat = (np.arange(len(ti)) % 2).astype(np.int32)
+    want = finite(P, lambda m, v: rotate_pixels(m, quantise_rotation(rot[v], n)) *
+                  brdf[mat[v]].astype(np.float64), ti, tv)
+    check(rrt.relight(n, dev(li), dev(lv), dev(rot), dev(ti), dev(tv), brdf=dev(brdf),
+                      material=dev(mat)), want)
+
+
+@pytest.mark.parametrize("H", [8, 64, 128])
+@pytest.mark.parametrize("repeat", [1, 90])
+def test_latlong(rrt, H, repeat):
+    from oracle.haar import haar_inverse
+    from oracle.latlong import rotate
+    g, V = np.random.default_rng(H), 60
+    li, lv = lighting(H, 2, g, 60 if H == 8 else 500)
+    c = np.zeros(2 * H * H)
+    c[li] = lv
+    ti, tv = transport(H, 2, V, g)
+    b = np.arccos(g.uniform(-1, 1, V))
+    elev = np.stack([np.cos(b), np.sin(b)], 1).astype(np.float32)
+    shift = g.integers(0, 2 * H, (V, 2)).astype(np.int32)
+    with np.errstate(all="ignore"):
+        P = haar_inverse(c.reshape(2, H, H))
+    want = finite(P, lambda m, v: rotate(m, *elev[v], *shift[v]), ti, tv)
+    a = [np.concatenate([x] * repeat) for x in (elev, shift, ti, tv)]
+    check(rrt.relight_latlong(H, dev(li), dev(lv), *map(dev, a)), want)
