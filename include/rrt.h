@@ -156,6 +156,9 @@ int rrt_haar_phase_shift(const float* coef_in, int n, const float* rot, int nrot
  * A radiance is not finite where any entry of its row, one of value zero and
  * entries that cancel among them, reaches an infinite or NaN texel of the
  * source map; the others are as without those texels.
+ * A vertex and frame have the same radiance whatever else the call holds, but
+ * for the order of FP64 sums: where one lies within their rounding of the
+ * middle of two binary32 values the last place can differ.
  * --------------------------------------------------------------------- */
 typedef struct {
   int n;                 /* face side, 2 <= n <= 1024, power of two */

@@ -168,16 +168,6 @@ __device__ __forceinline__ void acc_add(Acc& a, float x, float y, bool comp) {
   a.s = t;
   a.c += e + pe;
 }
-
-__device__ __forceinline__ Acc acc_merge(Acc a, Acc b) {
-  const float t = a.s + b.s;
-  const float bb = t - a.s;
-  const float e = (a.s - (t - bb)) + (b.s - bb);
-  Acc r;
-  r.s = t;
-  r.c = (a.c + b.c) + e;
-  return r;
-}
 #pragma clang fp contract(fast)
 
 __device__ __forceinline__ void tile_levels_d(double a, double b, double c, double d, double& S,
@@ -934,8 +924,7 @@ __global__ __launch_bounds__((MODE ? kMostWaves : 1) * kThreads, CHAIN || LOGN ?
 #pragma unroll
       for (int k = 0; k < 9; ++k) rot_ok = rot_ok && R.m[k] <= one && R.m[k] >= -one;
     }
-    Acc acc = {0.0f, 0.0f};
-    double accw = 0.0;  // the part of the levels above the blocks
+    double accw = 0.0;  // this lane's part of the radiance
 
     for (int grp = 0; grp < ngroups; ++grp) {
       const int g0 = grp * FG;
@@ -1247,6 +1236,11 @@ __global__ __launch_bounds__((MODE ? kMostWaves : 1) * kThreads, CHAIN || LOGN ?
             // levels above the tile, unscaled
             if constexpr (TS > 1) tile_level_above<1, TS, T, STRIDE>(s, img, lane, tx, ty, owns_tile);
             wave_sync();
+            // The entries inside the block, in FP32 for each lane and block and in
+            // FP64 from there on: the division of blocks and frames among waves,
+            // which follows the numbers of vertices and frames, then moves sums
+            // only in FP64, far below the binary32 result.
+            Acc acc = {0.0f, 0.0f};
             // listed entries of this block: four keys per lane and LDS read
             for (int k0 = 4 * lane; k0 < nfine; k0 += 4 * kThreads) {
               const int4 keys = *reinterpret_cast<const int4*>(&lkey[k0]);
@@ -1290,6 +1284,7 @@ __global__ __launch_bounds__((MODE ? kMostWaves : 1) * kThreads, CHAIN || LOGN ?
                 acc_add(acc, transport_value(p.tval, p.tscale, p.dtype, v, p.nnz, e),
                         ldexpf(img[key & ((1 << kOffBits) - 1)], -(key >> kLogbShift)), comp);
             }
+            accw += comp ? double(acc.s) + double(acc.c) : double(acc.s);
             wave_sync();
           }
         }
@@ -1299,19 +1294,7 @@ __global__ __launch_bounds__((MODE ? kMostWaves : 1) * kThreads, CHAIN || LOGN ?
 
     // reduction across the wave
 #pragma unroll
-    for (int o = 32; o >= 1; o >>= 1) {
-      Acc other;
-      other.s = __shfl_xor(acc.s, o, 64);
-      other.c = __shfl_xor(acc.c, o, 64);
-      if (comp) {
-        acc = acc_merge(acc, other);
-      } else {
-        acc.s += other.s;
-      }
-    }
-#pragma unroll
     for (int o = 32; o >= 1; o >>= 1) accw += __shfl_xor(accw, o, 64);
-    accw += comp ? double(acc.s) + double(acc.c) : double(acc.s);
     if (MODE && waves > 1) {
       double* part = reinterpret_cast<double*>(dyn_lds + waves * p.lds_wave);
       if (lane == 0) part[wave] = accw;
