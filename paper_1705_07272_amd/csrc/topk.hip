@@ -364,10 +364,11 @@ __global__ __launch_bounds__(kThreads) void topk_select(const float* __restrict_
 // k = len: every value in place.
 __global__ void topk_all(const float* __restrict__ x, int64_t total, int64_t len,
                          int32_t* __restrict__ oidx, float* __restrict__ oval) {
-  const int64_t i = int64_t(blockIdx.x) * blockDim.x + threadIdx.x;
-  if (i >= total) return;
-  oidx[i] = int32_t(i % len);
-  oval[i] = x[i];
+  const int64_t step = int64_t(gridDim.x) * blockDim.x;
+  for (int64_t i = int64_t(blockIdx.x) * blockDim.x + threadIdx.x; i < total; i += step) {
+    oidx[i] = int32_t(i % len);
+    oval[i] = x[i];
+  }
 }
 
 // ---------------------------------------------------------------------------
@@ -739,9 +740,12 @@ int launch_topk(const float* x, int64_t rows, int64_t len, int k, int32_t* idx, 
                 void* ws, hipStream_t s) {
   if (rows == 0 || k == 0) return RRT_OK;
   const int64_t total = rows * len;
-  if (int64_t(k) == len && total <= int64_t(0x7fffffff) * 256) {
-    hipLaunchKernelGGL(topk_all, dim3(unsigned((total + 255) / 256)), dim3(256), 0, s, x, total, len,
-                       idx, val);
+  // (a launch has fewer than 2^32 threads: the grid ends at 2^30 and goes on from
+  // there, and so many long rows take the smaller workgroup)
+  if (int64_t(k) == len) {
+    const int64_t grid = (total + 255) / 256, most = int64_t(1) << 22;
+    hipLaunchKernelGGL(topk_all, dim3(unsigned(grid < most ? grid : most)), dim3(256), 0, s, x, total,
+                       len, idx, val);
     return check_launch("topk_all");
   }
   // One workgroup for a row of a map's coefficients: 80 us for 512 rows of
@@ -750,7 +754,7 @@ int launch_topk(const float* x, int64_t rows, int64_t len, int k, int32_t* idx, 
   // 98,304 log-normal values against 33).
   if (len <= kSelMaxLen && !few_long_rows(rows, len, k)) {
     const size_t lds = (kSelBins + size_t((len + 31) >> 5)) * sizeof(unsigned);
-    if (len > 8192) {
+    if (len > 8192 && rows < (int64_t(1) << 22)) {
       hipLaunchKernelGGL(topk_select<1024>, dim3(unsigned(rows)), dim3(1024), lds, s, x, int(len), k,
                          idx, val);
     } else {

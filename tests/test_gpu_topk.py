@@ -53,3 +53,33 @@ def test_topk_ways(rrt, rows, length, k, kind):
         want = topk_abs(x[r], k)
         assert np.array_equal(idx[r], want), (r, int((idx[r] != want).sum()))
         assert np.array_equal(val[r].view(np.uint32), x[r][want].view(np.uint32))
+
+
+def room(gib):
+    torch.cuda.empty_cache()
+    if torch.cuda.mem_get_info()[0] < gib * 2**30:
+        pytest.skip(f"needs {gib} GiB of device memory")
+
+
+def test_topk_all_past_a_launch(rrt):
+    """k = len of more values than one launch has threads (2^32)."""
+    room(70)
+    rows, length = (1 << 26) + 3, 64
+    x = torch.empty((rows, length), device="cuda").uniform_()
+    idx, val = rrt.topk(x, length)
+    assert torch.equal(val, x)
+    del val, x
+    assert bool((idx == torch.arange(length, dtype=torch.int32, device="cuda")).all())
+
+
+def test_topk_rows_past_a_launch(rrt):
+    """As many rows as 1,024 threads each are 2^32."""
+    room(160)
+    rows, length = 1 << 22, 8193
+    x = torch.zeros((rows, length), device="cuda")
+    at = (torch.arange(rows, device="cuda") * 7919 % length).view(-1, 1)
+    x.scatter_(1, at, -2.0)
+    idx, val = rrt.topk(x, 1)
+    del x
+    assert torch.equal(idx.long(), at)
+    assert bool((val == -2.0).all())
