@@ -315,13 +315,15 @@ __device__ __forceinline__ unsigned latlong_source(const LLTab& t, int i, int jc
   return latlong_index<LOGH>(row, col);
 }
 
-// The same rule without the searches, for a unit (cb, sb).  A count #{k : x <=
-// C_k} is the angle acos x in rows (or columns) but for the boundary it rounds
-// to: an estimate of the angle less than half a texel off names that boundary,
-// and one comparison with it decides, as the search would.  acos x =
-// sqrt(1 - |x|) (c0 + c1 |x| + c2 x^2), mirrored for x < 0: a minimax fit (3.3e-4, 0.054
-// rows at H = 512); next to the poles the binary32 roundings of x add less than
-// 7e-4 (0.11 rows).
+// The same rule without the searches, for (cb, sb) of any length up to
+// kEstimated.  A count #{k : x <= C_k} is the angle acos x in rows (or columns)
+// but for the boundary it rounds to: an estimate of the angle less than half a
+// texel off names that boundary, and one comparison with it decides, as the
+// search would.  acos x = sqrt(1 - |x|) (c0 + c1 |x| + c2 x^2), mirrored for x < 0
+// (the form of Hastings' approximation, with a minimax fit of its own: 3.3e-4,
+// 0.054 rows at H = 512), and 0 or pi beyond 1, which only a q_y that is no
+// cosine reaches; next to the poles the binary32 roundings of x = q_z / rho add less
+// than 7e-4 (0.11 rows).
 // The azimuth's comparison takes rho = s rsq(s), s = q_x^2 + q_z^2, within 1.8e-7 of the
 // square root of s; correctly rounded, rho and C_k rho differ from it by at
 // most 3.6e-7 rho, so a comparison closer than 4e-7 rho is made again with the
@@ -331,7 +333,10 @@ __device__ __forceinline__ unsigned latlong_source(const LLTab& t, int i, int jc
 // and dependent LDS reads per texel, the estimates 48 instructions in all and
 // two independent reads.  50,000 vertices at H = 128: 3.26 -> 2.01 ms (the rounded rho
 // for every texel 2.15; the whole search again for a close one 2.69), and 1.13 ms
-// since blocks of weight zero are left out.
+// since blocks of weight zero are left out (3.54 in the searches, one texel after
+// the other, which only pairs past kEstimated or not finite take).
+constexpr float kEstimated = 0x1p20f;  // nothing overflows up to here
+
 template <int LOGH, bool EXACT>
 __device__ __forceinline__ unsigned latlong_fast(const LLTab& t, int i, int jc, float cb, float sb,
                                                  int sa, float& gap) {
@@ -350,7 +355,7 @@ __device__ __forceinline__ unsigned latlong_fast(const LLTab& t, int i, int jc, 
   // nearest boundary of the angle of x in texels
   auto boundary = [](float x) {
     const float ax = fabsf(x);
-    const float root = __builtin_amdgcn_sqrtf(fabsf(1.0f - ax));
+    const float root = __builtin_amdgcn_sqrtf(__builtin_amdgcn_fmed3f(1.0f - ax, 0.0f, 1.0f));
     const float poly = __builtin_fmaf(
         __builtin_fmaf(0.05139111f * kRows, ax, -0.20549912f * kRows), ax, 1.57047056f * kRows);
     const float from_equator = __builtin_fmaf(-root, poly, 0.5f * float(H));
@@ -374,10 +379,10 @@ template <int LOGH, int Q, int TS, int T>
 __device__ __forceinline__ void latlong_gather(float (&val)[T][T], const LLTab& tab,
                                                __amdgpu_buffer_rsrc_t src, int face, int by,
                                                int bx, int gy, int gx, float cb, float sb, int sa,
-                                               int sc, bool unit) {
+                                               int sc, bool estimated) {
   constexpr int n = 1 << LOGH;
   const int i0 = by * Q + gy, j0 = face * n + bx * Q + gx + sc;
-  if (unit) {
+  if (estimated) {
 #pragma unroll
     for (int a = 0; a < T; ++a) {
       float gap = 1.0f;
@@ -395,7 +400,7 @@ __device__ __forceinline__ void latlong_gather(float (&val)[T][T], const LLTab& 
       }
     }
   } else {
-    // not a rotation: the searches
+    // not finite, or past kEstimated: the searches
 #pragma unroll 1
     for (int e = 0; e < T * T; ++e) {
       const float x = load_src(src, latlong_source<LOGH>(tab, i0 + TS * (e / T),
@@ -890,7 +895,7 @@ __global__ __launch_bounds__((MODE ? kMostWaves : 1) * kThreads, CHAIN || LOGN ?
   LLTab tab = {};
   float llcb = 0.0f, llsb = 0.0f;
   int llsa = 0, llsc = 0;
-  [[maybe_unused]] bool unit = false;  // (cos b, sin b) as it should be
+  [[maybe_unused]] bool estimated = false;
   if constexpr (LL) {
     float* t = reinterpret_cast<float*>(wave_lds + p.ll_tab_off);
     for (int k = lane; k < 7 * n; k += kThreads) t[k] = p.ll_grid[k];
@@ -902,7 +907,7 @@ __global__ __launch_bounds__((MODE ? kMostWaves : 1) * kThreads, CHAIN || LOGN ?
     tab = {t, t + n, t + 2 * n, t + 4 * n, t + 6 * n};
     llcb = __int_as_float(__builtin_amdgcn_readfirstlane(__float_as_int(p.ll_elev[2 * v])));
     llsb = __int_as_float(__builtin_amdgcn_readfirstlane(__float_as_int(p.ll_elev[2 * v + 1])));
-    unit = fabsf(llcb * llcb + llsb * llsb - 1.0f) <= 1e-6f;
+    estimated = fabsf(llcb) <= kEstimated && fabsf(llsb) <= kEstimated;
     llsa = __builtin_amdgcn_readfirstlane(p.ll_shift[2 * v]) & (2 * n - 1);
     llsc = __builtin_amdgcn_readfirstlane(p.ll_shift[2 * v + 1]) & (2 * n - 1);
     wave_sync();
@@ -1075,7 +1080,7 @@ __global__ __launch_bounds__((MODE ? kMostWaves : 1) * kThreads, CHAIN || LOGN ?
               if (owns_tile) {
                 float val[T][T];
                 latlong_gather<LOGN, Q, TS, T>(val, tab, src, face, by, bx, gy, gx, llcb, llsb, llsa,
-                                               llsc, unit);
+                                               llsc, estimated);
                 if (full) {
 #pragma unroll
                   for (int a = 0; a < T; ++a)
