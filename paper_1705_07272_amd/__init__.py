@@ -38,11 +38,16 @@ def s11_words(nnz):
     return (11 * nnz + 31) // 32
 
 
+# The current stream's handle without the Stream object that
+# torch.cuda.current_stream() makes for it (host time is what the smallest calls
+# take); torch keeps it to itself, so it may be absent.
+_raw_stream = getattr(torch._C, "_cuda_getCurrentRawStream", None)
+
+
 def _stream():
-    # the current stream of the current device, without the Stream object that
-    # torch.cuda.current_stream() makes for it (host time is what the smallest
-    # calls take)
-    return ctypes.c_void_p(torch._C._cuda_getCurrentRawStream(torch.cuda.current_device()))
+    if _raw_stream is None:
+        return ctypes.c_void_p(torch.cuda.current_stream().cuda_stream)
+    return ctypes.c_void_p(_raw_stream(torch.cuda.current_device()))
 
 
 def _address(t, name, dtype=None):
