@@ -825,6 +825,15 @@ int launch_mlp_forward(const void* w, const float* b, const void* x, int64_t B, 
     f.a[l] = k.a[l];
   }
   f.out = out;
+  // the launch reads x while it writes out: an x inside out is copied first, to
+  // the space of a gradient
+  const size_t xbytes = size_t(B) * RRT_MLP_IN * 2, obytes = size_t(B) * RRT_MLP_OUT * 4;
+  const uintptr_t xa = reinterpret_cast<uintptr_t>(x), oa = reinterpret_cast<uintptr_t>(out);
+  if (xa < oa + obytes && oa < xa + xbytes) {
+    const hipError_t e = hipMemcpyAsync(k.dz[0], x, xbytes, hipMemcpyDeviceToDevice, s);
+    if (e != hipSuccess) return fail(RRT_ERR_DEVICE, "forward: %s", hipGetErrorString(e));
+    f.x = k.dz[0];
+  }
   hipLaunchKernelGGL(forward_kernel, dim3(unsigned((B + kRowTile - 1) / kRowTile)), dim3(512), 0, s, f);
   return check_launch("forward");
 }

@@ -46,3 +46,17 @@ def test_row_tiles(rrt, B):
     dWs, dbs = ref.backward(Wq, cache, dout.cpu().numpy().astype(np.float64))
     assert _rel(grads[0].cpu().numpy(), np.concatenate([d.ravel() for d in dWs])) <= 3e-2
     assert _rel(grads[1].cpu().numpy(), np.concatenate(dbs)) <= 3e-2
+
+
+@pytest.mark.parametrize("B,at", [(33, 0), (4096, 0), (4096, 1024), (20000, 3072)])
+def test_x_inside_out(rrt, B, at):
+    """The encoded batch may lie in the array that the result is written to
+    (`at`: 16-byte units from its start)."""
+    _, _, w_dev, b_dev = _net(6)
+    g = np.random.default_rng(B)
+    x = _bf16(ref.encode(g.uniform(-1, 1, size=(B, 6)))).cuda()
+    want = rrt.mlp_forward(w_dev, b_dev, x)
+    out = torch.empty((B, ref.OUT), device="cuda")
+    inside = out.view(-1).view(torch.bfloat16)[8 * at:8 * at + x.numel()].view(x.shape)
+    inside.copy_(x)
+    assert torch.equal(rrt.mlp_forward(w_dev, b_dev, inside, out=out), want)
