@@ -1491,8 +1491,7 @@ int launch_q(const RelightParams& prm_in, int64_t nvert, hipStream_t s) {
   // Up to a round of waves (one of them per vertex leaves the chip idle and
   // waiting for its own loads) a vertex is divided among the waves of a
   // workgroup: a dense row by faces, which have the same work; other rows by
-  // blocks, at most as many waves as one face (both squares) has blocks, whatever
-  // the factors: a triple product with ones is the double product bit for bit.
+  // blocks, at most as many waves as one face (both squares) has blocks.
   // Every wave lists the row for itself, which only pays while the chip is not
   // full (of registers; of LDS where every wave copies the lat-long tables, too:
   // 2,560 vertices at H = 256 took 412 us in two waves each, 373 in one, while

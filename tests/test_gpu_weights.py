@@ -108,3 +108,27 @@ def test_triple_zero_factors(rrt, kind):
         dense[v] = haar_forward(texels).ravel()
     ref = relight(li, lv, n, rot, None, None, dense, return_scale=True)
     check_frames(out.cpu().numpy(), ref, rel_l2=False)
+
+
+@pytest.mark.parametrize("n", [32, 64, 128])
+def test_triple_with_ones(rrt, n):
+    """A triple product whose factor is one everywhere is the double product,
+    each within its FP32 bound of the same sum (a block without entries inside
+    is summed in another order, so not bit for bit)."""
+    from oracle.relight import relight
+    from scenes.scene import random_rotations
+    V, g = 6, np.random.default_rng(n)
+    li, lv = lighting(n, g)
+    rot = random_rotations(n, V)
+    wide = g.integers(0, max(n // 16, 2), (V, 40, 2))
+    ti = np.stack([np.unique(np.concatenate([
+        (g.integers(0, 6, 40) * n + wide[v, :, 0]) * n + wide[v, :, 1],
+        g.choice(6 * n * n, 200, replace=False)]))[:200] for v in range(V)]).astype(np.int32)
+    tv = g.normal(size=ti.shape).astype(np.float32)
+    args = (n, dev(li), dev(lv), dev(rot), dev(ti), dev(tv))
+    double = rrt.relight(*args).cpu().numpy()
+    triple = rrt.relight(*args, brdf=torch.ones(1, 6, n, n, device="cuda"),
+                         material=torch.zeros(V, dtype=torch.int32, device="cuda")).cpu().numpy()
+    ref, s = relight(li, lv, n, rot, None, ti, tv, return_scale=True)
+    check_frames(double, (ref, s), rel_l2=False)
+    assert np.all(np.abs(triple - double) <= 2 * (1e-5 * np.abs(ref) + 2e-7 * s))
