@@ -25,9 +25,9 @@
 //     entries inside the block read the image; those of the levels above the
 //     blocks are turned into a weight per block (their inverse transform, once
 //     per vertex, FP64) that multiplies the block's sum, each lane its own
-//     texels' share; products are accumulated per lane and reduced with lane
-//     shuffles (a dense row has no list: each image and grid position reads
-//     its own entry);
+//     texels' share; products are accumulated per lane, in FP32 inside a block
+//     and in FP64 over the blocks, and reduced with lane shuffles (a dense row
+//     has no list: each image and grid position reads its own entry);
 //   * a block that holds no listed entry only counts through its sum and skips
 //     the image, the levels and the entry scan.
 //
@@ -227,7 +227,7 @@ struct RelightParams {
   int dtype;
   int comp;
   int listed;       // entries of each row listed in LDS: min(nnz, kMaxListed)
-  int group_faces;  // faces whose block sums fit in LDS together
+  int group_faces;  // faces whose block weights fit in LDS together
   const float4* blocks;  // chain rule: (S, H, V, D) of every 2x2 source block;
                          // else kMapFinite per tile of the source map (rrt_internal.h)
   const float* brdf;        // triple product: [nmat][6 n^2] texel factor, or NULL
@@ -1008,9 +1008,9 @@ __global__ __launch_bounds__((MODE ? kMostWaves : 1) * kThreads, CHAIN || LOGN ?
           }
           wave_sync();
         }
-        if constexpr (!DENSE && (Q < kBlock || LOGN == 5)) {
+        if constexpr (!DENSE && (Q < kBlock || LOGN == 5 || CHAIN)) {
           // one block per face: no level that marks a zero weight
-          if (lane < nfg && !uncovered(gW[lane])) gW[lane] = reached(gW[lane]);
+          if (G == 1 && lane < nfg && !uncovered(gW[lane])) gW[lane] = reached(gW[lane]);
           wave_sync();
         }
       }

@@ -110,10 +110,10 @@ def test_prepared(rrt, way):
     check(rrt.relight_prepared(light, dev(rot), dev(ti), dev(tv)), want)
 
 
-def test_chain_rule(rrt):
+@pytest.mark.parametrize("n", [32, 64])
+def test_chain_rule(rrt, n):
     from oracle.chain import chain_rotate
     from oracle.sphere import quantise_rotation
-    n = 64
     _, li, lv, P, rot, ti, tv = scene(n)
     want = finite(P, lambda m, v: chain_rotate(m, quantise_rotation(rot[v], n)), ti, tv)
     check(rrt.relight(n, dev(li), dev(lv), dev(rot), dev(ti), dev(tv), chain_rule=True), want)
