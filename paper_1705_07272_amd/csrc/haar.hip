@@ -247,7 +247,7 @@ __global__ __launch_bounds__(kThreads) void haar_inv_tiles(const float* coef, co
 // per side barriers); the staged way clears, scatters and inverts a dense map in
 // three or four launches.  13 KiB of LDS and few registers, to run beside relight waves.
 // The call that prepares a lighting of 1,024 entries at n = 128 takes 7.2 us
-// (the host's time; 4.9 us in a graph) instead of 18.7, at n = 16 7.2 instead of
+// (the host's time; 4.8 us in a graph) instead of 18.7, at n = 16 7.2 instead of
 // 14.9.  (Plain stores without the entry number and no flags: 4.6 us in a graph,
 // 11.3 for 16,384 entries at n = 64 against 11.6.)
 constexpr int kMapTile = 32;
@@ -255,10 +255,11 @@ constexpr int kMapMost = 16384;                    // entries
 constexpr int64_t kMapEntries = int64_t(1) << 22;  // tiles x entries of the one-launch way
 
 // The flag of a tile, a byte from each of the workgroup's four waves (without a
-// barrier, which takes 0.6 us here).
-__device__ __forceinline__ void flag_tile(unsigned* flag, bool finite) {
+// barrier, which takes 0.6 us here); most: the largest magnitude bits of the
+// thread's texels.
+__device__ __forceinline__ void flag_tile(unsigned* flag, unsigned most) {
   static_assert(kThreads == 256, "four waves");
-  const bool all = __ballot(!finite) == 0;
+  const bool all = __ballot(most >= 0x7f800000u) == 0;
   const int wave = threadIdx.x >> 6;
   if ((threadIdx.x & 63) == 0)
     reinterpret_cast<uint8_t*>(flag)[wave] = all ? uint8_t(kMapFinite >> (8 * wave)) : uint8_t(0);
@@ -333,16 +334,16 @@ __global__ __launch_bounds__(kThreads) void source_map_kernel(const int32_t* __r
   for (int B = Q; B >= 2; B >>= 1) level(tile, coef, Q, B);
   float* dst = pix + (int64_t(face) << (2 * logn));
   const int row0 = ty * Q, col0 = tx * Q;
-  bool finite = true;
+  unsigned most = 0;
   for (int e = threadIdx.x; e < Q * Q; e += kThreads) {
     const int r = strips ? (e >> 3) & (Q - 1) : e >> logq;
     const int c = strips ? ((e >> (logq + 3)) << 3) + (e & 7) : e & (Q - 1);
     const float x = tile[r * Q + c];
-    finite = finite && __builtin_isfinite(x);
+    most = max(most, __float_as_uint(x) & 0x7fffffffu);
     dst[strips ? int64_t((col0 + c) >> 3) * 8 * n + 8 * (row0 + r) + (c & 7)
                : int64_t(row0 + r) * n + col0 + c] = x;
   }
-  flag_tile(flags + blk, finite);
+  flag_tile(flags + blk, most);
 }
 
 // The flags of a finished map (its layout does not matter: a tile is that many
@@ -351,9 +352,9 @@ __global__ __launch_bounds__(kThreads) void source_map_kernel(const int32_t* __r
 __global__ __launch_bounds__(kThreads) void map_flags_kernel(const float* __restrict__ pix, int texels,
                                                              unsigned* __restrict__ flags) {
   const float* t = pix + int64_t(blockIdx.x) * texels;
-  bool finite = true;
-  for (int e = threadIdx.x; e < texels; e += kThreads) finite = finite && __builtin_isfinite(t[e]);
-  flag_tile(flags + blockIdx.x, finite);
+  unsigned most = 0;
+  for (int e = threadIdx.x; e < texels; e += kThreads) most = max(most, __float_as_uint(t[e]) & 0x7fffffffu);
+  flag_tile(flags + blockIdx.x, most);
 }
 
 }  // namespace

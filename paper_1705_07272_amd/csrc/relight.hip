@@ -228,8 +228,9 @@ struct RelightParams {
   int comp;
   int listed;       // entries of each row listed in LDS: min(nnz, kMaxListed)
   int group_faces;  // faces whose block weights fit in LDS together
-  const float4* blocks;  // chain rule: (S, H, V, D) of every 2x2 source block;
-                         // else kMapFinite per tile of the source map (rrt_internal.h)
+  const float4* blocks;  // chain rule: (S, H, V, D) of every 2x2 source block (the first S
+                         // may be kMapUnsure); else kMapFinite per tile of the source map
+                         // (rrt_internal.h)
   const float* brdf;        // triple product: [nmat][6 n^2] texel factor, or NULL
   const int32_t* material;  // [V] row of brdf, or NULL (row 0)
   int nmat;
@@ -692,6 +693,11 @@ __device__ __forceinline__ void tile_levels_from(float (&g)[T][T]) {
   }
 }
 
+// S of the 2x2 source block with texels a b / c d.
+__device__ __forceinline__ float block_s(float a, float b, float c, float d) {
+  return 0.5f * ((a + b) + (c + d));
+}
+
 // In-face and major components (sc, tc, D) of v for source face f:
 //   +X (-z,-y, x)  -X (z,-y,-x)  +Y (x, z, y)  -Y (x,-z,-y)  +Z (x,-y, z)  -Z (-x,-y,-z)
 __device__ __forceinline__ float3 face_components(int f, float x, float y, float z) {
@@ -861,11 +867,16 @@ __global__ __launch_bounds__((MODE ? kMostWaves : 1) * kThreads, CHAIN || LOGN ?
   const int nnz = row_valid ? p.nnz : 0;
   const int listed = row_valid ? p.listed : 0;
 
-  // the source map's flags (where the chain rule has its blocks, which no flag
-  // looks like; a dense row reaches every texel of its faces)
+  // the source map's flags, or what the chain rule's blocks have instead (which
+  // look like no flag; a dense row reaches every texel of its faces)
   [[maybe_unused]] bool finite = false;
-  if constexpr (!CHAIN && (!DENSE || BRDF))
+  [[maybe_unused]] float first_s = 0.0f;  // chain rule, not finite: S of the first block
+  if constexpr (CHAIN) {
+    finite = __builtin_amdgcn_readfirstlane(__float_as_int(p.blocks[0].x)) != int(kMapUnsure);
+    if (!finite) first_s = block_s(p.src[0], p.src[1], p.src[8], p.src[9]);
+  } else if constexpr (!DENSE || BRDF) {
     finite = tiles_finite<NF << (LOGN > 5 ? 2 * (LOGN - 5) : 0)>(p.blocks, lane);
+  }
 
   // faces touched by this vertex's transport row (a dense row: all)
   unsigned m = 0;
@@ -1100,6 +1111,7 @@ __global__ __launch_bounds__((MODE ? kMostWaves : 1) * kThreads, CHAIN || LOGN ?
               if (SUM_ONLY && !full) {
                 // only the block's sum: twice the source blocks' S
                 float sv[2][2];
+                unsigned ats[2][2];
 #pragma unroll
                 for (int a = 0; a < 2; ++a)
 #pragma unroll
@@ -1107,11 +1119,18 @@ __global__ __launch_bounds__((MODE ? kMostWaves : 1) * kThreads, CHAIN || LOGN ?
                     const float3 d = dir_mad(ax.mU, float(16 * b), ax.mV, float(16 * a), rb);
                     const unsigned at = source_texel_scaled<4>(d.x, d.y, d.z, logn - 1);
                     sv[a][b] = __uint_as_float(__builtin_amdgcn_raw_buffer_load_b32(blk, int(at), 0, 0));
+                    ats[a][b] = at;
                   }
+                if (!finite) {
+#pragma unroll
+                  for (int k = 0; k < 4; ++k)
+                    if (ats[k >> 1][k & 1] == 0) sv[k >> 1][k & 1] = first_s;
+                }
                 lane_sum = 2.0f * ((sv[0][0] + sv[0][1]) + (sv[1][0] + sv[1][1]));
               } else {
               float4 cf[2][2];
               int sf[2][2];
+              unsigned ats[2][2];
 #pragma unroll
               for (int a = 0; a < 2; ++a)
 #pragma unroll
@@ -1122,7 +1141,13 @@ __global__ __launch_bounds__((MODE ? kMostWaves : 1) * kThreads, CHAIN || LOGN ?
                   const u32x4_t raw = __builtin_amdgcn_raw_buffer_load_b128(blk, int(at), 0, 0);
                   cf[a][b] = make_float4(__uint_as_float(raw.x), __uint_as_float(raw.y),
                                          __uint_as_float(raw.z), __uint_as_float(raw.w));
+                  ats[a][b] = at;
                 }
+              if (!finite) {
+#pragma unroll
+                for (int k = 0; k < 4; ++k)
+                  if (ats[k >> 1][k & 1] == 0) cf[k >> 1][k & 1].x = first_s;
+              }
               const float3 ex = make_float3(2.0f * ax.mU.x, 2.0f * ax.mU.y, 2.0f * ax.mU.z);
               const float3 ey = make_float3(2.0f * ax.mV.x, 2.0f * ax.mV.y, 2.0f * ax.mV.z);
 #pragma unroll
@@ -1329,11 +1354,22 @@ __global__ void scatter_light(const int32_t* __restrict__ idx, const void* __res
 }
 
 // Orthonormal (S, H, V, D) of every 2x2 block of the source map, for the
-// chain-rule rotation: blocks[face][bi][bj].
-__global__ void source_blocks_kernel(const float* __restrict__ src, int logn,
-                                     float4* __restrict__ blocks) {
+// chain-rule rotation: blocks[face][bi][bj].  They take the place of the map's
+// `tiles` flags: the first workgroup, which alone writes there (for up to 4
+// floats x 256 threads of them), reads those first and leaves kMapUnsure in the
+// first S unless all of them are kMapFinite.
+__global__ __launch_bounds__(256) void source_blocks_kernel(const float* __restrict__ src, int logn,
+                                                            int tiles, float4* blocks) {
   const int hl = logn - 1;
   const int q = blockIdx.x * blockDim.x + threadIdx.x;
+  bool finite = true;
+  if (blockIdx.x == 0) {
+    const unsigned* flags = reinterpret_cast<const unsigned*>(blocks);
+    finite = tiles <= 1024;
+    if (finite)
+      for (int k = threadIdx.x; k < tiles; k += 256) finite = finite && flags[k] == kMapFinite;
+    finite = __syncthreads_and(finite);
+  }
   if (q >= 6 << (2 * hl)) return;
   const int f = q >> (2 * hl), bi = (q >> hl) & ((1 << hl) - 1), bj = q & ((1 << hl) - 1);
   // the source map is in strips of eight columns (n >= 32 here): the block's
@@ -1341,8 +1377,9 @@ __global__ void source_blocks_kernel(const float* __restrict__ src, int logn,
   const unsigned at = strip_offset(unsigned(f), unsigned(2 * bi), unsigned(2 * bj), logn);
   const float a = src[at], b = src[at + 1];
   const float c = src[at + 8], d = src[at + 9];
-  blocks[q] = make_float4(0.5f * ((a + b) + (c + d)), 0.5f * ((a - b) + (c - d)),
-                          0.5f * ((a + b) - (c + d)), 0.5f * ((a - b) - (c - d)));
+  blocks[q] = make_float4(finite || q != 0 ? block_s(a, b, c, d) : __uint_as_float(kMapUnsure),
+                          0.5f * ((a - b) + (c - d)), 0.5f * ((a + b) - (c + d)),
+                          0.5f * ((a - b) - (c - d)));
 }
 
 // The lat-long rule's tables: binary32 roundings of sin / cos of the row and
@@ -1615,7 +1652,7 @@ int launch_scatter_light(const int32_t* idx, const void* val, int dtype, int k, 
 int launch_source_blocks(const float* src, int n, float* blocks, hipStream_t s) {
   const int total = 6 * (n / 2) * (n / 2);
   hipLaunchKernelGGL(source_blocks_kernel, dim3(unsigned((total + 255) / 256)), dim3(256), 0, s,
-                     src, ilog2(n), reinterpret_cast<float4*>(blocks));
+                     src, ilog2(n), 6 * (n / kBlock) * (n / kBlock), reinterpret_cast<float4*>(blocks));
   return check_launch("source_blocks");
 }
 

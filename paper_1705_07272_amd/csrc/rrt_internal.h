@@ -53,6 +53,9 @@ int launch_topk(const float* x, int64_t rows, int64_t len, int k, int32_t* idx, 
 // below n = 32) without an infinite or NaN texel: a signalling NaN, which no
 // arithmetic returns, so no word of the chain rule's blocks is taken for it.
 constexpr unsigned kMapFinite = 0x7fa5a5a5u;
+// S of the chain rule's first block where the map is not known to be finite
+// (the block's own S then follows from its texels).
+constexpr unsigned kMapUnsure = 0x7fb4b4b4u;
 
 // Source map pix of a sparse lighting: scatter and inverse transform, in one
 // launch where the map and the entries allow, else through the dense staging

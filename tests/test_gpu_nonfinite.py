@@ -151,3 +151,39 @@ def test_latlong(rrt, H, repeat):
     want = finite(P, lambda m, v: rotate(m, *elev[v], *shift[v]), ti, tv)
     a = [np.concatenate([x] * repeat) for x in (elev, shift, ti, tv)]
     check(rrt.relight_latlong(H, dev(li), dev(lv), *map(dev, a)), want)
+
+
+@pytest.mark.parametrize("n,bad", [(32, True), (64, True), (128, False), (512, False)])
+def test_chain_rule_first_block(rrt, n, bad):
+    """The chain rule's first source block, in whose place a map with an
+    infinite texel (and any at n = 512) is marked, against the FP64 checker's
+    bound: vertices turned by up to 0.2 rad see it in face 0."""
+    from cases import chain_reference
+    from test_gpu_parity import check_frames
+    g, V = np.random.default_rng(n), 3 if n > 128 else 8
+    q = np.arange(4)
+    li = np.concatenate([[0, 1, n, n + 1], ((n // 2 + q[:, None]) * n + q).ravel(),
+                         (q[:, None] * n + n // 2 + q).ravel(), [n * n + (n - 1) * n + n // 2]])
+    lv = g.normal(size=li.size) * 4.0
+    lv[-1] = np.inf if bad else 1.0
+    order = np.argsort(li)
+    li, lv = li[order].astype(np.int32), lv[order].astype(np.float32)
+    a = g.uniform(-0.2, 0.2, V)
+    a[0] = 0.0
+    rot = np.zeros((V, 3, 3))
+    for v in range(V):
+        i, j = (v % 3), (v + 1) % 3
+        rot[v] = np.eye(3)
+        rot[v, i, i] = rot[v, j, j] = np.cos(a[v])
+        rot[v, i, j], rot[v, j, i] = -np.sin(a[v]), np.sin(a[v])
+    row = np.concatenate([[0, 2, 2 * n], (q[:, None] * n + n // 2 + q).ravel(),
+                          ((n // 2 + q[:, None]) * n + q).ravel()])
+    ti = np.sort(np.tile(row, (V, 1)), 1).astype(np.int32)
+    tv = g.normal(size=ti.shape).astype(np.float32)
+    rot = rot.astype(np.float32)
+    out = rrt.relight(n, dev(li), dev(lv), dev(rot), dev(ti), dev(tv), chain_rule=True)
+    with np.errstate(all="ignore"):
+        ref = chain_reference(dict(n=n, light_idx=li, light_val=lv, vert_rot=rot, frame_rot=None,
+                                   t_idx=ti, t_val=tv))
+    assert np.isfinite(ref[0]).all() and np.all(ref[1] > 0.0)
+    check_frames(out.cpu().numpy(), ref, rel_l2=False)
