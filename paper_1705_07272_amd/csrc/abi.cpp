@@ -178,6 +178,8 @@ int rrt_haar_phase_shift_workspace(int n, int nrot, size_t* bytes) {
   if (!bytes) return fail(RRT_ERR_INVALID, "phase_shift_workspace: null bytes");
   if (!valid_n(n, 2) || nrot < 0) return fail(RRT_ERR_INVALID, "phase_shift_workspace: bad sizes");
   const size_t cells = size_t(6) * n * n;
+  // the source map, and space for the rotated maps, which are not written any
+  // more: the size stays what callers have provided
   *bytes = align256(cells * sizeof(float)) + align256(cells * sizeof(float) * size_t(nrot));
   return RRT_OK;
 }
@@ -326,8 +328,8 @@ int rrt_relight(const rrt_light* L, const rrt_rotations* R, const rrt_transport*
   return rrt_relight_prepared(L, R, T, radiance, flags, ws, ws_bytes, stream);
 }
 
-// Workspace of the lat-long relight: [dense staging 2H^2 float][source map
-// 2H^2 float|half][rule tables 7H float]
+// Workspace of the lat-long relight: [dense staging 2H^2 float, then the
+// source map's flags][source map 2H^2 float][rule tables 7H float]
 struct LatLongWs {
   size_t dense_off, src_off, grid_off, total;
 };

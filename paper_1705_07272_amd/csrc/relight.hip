@@ -333,7 +333,7 @@ __device__ __forceinline__ unsigned latlong_source(const LLTab& t, int i, int jc
 // What bounds it: vector issue.  Two binary searches take 7 log2 H operations
 // and dependent LDS reads per texel, the estimates 48 instructions in all and
 // two independent reads.  50,000 vertices at H = 128: 3.26 -> 2.01 ms (the rounded rho
-// for every texel 2.15; the whole search again for a close one 2.69), and 1.13 ms
+// for every texel 2.15; the whole search again for a close one 2.69), and 1.12 ms
 // since blocks of weight zero are left out (3.54 in the searches, one texel after
 // the other, which only pairs past kEstimated or not finite take).
 constexpr float kEstimated = 0x1p20f;  // nothing overflows up to here
@@ -511,7 +511,7 @@ __device__ __forceinline__ void tile_level_above(float& s, float* img, int lane,
 // step with 50,000 vertices, n = 128, 256 coefficients, 0.639 -> 0.584 ms; 200,000
 // vertices, n = 256, 8.14 -> 7.21 ms; 12,500 vertices x 64 frames, n = 128, 9.03 ->
 // 8.07 ms.  With the weights of the levels above the blocks and the frames divided
-// among waves these three take 0.541, 7.00 and 6.82 ms: 21.5 vector instructions per
+// among waves these three take 0.546, 6.9 and 6.87 ms: 21.5 vector instructions per
 // texel in all (28.9 before), the texture data path busy 0.93 of the cycles.
 // ---------------------------------------------------------------------------
 constexpr int kMixed = 6;  // quarter_face: several faces
@@ -783,7 +783,7 @@ __device__ __forceinline__ int classify(int idx, int logn, int G, unsigned faces
 // elevation-plus-shift rotation of latlong_source) instead of a cube map.
 // The chain-rule variant is held to 5 waves per SIMD (96 VGPRs, a few
 // spilled): 0.430 -> 0.411 ms on the benchmark launch against 4 waves
-// unspilled (0.370 now); the lat-long variant held to 6 waves spills more and runs
+// unspilled (0.372 now); the lat-long variant held to 6 waves spills more and runs
 // slower, so it keeps its 5.  Sizes below 32 are held to 6 (80 VGPRs): 24,510
 // vertices x 12 frames at n = 16 680 -> 556 us against 4 waves.
 // LOGN: log2 n where the block is gathered in quarters (cube map, exact
@@ -1069,7 +1069,7 @@ __global__ __launch_bounds__((MODE ? kMostWaves : 1) * kThreads, CHAIN || LOGN ?
             const double weight = gW[gi] * (1.0 / Q);
             // nothing reads a block of weight zero (the part of a lobe's square
             // below the horizon, where the entries of the levels above cancel):
-            // 50,000 lat-long vertices at H = 128 2.01 -> 1.13 ms
+            // 50,000 lat-long vertices at H = 128 2.01 -> 1.12 ms
             if (!full && __ballot(!(fabs(weight) <= skipped)) == 0) continue;
             if constexpr (BRDF && QUARTERS) {
               // nor does one whose factor is zero everywhere (below the horizon)
@@ -1513,7 +1513,7 @@ int launch_q(const RelightParams& prm_in, int64_t nvert, hipStream_t s) {
   // of them, or leave the last round of the chip (kRoundWaves at a time) mostly
   // empty: the frames are divided until there are eight rounds.
   // 12,500 vertices x 64 frames at n = 128 (2.4 rounds undivided): 8.07 -> 7.21
-  // ms (6.82 now); the list is then built once for 16 frames.  Listing an entry
+  // ms (6.87 now); the list is then built once for 16 frames.  Listing an entry
   // takes about as long as 14 texels, so past the chip's first round a wave keeps
   // frames of 64 texels per listed entry: 24,510 vertices x 12 frames at n = 16 with 238
   // entries took 709 us in two waves each, 680 in one.
@@ -1533,10 +1533,10 @@ int launch_q(const RelightParams& prm_in, int64_t nvert, hipStream_t s) {
   // full (of registers; of LDS where every wave copies the lat-long tables, too:
   // 2,560 vertices at H = 256 took 412 us in two waves each, 373 in one, while
   // 1,280 rows of 600 at n = 128, whose lists fill the LDS, gain: 131 -> 82).
-  // A call with 300 vertices, one wave each and eight: n = 128 88 -> 33 us, n = 256
-  // 294 -> 104, triple product at n = 128 146 -> 54, lat-long at H = 128 86 -> 41,
-  // chain rule at n = 128 71 -> 35; 2,560 vertices at n = 128, one and two: 90 -> 61.
-  // 1,000 dense rows at n = 32: relight 49 -> 29 us, the whole step 69.5 -> 45.1.
+  // A call with 300 vertices, one wave each and eight: n = 128 88 -> 32 us, n = 256
+  // 294 -> 103, triple product at n = 128 146 -> 53, lat-long at H = 128 86 -> 41,
+  // chain rule at n = 128 71 -> 33; 2,560 vertices at n = 128, one and two: 90 -> 60.
+  // 1,000 dense rows at n = 32: relight 49 -> 29 us, the whole step 69.5 -> 44.9.
   prm.lds_wave = int((lds + 15) & ~size_t(15));
   const int64_t round =
       LL ? std::min(kRoundWaves, 256 * (int64_t(160 * 1024) / prm.lds_wave)) : kRoundWaves;
