@@ -102,7 +102,7 @@ def test_vertex_alone(rrt, n, kind):
 def test_frame_alone(rrt, n, nnz, F):
     """40 vertices in 16 to 65 frames (the parts of the frames times the
     vertices on both sides of 640, 1,280 and 2,560) have the values of calls
-    with one frame, and those of the FP64 checker."""
+    with one frame, and those of the FP64 oracle."""
     from oracle.relight import relight
     from scenes.scene import random_rotations
     g, V = np.random.default_rng(n), 40

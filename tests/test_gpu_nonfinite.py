@@ -1,5 +1,5 @@
 """Infinite and NaN lighting: a radiance is finite exactly where the FP64
-checker's is, i.e. where no entry of the row (of whatever value, a zero and
+oracle's is, i.e. where no entry of the row (of whatever value, a zero and
 entries that cancel among them) reaches a texel that is not, for blocks whose
 weight or factor is zero as for the others.
 """
@@ -156,7 +156,7 @@ def test_latlong(rrt, H, repeat):
 @pytest.mark.parametrize("n,bad", [(32, True), (64, True), (128, False), (512, False)])
 def test_chain_rule_first_block(rrt, n, bad):
     """The chain rule's first source block, in whose place a map with an
-    infinite texel (and any at n = 512) is marked, against the FP64 checker's
+    infinite texel (and any at n = 512) is marked, against the FP64 oracle's
     bound: vertices turned by up to 0.2 rad see it in face 0."""
     from cases import chain_reference
     from test_gpu_parity import check_frames
